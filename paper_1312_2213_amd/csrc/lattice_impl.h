@@ -1368,7 +1368,6 @@ static hipError_t launch_lpc(int lpc, int threads, const LatticeArgs &a, hipStre
     case 1: return launch_variant<MODEL, L, LAYOUT, 1>(threads, a, s);
     case 2: return launch_variant<MODEL, L, LAYOUT, 2>(threads, a, s);
     case 4: return launch_variant<MODEL, L, LAYOUT, 4>(threads, a, s);
-    case 16: return launch_variant<MODEL, L, LAYOUT, 16>(threads, a, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -31,9 +31,11 @@ struct LatticeArgs {
     // row e = (E + 2N) / 4 and the magnetisation bin after each recorded sweep
     unsigned long long *em;
     unsigned long long *accepts; // accepted moves of the recorded sweeps, or null
-    // or null: one histogram [n_bins] per block of chains (the plain launch's
-    // workgroups, chains [k * cpb, (k + 1) * cpb)), for jackknife errors
+    // or null: one histogram [n_bins] per block of hist_block_chains chains
+    // (chains [k * h, (k + 1) * h)), for jackknife errors
     unsigned long long *hist_blocks;
+    int32_t hist_block_chains;
+    int32_t layout;             // storage of Ising / MUMA spins (tile kernels)
 };
 
 struct LatticeInitArgs {
@@ -84,9 +86,11 @@ __host__ __device__ inline int words_per_row(int L, int layout) { return layout 
 
 // Launchers (lattice.hip).
 hipError_t launch_lattice_init(const LatticeInitArgs &a, hipStream_t s);
-// threads per block in {64, 128, 256}; lpc lanes per chain in {1, 2, 4, 16}
+// threads per block in {64, 128, 256, 512}; lpc lanes per chain in {1, 2, 4}
 hipError_t launch_lattice_sweeps(int model, int L, int layout, int lpc, int threads, const LatticeArgs &a,
                                  hipStream_t s);
+// one wavefront per chain, `chains` (1..16) of them per block
+hipError_t launch_lattice_tiles(int model, int L, int chains, const LatticeArgs &a, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, hipStream_t s);
 // host: device address of page-locked host memory (hipHostGetDevicePointer)
 hipError_t launch_drain_u64(unsigned long long *p, unsigned long long *host, int64_t n, hipStream_t s);

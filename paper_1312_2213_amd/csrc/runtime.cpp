@@ -86,6 +86,16 @@ static size_t align256(size_t x) { return (x + 255u) & ~(size_t)255u; }
 // ---------------------------------------------------------------------------
 // Geometry of a configuration
 // ---------------------------------------------------------------------------
+// Most chains of a run that takes the one-wavefront-per-chain kernels by
+// default.  Their rate stops growing once every SIMD has four wavefronts
+// (4096 chains), that of 1 to 4 lanes per chain grows until the lanes fill
+// the chip.  Measured, 1e9 attempts/s, a wavefront / the best of 1, 2 and 4
+// lanes per chain: at 4096 chains Ising L = 64 206 / 100, L = 16 138 / 79,
+// MUMA L = 32 241 / 90, Potts q = 8 L = 48 170 / 59, L = 16 151 / 53; at 8192
+// Ising L = 64 182 / 200, L = 16 137 / 158, MUMA L = 32 251 / 179, Potts
+// L = 48 182 / 117, L = 16 158 / 107.
+static const long kTileMaxChains = 4096;
+
 static int bin_step(int model) { return model == kIsing ? 4 : (model == kPotts ? 1 : 2); }
 
 static int n_cols_of(int model) { return model == kIsing ? 5 : (model == kPotts ? 9 : 10); }
@@ -150,6 +160,8 @@ int muca_geometry(const muca_config *c, Geometry *g)
     if (lpc != 1 && lpc != 2 && lpc != 4 && lpc != 16)
         return muca_fail(MUCA_E_ARG, "lanes_per_chain %d not in {1, 2, 4, 16}", lpc);
     g->lpc = lpc;
+    if (c->lanes_per_chain == 16 || (c->lanes_per_chain == 0 && (long)g->c_pad <= kTileMaxChains))
+        g->tile_chains = 16;
     // default: 256-thread blocks, so a block that stages the threshold table
     // in LDS (one block per CU) still carries four wavefronts of work; at
     // init, 512 where that table leaves room for one block per CU and the
@@ -333,6 +345,15 @@ try {
                 g.cpb = 512;
         }
     }
+    if (g.tile_chains) {
+        // as many workgroups as there are CUs, down to one wavefront per SIMD
+        int dev = 0, cus = 256;
+        if (hipGetDevice(&dev) == hipSuccess)
+            (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        g.tile_chains = std::min(16, g.cpb / g.lpc);
+        while (c->chains_per_block == 0 && g.tile_chains > 4 && (long)c->n_chains <= (long)cus * (g.tile_chains / 2))
+            g.tile_chains /= 2;
+    }
     RoctxRange range("muca_init");
     muca_run *r = new muca_run();
     r->log_id = ++g_run_ids;
@@ -454,7 +475,12 @@ int muca_enqueue_sweeps(muca_run *r, int64_t sweeps, bool record, hipStream_t s,
         a.em = em;
         a.accepts = r->d_hist + g.n_bins;
         a.hist_blocks = hist_blocks;
-        HIP_OR_POISON(r, launch_lattice_sweeps(g.model, g.L, g.layout, g.lpc, g.cpb, a, s));
+        a.hist_block_chains = g.cpb / g.lpc;
+        a.layout = g.layout;
+        if (g.tile_chains)
+            HIP_OR_POISON(r, launch_lattice_tiles(g.model, g.L, g.tile_chains, a, s));
+        else
+            HIP_OR_POISON(r, launch_lattice_sweeps(g.model, g.L, g.layout, g.lpc, g.cpb, a, s));
         r->sweep += (uint32_t)n;
         done += n;
     }

@@ -21,6 +21,7 @@ struct Geometry {
     int c_pad;           // chains rounded up to a multiple of 64
     int cpb;             // threads per block
     int lpc;             // lanes per chain
+    int tile_chains;     // > 0: one wavefront per chain, this many chains per workgroup
     bool table_in_lds;
     size_t lds_bytes;    // LDS of one lattice block with the table staged
     size_t off_words, off_bins, off_values, off_table, off_hist, off_energy;
