@@ -91,8 +91,10 @@ typedef struct muca_config {
     double lj_eps, lj_sigma, lj_rcut;
     double fene_k, fene_r0, fene_R; /* FENE -(K/2) R^2 ln(1-((r-r0)/R)^2)     */
     float step;             /* side of the displacement cube                   */
-    int32_t lanes_per_chain; /* lattice: 0 = auto, else 1, 2, 4 or 16 lanes share
-                                one chain's random-number work                 */
+    int32_t lanes_per_chain; /* lattice: 0 = auto, else 1, 2 or 4 lanes share one
+                                chain's random-number work, or 16: a wavefront per
+                                chain (fewest attempts at a time in sequence; it
+                                counts as 16 threads in chains_per_block)      */
     int32_t chain0;         /* global index of the run's first chain: its chains
                                are numbered chain0 .. chain0 + n_chains - 1 in the
                                random-number counters, so a run of C chains can
@@ -269,17 +271,16 @@ int muca_reweight_em(const muca_run *run, const uint64_t *h_em, int64_t n_em, co
 
 /* Batched iterations (one persistent launch for several lattice runs of
  * mixed model, L, q, ensemble and layout).  The runs' chains are cut into
- * work items of 256 / lanes_per_chain chains that a grid sized to the chip
- * takes longest first from an atomic queue; each work item runs exactly the
- * sweep code of muca_run_iteration, so every run's histogram and chains are
- * bit-identical to plain launches.
+ * work items of (at most) 256 / lanes_per_chain chains that a grid sized to
+ * the chip takes longest first from an atomic queue; each work item runs
+ * exactly the sweep code of muca_run_iteration, so every run's histogram and
+ * chains are bit-identical to plain launches.
  *   muca_batch_workspace_bytes: device bytes for up to max_runs runs and
  *     max_items work items (two staging areas, used by alternate rounds).
- *   muca_batch_create: lanes_per_chain 4 or 16 for every run, or 0 to
- *     choose per launch: runs start at 4 and, longest per-chain work first,
- *     move to 16 while all lanes fit one 256-thread workgroup per compute
- *     unit and the items fit max_items (see muca_batch_tune for runs whose
- *     item times were measured).  use_graph != 0 captures [descriptor
+ *   muca_batch_create: lanes_per_chain 4 or 16 (a wavefront per chain) for
+ *     every run, or 0 to choose per launch: 16 where the items fit max_items
+ *     (see muca_batch_tune for runs whose item times were measured), in
+ *     smaller items while every item has a compute unit of its own.  use_graph != 0 captures [descriptor
  *     upload, queue reset, persistent kernel] in a hipGraph once per staging
  *     area and relaunches it (requires a non-null stream).  d_ws is
  *     caller-owned (256-byte aligned); the handle owns two small pinned host
@@ -308,7 +309,7 @@ void muca_batch_free(muca_batch *batch);
  * process ends; the call allocates no device or pinned host memory.  Limits:
  * at most MUCA_NOALLOC_MAX_RUNS runs and MUCA_NOALLOC_MAX_ITEMS work items
  * (256 / lanes_per_chain chains each) per call, else MUCA_E_ARG with the run
- * unchanged.  lanes_per_chain: 4, 16, or 0 to choose per run as
+ * unchanged.  lanes_per_chain: 4, 16, or 0 to choose as
  * muca_batch_create does.  The runs must live on the current device
  * (MUCA_E_ARG otherwise).  No graph capture of this call; it returns after
  * the launch has completed.  All calls on one GPU share that array: calls
@@ -323,7 +324,7 @@ int muca_batch_run_iteration_noalloc(muca_run *const *runs, int32_t n_runs, cons
 /* Autotuner of the batched launch (the batching pattern's chains per
  * workgroup and table placement, per class of run).  Measures the time of
  * one work item of the run's class (model, layout, L, q) for every candidate:
- * 4 or 16 lanes per chain (64 or 16 chains per 256-thread work item), and
+ * 4 or 16 lanes per chain (64 or 16 chains per work item), and
  * the threshold table staged in LDS (where it fits) or read from global
  * memory.  Each probe runs the run's first work item for probe_sweeps sweeps
  * (0: about 5e4 site updates per chain) alone on the device; the run's
@@ -335,10 +336,9 @@ int muca_batch_run_iteration_noalloc(muca_run *const *runs, int32_t n_runs, cons
  * chains).  The run keeps the measurement: a batched launch with
  * lanes_per_chain 0 (muca_batch_create, muca_batch_run_iteration_noalloc)
  * whose runs are all tuned takes per run the table placement of the faster
- * item and the lanes per chain that minimise the estimated length of the
- * round, max(longest item, total item time / compute units), starting from
- * the choice of least total item time; items are ordered by their measured
- * time.  The probes use the library's device array of
+ * item, and for the round the lanes per chain that give the shorter
+ * estimate of its length, max(longest item, total item time / compute
+ * units); items are ordered by their measured time.  The probes use the library's device array of
  * muca_batch_run_iteration_noalloc: they must not overlap with such a call
  * on the same GPU.  Returns after the probes have completed.  MUCA_E_ARG for
  * a run without a batched variant; MUCA_E_HIP if a probe fails (run

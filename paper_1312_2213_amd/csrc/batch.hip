@@ -1,14 +1,16 @@
 // batch.hip -- one persistent launch advancing many multicanonical runs
 // (mixed models, lattice sizes, q, ensembles) by one iteration each.
 //
-// The runs' chains are cut into work items of 256 / LPC chains (one
-// 256-thread workgroup each).  Items are ordered longest first (sites x
-// sweeps x per-site cost) and handed out by an atomic counter to a grid
-// sized to fill the chip once; a workgroup stages the item's threshold
-// table in LDS when it fits, runs the item's sweeps with the same sweep
-// code as the plain launch, adds its LDS histogram to the run's histogram,
-// and takes the next item until the queue is empty.  Chains never interact,
-// so every run's histogram and chains are bit-identical to a plain launch.
+// The runs' chains are cut into work items: up to sixteen chains on a
+// 1024-thread workgroup, one wavefront per chain (lattice_tile.h), or 64
+// chains on a 256-thread workgroup, four lanes per chain.  Items are ordered
+// longest first (sites x sweeps x per-site cost) and handed out by an atomic
+// counter to a grid sized to fill the chip once; a workgroup stages the
+// item's threshold table in LDS when it fits, runs the item's sweeps with the
+// same sweep code as the plain launch, adds its LDS histogram to the run's
+// histogram, and takes the next item until the queue is empty.  Chains never
+// interact, so every run's histogram and chains are bit-identical to a plain
+// launch.
 //
 // The host side captures [descriptor upload, counter reset, persistent
 // kernel] once in a hipGraph and relaunches it every round after rewriting
@@ -23,6 +25,7 @@
 #include <vector>
 
 #include "lattice_impl.h"
+#include "lattice_tile.h"
 #include "runtime_internal.h"
 
 namespace muca {
@@ -30,7 +33,8 @@ namespace muca {
 struct BatchDesc {
     LatticeArgs a;
     int32_t variant;
-    int32_t pad[3];
+    int32_t chains; // of one work item
+    int32_t pad[2];
 };
 
 struct BatchItem {
@@ -44,12 +48,10 @@ struct BatchHeader {
 };
 
 constexpr int kBatchLs[6] = {8, 16, 24, 32, 48, 64};
-constexpr int kNumVariants = 5 * 6 * 2 * 2; // {Ising bit, Ising byte, MUMA bit, MUMA byte, Potts} x L x LDS x LPC
+constexpr int kNumVariants = 5 * 6 * 2;     // {Ising bit, Ising byte, MUMA bit, MUMA byte, Potts} x L x LDS
+constexpr int kNumTileVariants = 3 * 6 * 2; // {Ising, Potts, MUMA} x L x LDS
 
-__host__ __device__ constexpr int variant_index(int kind, int li, int tlds, int lpc16)
-{
-    return ((kind * 6 + li) * 2 + tlds) * 2 + lpc16;
-}
+__host__ __device__ constexpr int variant_index(int kind, int li, int tlds) { return (kind * 6 + li) * 2 + tlds; }
 
 // The descriptor's values are the same for the whole workgroup, but inside a
 // non-inlined function the compiler cannot know it: read them through
@@ -64,18 +66,8 @@ __device__ __forceinline__ T *uni(T *p)
     return (T *)(((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v));
 }
 
-template <int V>
-__device__ __noinline__ void run_variant(const BatchDesc *d, int c_first)
+__device__ __forceinline__ LatticeArgs uniform_args(const BatchDesc *d)
 {
-    extern __shared__ uint32_t smem[];
-    constexpr int lpc16 = V % 2;
-    constexpr bool TLDS = (V / 2) % 2;
-    constexpr int li = (V / 4) % 6;
-    constexpr int kind = V / 24;
-    constexpr int L = kBatchLs[li];
-    constexpr int MODEL = kind <= 1 ? kIsing : (kind <= 3 ? kMuma : kPotts);
-    constexpr int LAYOUT = (kind == 0 || kind == 2) ? kLayoutBit : kLayoutByte;
-    constexpr int LPC = lpc16 ? 16 : 4;
     const LatticeArgs v = d->a;
     LatticeArgs a;
     a.words = uni(v.words);
@@ -89,7 +81,31 @@ __device__ __noinline__ void run_variant(const BatchDesc *d, int c_first)
     a.em = uni(v.em);
     a.accepts = uni(v.accepts);
     a.hist_blocks = uni(v.hist_blocks);
-    sweep_block<MODEL, L, LAYOUT, TLDS, LPC>(a, uni(c_first), smem);
+    a.hist_block_chains = uni(v.hist_block_chains);
+    a.layout = uni(v.layout);
+    return a;
+}
+
+template <int V>
+__device__ __noinline__ void run_variant(const BatchDesc *d, int c_first)
+{
+    extern __shared__ uint32_t smem[];
+    constexpr bool TLDS = V % 2;
+    constexpr int L = kBatchLs[(V / 2) % 6];
+    constexpr int kind = V / 12;
+    constexpr int MODEL = kind <= 1 ? kIsing : (kind <= 3 ? kMuma : kPotts);
+    constexpr int LAYOUT = (kind == 0 || kind == 2) ? kLayoutBit : kLayoutByte;
+    sweep_block<MODEL, L, LAYOUT, TLDS, 4>(uniform_args(d), uni(c_first), smem);
+}
+
+template <int V>
+__device__ __noinline__ void run_tile_variant(const BatchDesc *d, int c_first)
+{
+    extern __shared__ uint32_t smem[];
+    constexpr bool TLDS = V % 2;
+    constexpr int L = kBatchLs[(V / 2) % 6];
+    constexpr int MODEL = V / 12; // kIsing, kPotts, kMuma
+    tile_block<MODEL, L, TLDS>(uniform_args(d), uni(c_first), uni(d->chains), smem);
 }
 
 template <int... V>
@@ -98,8 +114,15 @@ __device__ __forceinline__ void dispatch(int v, const BatchDesc *d, int c_first,
     (void)((v == V ? (run_variant<V>(d, c_first), true) : false) || ...);
 }
 
-__global__ __launch_bounds__(256) void batch_persistent(const BatchHeader *hdr, int *counter,
-                                                        const BatchDesc *descs, const BatchItem *items)
+template <int... V>
+__device__ __forceinline__ void dispatch_tiles(int v, const BatchDesc *d, int c_first, std::integer_sequence<int, V...>)
+{
+    (void)((v == V ? (run_tile_variant<V>(d, c_first), true) : false) || ...);
+}
+
+template <class Run>
+__device__ __forceinline__ void take_items(const BatchHeader *hdr, int *counter, const BatchDesc *descs,
+                                           const BatchItem *items, Run run)
 {
     __shared__ int s_item;
     const int n = hdr->n_items;
@@ -113,9 +136,27 @@ __global__ __launch_bounds__(256) void batch_persistent(const BatchHeader *hdr, 
             break; // uniform: every workgroup leaves once the queue is empty
         const BatchItem item = items[it];
         const BatchDesc *d = descs + item.inst;
-        dispatch(d->variant, d, item.c_first, std::make_integer_sequence<int, kNumVariants>{});
+        run(d, item.c_first);
         __syncthreads(); // the next item reuses the LDS
     }
+}
+
+// Items of 64 chains on 256 threads, four lanes per chain.
+__global__ __launch_bounds__(256) void batch_persistent(const BatchHeader *hdr, int *counter,
+                                                        const BatchDesc *descs, const BatchItem *items)
+{
+    take_items(hdr, counter, descs, items, [](const BatchDesc *d, int c_first) {
+        dispatch(d->variant, d, c_first, std::make_integer_sequence<int, kNumVariants>{});
+    });
+}
+
+// Items of up to sixteen chains on 1024 threads, one wavefront per chain.
+__global__ __launch_bounds__(1024) void batch_tiles(const BatchHeader *hdr, int *counter, const BatchDesc *descs,
+                                                    const BatchItem *items)
+{
+    take_items(hdr, counter, descs, items, [](const BatchDesc *d, int c_first) {
+        dispatch_tiles(d->variant, d, c_first, std::make_integer_sequence<int, kNumTileVariants>{});
+    });
 }
 
 __global__ void batch_reset(int *counter) { *counter = 0; }
@@ -140,6 +181,7 @@ struct BatchSlot {
     hipStream_t graph_stream = nullptr;
     int graph_grid = 0;
     size_t graph_lds = 0;
+    bool graph_tiles = false;
 };
 
 struct muca_batch {
@@ -292,10 +334,11 @@ struct RoundPlan {
     int grid = 0;
     size_t lds = 0;
     int n_items = 0;
+    bool tiles = false; // batch_tiles, else batch_persistent
 };
 
 // The descriptor of run r for `sweeps` sweeps from its current sweep counter.
-static void fill_desc(BatchDesc &d, const muca_run *r, int64_t sweeps, bool tlds, int lpc)
+static void fill_desc(BatchDesc &d, const muca_run *r, int64_t sweeps, bool tlds, bool tiles, int chains)
 {
     std::memset(&d, 0, sizeof d);
     d.a.words = r->d_words;
@@ -314,91 +357,66 @@ static void fill_desc(BatchDesc &d, const muca_run *r, int64_t sweeps, bool tlds
     d.a.table_in_lds = tlds ? 1 : 0;
     d.a.chain0 = r->cfg.chain0;
     d.a.accepts = r->d_hist + r->g.n_bins;
-    d.variant = variant_index(kind_of(r), l_index(r->g.L), tlds ? 1 : 0, lpc == 16 ? 1 : 0);
+    d.a.layout = r->g.layout;
+    d.chains = chains;
+    d.variant = variant_index(tiles ? r->g.model : kind_of(r), l_index(r->g.L), tlds ? 1 : 0);
 }
 
-// Lanes per chain, table placement and item cost of every run of a round,
-// from the runs' measured item times (muca_batch_tune).  The chip is taken
-// as n_cus slots, each running one work item at a time, and the round's
-// length is estimated as max(longest item, total item time / slots): every
-// run starts at the choice of least total item time, then the run with the
-// longest item moves to the choice with the shorter item while that lowers
-// the estimate.  Returns false if some run is not tuned.
-static bool plan_tuned(muca_run *const *runs, int n, const int64_t *sweeps, int n_cus, int max_items, int *lpc,
-                       int *tlds, double *cost)
+// Chains of one work item: 64 at four lanes per chain, up to sixteen at one
+// wavefront per chain.
+constexpr int kItemChains = 64, kTileItemChains = 16;
+
+static long items_of(const muca_run *r, int chains) { return (r->cfg.n_chains + chains - 1) / chains; }
+
+// Table placement and item cost of every run of a round, from the runs'
+// measured item times (muca_batch_tune), and whether the round takes one
+// wavefront per chain: the chip is taken as n_cus slots, each running one
+// work item at a time, and the round's length is estimated as max(longest
+// item, total item time / slots) for either kind of item.  Returns false if
+// some run is not tuned.
+static bool plan_tuned(muca_run *const *runs, int n, const int64_t *sweeps, int n_cus, bool *tiles, int *tlds,
+                       double *cost)
 {
     for (int i = 0; i < n; ++i)
         if (!runs[i]->batch_tuned)
             return false;
-    auto items_of = [&](int i, int o) { return (double)((runs[i]->cfg.n_chains + 256 / (o ? 16 : 4) - 1) /
-                                                        (256 / (o ? 16 : 4))); };
-    // per-item time of option o (0: 4 lanes, 1: 16 lanes) at the faster table placement
+    // per-item time of kind o (0: 4 lanes, 1: a wavefront) at the faster table placement
     auto item_t = [&](int i, int o, int *tl) {
         const double g = runs[i]->batch_us[o][0], l = runs[i]->batch_us[o][1];
-        double best = -1.0;
-        int t = 0;
-        if (g >= 0.0)
-            best = g, t = 0;
-        if (l >= 0.0 && (best < 0.0 || l < best))
-            best = l, t = 1;
+        const bool lds = l >= 0.0 && (g < 0.0 || l < g);
         if (tl)
-            *tl = t;
+            *tl = lds;
+        const double best = lds ? l : g;
         return best < 0.0 ? -1.0 : best * (double)sweeps[i];
     };
-    double total = 0.0, items = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const double w4 = item_t(i, 0, nullptr), w16 = item_t(i, 1, nullptr);
-        int o = 0;
-        if (w4 < 0.0 || (w16 >= 0.0 && items_of(i, 1) * w16 < items_of(i, 0) * w4))
-            o = 1;
-        if (item_t(i, o, nullptr) < 0.0)
-            return false;
-        lpc[i] = o ? 16 : 4;
-        total += items_of(i, o) * item_t(i, o, nullptr);
-        items += items_of(i, o);
-    }
-    auto estimate = [&](double tot) {
-        double longest = 0.0;
-        for (int i = 0; i < n; ++i)
-            longest = std::max(longest, item_t(i, lpc[i] == 16, nullptr));
-        return std::max(longest, tot / (double)n_cus);
-    };
-    double est = estimate(total);
-    for (int step = 0; step < n; ++step) {
-        int k = 0;
-        for (int i = 1; i < n; ++i)
-            if (item_t(i, lpc[i] == 16, nullptr) > item_t(k, lpc[k] == 16, nullptr))
-                k = i;
-        const int o = lpc[k] == 16, alt = 1 - o;
-        const double now = item_t(k, o, nullptr), other = item_t(k, alt, nullptr);
-        if (other < 0.0 || other >= now)
-            break;
-        const double tot2 = total - items_of(k, o) * now + items_of(k, alt) * other;
-        const double items2 = items - items_of(k, o) + items_of(k, alt);
-        lpc[k] = alt ? 16 : 4;
-        const double est2 = estimate(tot2);
-        if (est2 >= est || items2 > (double)max_items) {
-            lpc[k] = o ? 16 : 4;
-            break;
+    double est[2];
+    for (int o = 0; o < 2; ++o) {
+        double total = 0.0, longest = 0.0;
+        for (int i = 0; i < n; ++i) {
+            const double t = item_t(i, o, nullptr);
+            if (t < 0.0)
+                return false;
+            total += t * (double)items_of(runs[i], o ? kTileItemChains : kItemChains);
+            longest = std::max(longest, t);
         }
-        est = est2, total = tot2, items = items2;
+        est[o] = std::max(longest, total / (double)n_cus);
     }
+    *tiles = est[1] <= est[0];
     for (int i = 0; i < n; ++i)
-        cost[i] = item_t(i, lpc[i] == 16, &tlds[i]);
+        cost[i] = item_t(i, *tiles ? 1 : 0, &tlds[i]);
     return true;
 }
 
 // Plans one batched round: checks the runs, moves each to stream s, chooses
-// lanes per chain (lpc_fixed, or per run when 0: from the measured item
-// times when every run is tuned, else by the rule below) and the table
+// the kind of work item (lpc_fixed, or when 0: from the measured item times
+// when every run is tuned, else one wavefront per chain) and the table
 // placement, and writes the header, one descriptor per run and the work
-// items (longest first) into the host staging area `stage`.  `lpc`, `tlds`,
-// `order` and `cost` are caller-owned work arrays of n entries; nothing is
-// allocated here, so the entry point that must not allocate can use it.
+// items (longest first) into the host staging area `stage`.  `tlds` and
+// `cost` are caller-owned work arrays of n entries; nothing is allocated
+// here, so the entry point that must not allocate can use it.
 // Returns a muca_status.
 static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int lpc_fixed, int max_runs, int max_items,
-                      int n_cus, int lds_limit, uint8_t *stage, int *lpc, int *tlds, int *order, double *cost,
-                      hipStream_t s, RoundPlan *out)
+                      int n_cus, int lds_limit, uint8_t *stage, int *tlds, double *cost, hipStream_t s, RoundPlan *out)
 {
     if (n > max_runs)
         return muca_fail(MUCA_E_ARG, "%d runs exceed the batch capacity %d", n, max_runs);
@@ -417,54 +435,34 @@ static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int l
                 return muca_fail(MUCA_E_ARG, "run %d appears twice", i);
     }
     const size_t lds_budget = (size_t)std::min(lds_limit, 160 * 1024) - 256; // static LDS of the kernel
-    auto items_of = [&](int i, int l) { return (long)((runs[i]->cfg.n_chains + 256 / l - 1) / (256 / l)); };
-    // untuned rule: the per-site cost of Potts counted twice that of Ising
-    auto work = [&](int i) {
-        return (runs[i]->g.model == kPotts ? 2.0 : 1.0) * (double)runs[i]->g.n_sites * (double)sweeps[i];
-    };
+    bool tiles = lpc_fixed != 4;
     for (int i = 0; i < n; ++i) {
-        lpc[i] = lpc_fixed ? lpc_fixed : 4;
-        tlds[i] = runs[i]->g.table_in_lds && runs[i]->g.lds_bytes <= lds_budget;
-        cost[i] = work(i);
+        tlds[i] = 1;
+        // untuned: the per-site cost of Potts counted twice that of Ising
+        cost[i] = (runs[i]->g.model == kPotts ? 2.0 : 1.0) * (double)runs[i]->g.n_sites * (double)sweeps[i];
     }
-    if (lpc_fixed == 0 && plan_tuned(runs, n, sweeps, n_cus, max_items, lpc, tlds, cost)) {
-        for (int i = 0; i < n; ++i) // a measured LDS placement must still fit this device
-            tlds[i] = tlds[i] && runs[i]->g.table_in_lds && runs[i]->g.lds_bytes <= lds_budget;
-    } else if (lpc_fixed == 0) {
-        // every run starts at 4 lanes per chain; runs are raised to 16 in
-        // order of decreasing per-chain work (the critical path of the
-        // launch) while all lanes still fit one resident 256-thread
-        // workgroup per CU and the item list its capacity
-        long lanes = 0, n_items = 0;
-        for (int i = 0; i < n; ++i) {
-            order[i] = i;
-            lanes += items_of(i, 4) * 256;
-            n_items += items_of(i, 4);
-        }
-        std::sort(order, order + n, [&](int x, int y) {
-            const double wx = work(x), wy = work(y);
-            return wx != wy ? wx > wy : x < y;
-        });
-        const long cap = (long)n_cus * 256;
-        for (int k = 0; k < n; ++k) {
-            const int i = order[k];
-            if (runs[i]->g.model == kPotts && runs[i]->g.L % 16)
-                continue; // Potts rows split over the lanes: 16 lanes need L a multiple of 16
-            const long extra_items = items_of(i, 16) - items_of(i, 4), extra = extra_items * 256;
-            if (lanes + extra > cap || n_items + extra_items > max_items)
-                break;
-            lanes += extra;
-            n_items += extra_items;
-            lpc[i] = 16;
-        }
-    }
+    if (lpc_fixed == 0)
+        (void)plan_tuned(runs, n, sweeps, n_cus, &tiles, tlds, cost);
+    for (int i = 0; i < n; ++i) // a placement in LDS must fit this device
+        tlds[i] = tlds[i] && runs[i]->g.table_in_lds && runs[i]->g.lds_bytes <= lds_budget;
     // Work items cover the run's chains only: items made of padding chains
     // alone are not launched (padding chains are never histogrammed or read).
-    long total_items = 0;
-    for (int i = 0; i < n; ++i)
-        total_items += items_of(i, lpc[i]);
-    if (total_items > max_items)
-        return muca_fail(MUCA_E_ARG, "%ld work items exceed the batch capacity %d", total_items, max_items);
+    auto total_items = [&](int chains) {
+        long t = 0;
+        for (int i = 0; i < n; ++i)
+            t += items_of(runs[i], chains);
+        return t;
+    };
+    int chains = tiles ? kTileItemChains : kItemChains;
+    if (lpc_fixed == 0 && tiles && total_items(chains) > max_items) {
+        tiles = false; // the larger items fit where the smaller ones do not
+        chains = kItemChains;
+    }
+    if (total_items(chains) > max_items)
+        return muca_fail(MUCA_E_ARG, "%ld work items exceed the batch capacity %d", total_items(chains), max_items);
+    // few chains: smaller items, while every one still has a CU of its own
+    while (tiles && chains > 4 && total_items(chains / 2) <= std::min(n_cus, max_items))
+        chains /= 2;
     const StageLayout sl = stage_layout(max_runs, max_items);
     BatchHeader *hdr = (BatchHeader *)stage;
     BatchDesc *desc = (BatchDesc *)(stage + sl.desc_off);
@@ -475,11 +473,10 @@ static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int l
         muca_run *r = runs[i];
         if (int rc = muca_use_stream(r, s))
             return rc; // the run's last threshold upload may still be queued elsewhere
-        const int cpi = 256 / lpc[i]; // chains per item
         const size_t hist = (size_t)lds_hist_words(r->g.n_bins) * 4u;
         lds = std::max(lds, tlds[i] ? r->g.lds_bytes : hist);
-        fill_desc(desc[i], r, sweeps[i], tlds[i] != 0, lpc[i]);
-        for (int c0 = 0; c0 < r->cfg.n_chains; c0 += cpi)
+        fill_desc(desc[i], r, sweeps[i], tlds[i] != 0, tiles, chains);
+        for (int c0 = 0; c0 < r->cfg.n_chains; c0 += chains)
             hitems[n_items++] = BatchItem{i, c0};
     }
     // longest first (per-item cost); equal costs keep the run and chain order
@@ -496,17 +493,29 @@ static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int l
     out->grid = std::max(1, std::min(n_items, n_cus * per_cu));
     out->lds = lds;
     out->n_items = n_items;
+    out->tiles = tiles;
     return MUCA_OK;
 }
 
-static hipError_t set_lds(size_t lds)
+static hipError_t set_lds(bool tiles, size_t lds)
 {
     if (lds > 65536u)
-        return hipFuncSetAttribute((const void *)batch_persistent, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        return hipFuncSetAttribute(tiles ? (const void *)batch_tiles : (const void *)batch_persistent,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     return hipSuccess;
 }
 
-static hipError_t enqueue_batch(muca_batch *b, const BatchSlot &sl, int grid, size_t lds, hipStream_t s)
+static hipError_t launch_items(bool tiles, int grid, size_t lds, const BatchHeader *hdr, int *counter,
+                               const BatchDesc *desc, const BatchItem *items, hipStream_t s)
+{
+    if (tiles)
+        hipLaunchKernelGGL(batch_tiles, dim3(grid), dim3(1024), lds, s, hdr, counter, desc, items);
+    else
+        hipLaunchKernelGGL(batch_persistent, dim3(grid), dim3(256), lds, s, hdr, counter, desc, items);
+    return hipGetLastError();
+}
+
+static hipError_t enqueue_batch(muca_batch *b, const BatchSlot &sl, const RoundPlan &plan, hipStream_t s)
 {
     hipError_t e = hipMemcpyAsync(sl.d_hdr, sl.h_buf, b->stage_bytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess)
@@ -515,9 +524,7 @@ static hipError_t enqueue_batch(muca_batch *b, const BatchSlot &sl, int grid, si
     e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(batch_persistent, dim3(grid), dim3(256), lds, s, sl.d_hdr, sl.d_counter, sl.d_desc,
-                       sl.d_items);
-    return hipGetLastError();
+    return launch_items(plan.tiles, plan.grid, plan.lds, sl.d_hdr, sl.d_counter, sl.d_desc, sl.d_items, s);
 }
 
 static void advance_runs(muca_run *const *runs, int n, const int64_t *sweeps)
@@ -544,21 +551,20 @@ try {
         b->poisoned = true;
         return muca_fail(MUCA_E_HIP, "batched launch: %s", hipGetErrorString(e));
     }
-    std::vector<int> lpc(n), tlds(n), order(n);
+    std::vector<int> tlds(n);
     std::vector<double> cost(n);
     RoundPlan plan;
     if (int rc = plan_round(runs, n, sweeps, b->lpc, b->max_runs, b->max_items, b->n_cus, b->lds_limit, sl.h_buf,
-                            lpc.data(), tlds.data(), order.data(), cost.data(), s, &plan))
+                            tlds.data(), cost.data(), s, &plan))
         return rc;
-    const int grid = plan.grid;
-    const size_t lds = plan.lds;
-    e = set_lds(lds);
+    e = set_lds(plan.tiles, plan.lds);
     if (e == hipSuccess && b->use_graph) {
-        if (!sl.exec || sl.graph_stream != s || sl.graph_grid != grid || sl.graph_lds != lds) {
+        if (!sl.exec || sl.graph_stream != s || sl.graph_grid != plan.grid || sl.graph_lds != plan.lds ||
+            sl.graph_tiles != plan.tiles) {
             drop_graph(sl);
             e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
             if (e == hipSuccess) {
-                hipError_t e2 = enqueue_batch(b, sl, grid, lds, s);
+                hipError_t e2 = enqueue_batch(b, sl, plan, s);
                 e = hipStreamEndCapture(s, &sl.graph);
                 if (e == hipSuccess)
                     e = e2;
@@ -566,13 +572,14 @@ try {
             if (e == hipSuccess)
                 e = hipGraphInstantiate(&sl.exec, sl.graph, nullptr, nullptr, 0);
             sl.graph_stream = s;
-            sl.graph_grid = grid;
-            sl.graph_lds = lds;
+            sl.graph_grid = plan.grid;
+            sl.graph_lds = plan.lds;
+            sl.graph_tiles = plan.tiles;
         }
         if (e == hipSuccess)
             e = hipGraphLaunch(sl.exec, s);
     } else if (e == hipSuccess) {
-        e = enqueue_batch(b, sl, grid, lds, s);
+        e = enqueue_batch(b, sl, plan, s);
     }
     if (e == hipSuccess)
         e = hipEventRecord(sl.done, s);
@@ -663,12 +670,12 @@ try {
     }
     // host staging on the stack: the copy below is complete before return
     alignas(256) uint8_t stage[kScratchStage];
-    int lpc[kScratchRuns], tlds[kScratchRuns], order[kScratchRuns];
+    int tlds[kScratchRuns];
     double cost[kScratchRuns];
     RoundPlan plan;
     hipStream_t s = (hipStream_t)stream;
-    if (int rc = plan_round(runs, n, sweeps, lanes_per_chain, kScratchRuns, kScratchItems, n_cus, lds_limit, stage, lpc,
-                            tlds, order, cost, s, &plan))
+    if (int rc = plan_round(runs, n, sweeps, lanes_per_chain, kScratchRuns, kScratchItems, n_cus, lds_limit, stage,
+                            tlds, cost, s, &plan))
         return rc;
     const StageLayout sl = stage_layout(kScratchRuns, kScratchItems);
     if (sl.bytes > kScratchStage)
@@ -676,7 +683,7 @@ try {
     int *d_counter = (int *)d_scratch;
     uint8_t *d_stage = d_scratch + 256;
     const size_t used = sl.items_off + (size_t)plan.n_items * sizeof(BatchItem);
-    e = set_lds(plan.lds);
+    e = set_lds(plan.tiles, plan.lds);
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_stage, stage, used, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
@@ -684,10 +691,8 @@ try {
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(batch_persistent, dim3(plan.grid), dim3(256), plan.lds, s, (const BatchHeader *)d_stage,
-                           d_counter, (const BatchDesc *)(d_stage + sl.desc_off),
-                           (const BatchItem *)(d_stage + sl.items_off));
-        e = hipGetLastError();
+        e = launch_items(plan.tiles, plan.grid, plan.lds, (const BatchHeader *)d_stage, d_counter,
+                         (const BatchDesc *)(d_stage + sl.desc_off), (const BatchItem *)(d_stage + sl.items_off), s);
     }
     if (e == hipSuccess)
         e = hipStreamSynchronize(s); // the staging is on this stack frame; the next call rewrites `scratch`
@@ -714,7 +719,7 @@ static std::string batch_cache_key(const muca_run *r, const char *arch)
     return buf;
 }
 
-// One work item (the run's chains [0, 256 / lpc)) of `sweeps` sweeps alone
+// One work item (the run's first 16 or 64 chains) of `sweeps` sweeps alone
 // on the device, timed by events around the kernel.
 static hipError_t probe_item(muca_run *r, uint8_t *d_scratch, int lpc, bool tlds, int64_t sweeps, hipStream_t s,
                              hipEvent_t e0, hipEvent_t e1, float *ms)
@@ -724,11 +729,12 @@ static hipError_t probe_item(muca_run *r, uint8_t *d_scratch, int lpc, bool tlds
     static_assert(sizeof(BatchDesc) <= 256 && sizeof(BatchItem) <= 256, "probe staging layout");
     std::memset(stage, 0, sizeof stage);
     ((BatchHeader *)stage)->n_items = 1;
-    fill_desc(*(BatchDesc *)(stage + sl.desc_off), r, sweeps, tlds, lpc);
+    const bool tiles = lpc == 16;
+    fill_desc(*(BatchDesc *)(stage + sl.desc_off), r, sweeps, tlds, tiles, tiles ? kTileItemChains : kItemChains);
     *(BatchItem *)(stage + sl.items_off) = BatchItem{0, 0};
     const size_t lds = tlds ? r->g.lds_bytes : (size_t)lds_hist_words(r->g.n_bins) * 4u;
     uint8_t *d_stage = d_scratch + 256;
-    hipError_t e = set_lds(lds);
+    hipError_t e = set_lds(tiles, lds);
     if (e == hipSuccess)
         e = hipMemcpyAsync(d_stage, stage, sl.bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
@@ -737,12 +743,9 @@ static hipError_t probe_item(muca_run *r, uint8_t *d_scratch, int lpc, bool tlds
     }
     if (e == hipSuccess)
         e = hipEventRecord(e0, s);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(batch_persistent, dim3(1), dim3(256), lds, s, (const BatchHeader *)d_stage,
-                           (int *)d_scratch, (const BatchDesc *)(d_stage + sl.desc_off),
-                           (const BatchItem *)(d_stage + sl.items_off));
-        e = hipGetLastError();
-    }
+    if (e == hipSuccess)
+        e = launch_items(tiles, 1, lds, (const BatchHeader *)d_stage, (int *)d_scratch,
+                         (const BatchDesc *)(d_stage + sl.desc_off), (const BatchItem *)(d_stage + sl.items_off), s);
     if (e == hipSuccess)
         e = hipEventRecord(e1, s);
     if (e == hipSuccess)

@@ -8,8 +8,11 @@
 // histogram that is merged over all chains (parallel-scheme paragraph).
 //
 // Mapping to the hardware:
-//  * one chain per lane; a wavefront runs 64 chains in lockstep on the same
-//    site, so the lattice words of 64 chains are 64 consecutive dwords;
+//  * one chain per lane, or per group of 2 or 4 lanes; a wavefront runs 64
+//    (32, 16) chains in lockstep on the same site, so the lattice words of 64
+//    chains are 64 consecutive dwords.  These kernels serve chain counts that
+//    fill the chip this way; runs of fewer chains take one wavefront per
+//    chain (lattice_tile.h);
 //  * a sweep streams the lattice row by row through registers: rows y-1, y,
 //    y+1 are held in VGPRs and row y+3 is prefetched while y is processed;
 //    every site update works on registers with compile-time bit positions;
@@ -57,9 +60,8 @@ __device__ __forceinline__ uint32_t colour(const uint32_t (&R)[W], int x)
 // ---------------------------------------------------------------------------
 // Random words of one row.  With LPC lanes per chain, lane j of a chain's
 // group computes the Philox calls j, j + LPC, ... of the row and every site
-// reads its word from the owning lane by a DPP broadcast (quad_perm within
-// quads, row_newbcast within rows of 16).  The counters, and so the words,
-// are those of the one-lane-per-chain order.
+// reads its word from the owning lane by a DPP broadcast (quad_perm).  The
+// counters, and so the words, are those of the one-lane-per-chain order.
 // ---------------------------------------------------------------------------
 template <int L, int LPC, int WPS>
 struct RowRng {
@@ -96,11 +98,9 @@ struct RowRng {
         } else if constexpr (LPC == 2) {
             constexpr int pat = src | (src << 2) | ((2 + src) << 4) | ((2 + src) << 6);
             return (uint32_t)__builtin_amdgcn_mov_dpp((int)w[reg], pat, 0xF, 0xF, false);
-        } else if constexpr (LPC == 4) {
-            return (uint32_t)__builtin_amdgcn_mov_dpp((int)w[reg], src * 0x55, 0xF, 0xF, false);
         } else {
-            static_assert(LPC == 16, "lanes per chain: 1, 2, 4 or 16");
-            return (uint32_t)__builtin_amdgcn_mov_dpp((int)w[reg], 0x150 + src, 0xF, 0xF, false);
+            static_assert(LPC == 4, "lanes per chain: 1, 2 or 4");
+            return (uint32_t)__builtin_amdgcn_mov_dpp((int)w[reg], src * 0x55, 0xF, 0xF, false);
         }
     }
 };
@@ -109,29 +109,23 @@ struct RowRng {
 template <int LPC, int O>
 __device__ __forceinline__ uint32_t group_bcast(uint32_t v)
 {
-    if constexpr (LPC == 4)
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, O * 0x55, 0xF, 0xF, false);
-    else
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150 + O, 0xF, 0xF, false);
+    static_assert(LPC == 4, "lane groups are quads");
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, O * 0x55, 0xF, 0xF, false);
 }
 
 // value of the previous / next lane of the group, cyclic
 template <int LPC>
 __device__ __forceinline__ uint32_t group_prev(uint32_t v)
 {
-    if constexpr (LPC == 4)
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x93, 0xF, 0xF, false); // quad_perm [3,0,1,2]
-    else
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x121, 0xF, 0xF, false); // row_ror:1
+    static_assert(LPC == 4, "lane groups are quads");
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x93, 0xF, 0xF, false); // quad_perm [3,0,1,2]
 }
 
 template <int LPC>
 __device__ __forceinline__ uint32_t group_next(uint32_t v)
 {
-    if constexpr (LPC == 4)
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x39, 0xF, 0xF, false); // quad_perm [1,2,3,0]
-    else
-        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x12F, 0xF, 0xF, false); // row_ror:15
+    static_assert(LPC == 4, "lane groups are quads");
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x39, 0xF, 0xF, false); // quad_perm [1,2,3,0]
 }
 
 // ---------------------------------------------------------------------------
@@ -303,8 +297,8 @@ __device__ __forceinline__ void ising_row(const uint32_t (&up)[Row1<L>::W], uint
 }
 
 // ---------------------------------------------------------------------------
-// Ising / MUMA with the per-site candidate work split over the lanes of a
-// chain (4 or 16 lanes).  The lane that draws a site's Philox word (site X:
+// Ising / MUMA with the per-site candidate work split over the four lanes of a
+// chain.  The lane that draws a site's Philox word (site X:
 // call X / 4, lane (X / 4) % LPC) also builds, from bit planes of the row as
 // it was when the row started, the site's descriptor: for both outcomes of
 // the left neighbour's attempt, the site's bin step, and the next site's
@@ -321,15 +315,11 @@ __device__ __forceinline__ void ising_row(const uint32_t (&up)[Row1<L>::W], uint
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int32_t sbyte(uint32_t v) { return (int32_t)(int8_t)(uint8_t)v; }
 
-// value of lane O of the chain's lane group, 64 bits (one v_mov_b64 DPP with
-// row_newbcast; two 32-bit quad permutes for groups of 4)
+// value of lane O of the chain's lane group, 64 bits
 template <int LPC, int O>
 __device__ __forceinline__ uint64_t group_bcast64(uint64_t v)
 {
-    if constexpr (LPC == 16)
-        return __builtin_amdgcn_mov_dpp(v, 0x150 + O, 0xF, 0xF, false);
-    else
-        return (uint64_t)group_bcast<LPC, O>((uint32_t)v) | ((uint64_t)group_bcast<LPC, O>((uint32_t)(v >> 32)) << 32);
+    return (uint64_t)group_bcast<LPC, O>((uint32_t)v) | ((uint64_t)group_bcast<LPC, O>((uint32_t)(v >> 32)) << 32);
 }
 
 // two signed bytes: f(nA) | f(nB) << 8, for the site's misalignment count
@@ -801,7 +791,7 @@ __device__ __forceinline__ uint32_t changed_bytes(const uint32_t (&a)[W], const 
 
 template <int L, int LPC>
 struct PottsLP {
-    static constexpr bool ok = (LPC == 4 || LPC == 16) && L % LPC == 0;
+    static constexpr bool ok = LPC == 4;
     static constexpr int S = L / LPC;       // sites per lane
     static constexpr int SW = (S + 3) / 4;  // words of a lane's segment
     // Philox calls (two sites each) that cover the segment: S / 2 when S is
