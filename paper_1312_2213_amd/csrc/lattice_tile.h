@@ -20,24 +20,37 @@
 // progress, 10 with thresholds that jump by a factor e from bin to bin.
 //
 // The thresholds of a pass are read for every outcome of the neighbours that
-// sit earlier in the tile (left, and up where a tile has several rows), so
-// the outcomes are 64-bit masks on the scalar unit and the dependence on
-// those neighbours is resolved there, without further reads.  The lattice
-// never leaves the registers during a launch: lane t holds tile t as a
-// 64-bit mask (Ising, MUMA), or lane i holds its site's colour of every tile,
-// four per register (Potts).
+// sit earlier in the tile (left, and up where a tile has several rows).  The
+// outcomes are 64-bit masks on the scalar unit, where the dependence on those
+// neighbours is followed a few links without further reads, and a lane's bin
+// is counted from them (Ising, MUMA: bits below the lane; Potts, whose steps
+// take nine values: a DPP scan).  The lattice never leaves the registers
+// during a launch: lane t holds tile t as a 64-bit mask (Ising, MUMA), or
+// lane i holds its site's colour of every tile, four per register (Potts).
 //
-// Bound: instruction issue with four wavefronts per SIMD, latency (LDS reads,
-// the scalar chain) below that.  Measured per iteration, before (16 lanes per
-// chain, site by site) and after: Ising L = 64, 4096 chains, 400 sweeps
-// 54.4 -> 23.0 ms; Ising L = 32 int8, 1000 chains, 35 sweeps 1.69 -> 0.46 ms;
-// MUMA L = 32 with the joint histogram, 512 chains, 67 sweeps 2.85 -> 0.69 ms;
-// Potts q = 8 L = 48, 2048 chains, 362 sweeps 39.4 -> 12.7 ms; Potts q = 10
-// L = 64 (table in global memory), 1024 chains, 60 sweeps 14.5 -> 3.5 ms.
+// Bound: instruction issue with four wavefronts per SIMD (Ising: scalar and
+// vector units about even, 130 instructions per tile of 64; Potts: vector),
+// latency (LDS reads, the scalar chain) below that.  Measured per iteration,
+// before (16 lanes per chain, site by site) and after: Ising L = 64, 4096
+// chains, 400 sweeps 54.4 -> 18.1 ms; Ising L = 32 int8, 1000 chains, 35
+// sweeps 1.69 -> 0.34 ms; MUMA L = 32 with the joint histogram, 512 chains,
+// 67 sweeps 2.85 -> 0.52 ms; Potts q = 8 L = 48, 2048 chains, 362 sweeps
+// 39.4 -> 10.9 ms; Potts q = 10 L = 64 (table in global memory), 1024 chains,
+// 60 sweeps 14.5 -> 2.7 ms.
 #pragma once
 #include "lattice_impl.h"
 
 namespace muca {
+
+// Links of the chains of neighbours followed in one pass beyond the first.
+// More save passes where weights are smooth, and cost scalar (Ising: vector)
+// instructions in every pass where they are rough.  Cycles per site of a SIMD
+// with four wavefronts, smooth weights / noise of 0.3 per bin: Ising L = 64
+// two links 23.4 / 45.4, three 23.5 / 48.7; L = 16 one 39.3 / 46.0, two 37.6 /
+// 46.9; MUMA L = 64 one 17.3 / 22.4, two 18.5 / 22.4; Potts L = 48 one 41.9 /
+// 67.2, two 42.0 / 68.9.
+template <int MODEL>
+constexpr int kTileAhead = MODEL == kIsing ? 2 : 1;
 
 template <int L>
 struct Tile {
@@ -104,29 +117,25 @@ __device__ __forceinline__ void quad_transpose(uint32_t (&w)[4])
     w[3] = high ? a[3] : x[1];
 }
 
+// The lanes below this one whose bit is set in m, added to v.
+__device__ __forceinline__ int32_t below(uint64_t m, int32_t v)
+{
+    return (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)v));
+}
+
+// v + (this lane's bit of m): one add with carry-in.  m comes from the scalar
+// unit (a mask that a vector compare has just written would need two wait
+// states).
+__device__ __forceinline__ int32_t add_bit(int32_t v, uint64_t m)
+{
+    int32_t out;
+    asm("v_addc_co_u32 %0, vcc, 0, %1, %2" : "=v"(out) : "v"(v), "s"(m) : "vcc");
+    return out;
+}
+
 // ---------------------------------------------------------------------------
 // Ising / MUMA
 // ---------------------------------------------------------------------------
-// Thresholds T[bin][first + k + j * stride], j = 0..n-1, n = 2 or 3.
-template <int MODEL, bool TLDS, int n>
-__device__ __forceinline__ void spin_thresholds(const uint32_t *T, int32_t tbase, int32_t bin, int32_t col,
-                                                uint32_t (&t)[3])
-{
-    constexpr int NC = Cols<MODEL>::value, ST = MODEL == kIsing ? 1 : 2;
-    const int32_t at = bin * (4 * NC) + col;
-    if constexpr (TLDS) {
-        lds_u32 *p = (lds_u32 *)(uintptr_t)(uint32_t)(tbase + at);
-#pragma unroll
-        for (int j = 0; j < n; ++j)
-            t[j] = p[j * ST];
-    } else {
-        const gu32 *p = (const gu32 *)((uintptr_t)T + (uint32_t)at);
-#pragma unroll
-        for (int j = 0; j < n; ++j)
-            t[j] = p[j * ST];
-    }
-}
-
 // The attempts of one tile: S its spins (bit set = +1), P and N the tiles
 // above and below it, r each lane's acceptance word (accept iff r < T; lanes
 // beyond the tile hold 2^32 - 1).  Returns the accepted sites; b becomes the
@@ -137,6 +146,7 @@ __device__ __forceinline__ uint64_t spin_tile(uint64_t S, uint64_t P, uint64_t N
 {
     using G = Tile<L>;
     constexpr int R = G::R, TS = G::TS, UP = TS - L;
+    constexpr int COL = MODEL == kIsing ? 4 : 8, ROW = 4 * Cols<MODEL>::value; // bytes
     uint64_t Su, Sd;
     if constexpr (G::kWhole) {
         Su = (S << L) | (S >> UP);
@@ -152,62 +162,93 @@ __device__ __forceinline__ uint64_t spin_tile(uint64_t S, uint64_t P, uint64_t N
     const uint64_t Sr = ((S >> 1) & ~G::kLast) | ((S << (L - 1)) & G::kLast);
     // aligned with the left, up, right and down neighbours as the tile starts
     const uint64_t AL = ~(S ^ Sl), AU = ~(S ^ Su), AR = ~(S ^ Sr), AD = ~(S ^ Sd);
-    const int32_t plus = MODEL == kMuma ? (lane_bit(S) ? 4 : 0) : 0;
+    // column of the aligned neighbours that earlier attempts of the tile do
+    // not change
+    int32_t col = TLDS ? tbase : 0;
+    if constexpr (MODEL == kMuma)
+        col += lane_bit(S) ? 4 : 0;
+    const int32_t dr = lane_bit(AR) ? COL : 0, dd = lane_bit(AD) ? COL : 0;
+    col += dr + dd;
+    if constexpr (R == 1)
+        col += lane_bit(AU) ? COL : 0;
+    const int32_t wrap_r = COL - 2 * dr, wrap_d = COL - 2 * dd;
 
-    uint64_t F = 0ull;  // accepted, as the last pass found it
-    int32_t x = b;      // this lane's bin if F is right
-    int32_t end = b;    // the bin after the tile if F is right
-    for (;;) {
-        // neighbours that the inner resolution does not follow: a row's last
-        // site sees site 0 (its right neighbour) as this pass's F left it,
-        // and the last row of a whole lattice the first one
-        const uint64_t ar = AR ^ ((F << (L - 1)) & G::kLast);
-        const uint64_t ad = G::kWhole ? AD ^ (F << UP) : AD;
-        int32_t k = (lane_bit(ar) ? 1 : 0) + (lane_bit(ad) ? 1 : 0);
-        if constexpr (R == 1)
-            k += lane_bit(AU) ? 1 : 0;
-        if (F) {
-            if constexpr (MODEL == kIsing) {
-                int32_t n = k - 2 + (lane_bit(AL ^ ((F << 1) & ~G::kFirst)) ? 1 : 0);
-                if constexpr (R > 1)
-                    n += lane_bit(AU ^ (F << L)) ? 1 : 0;
-                n = lane_bit(F) ? n : 0;
-                x = prefix_from(b, n);
-                end = __builtin_amdgcn_readlane(x, TS - 1) + __builtin_amdgcn_readlane(n, TS - 1);
-            } else {
-                const uint64_t up = F & ~S, dn = F & S; // M grows where a -1 flips
-                x = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(up >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)up, (uint32_t)b));
-                x -= (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(dn >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)dn, 0u));
-                end = b + __builtin_popcountll(up) - __builtin_popcountll(dn);
-            }
-            // a wrong guess may leave the table; the answer cannot
-            x = min(max(x, 0), n_bins - 1);
-        }
-        uint32_t t[3];
-        const int32_t col = MODEL == kIsing ? 4 * k : 8 * k + plus;
-        spin_thresholds<MODEL, TLDS, (R == 1 ? 2 : 3)>(T, tbase, x, col, t);
-        // outcome by the number of aligned neighbours among left (and up)
-        const uint64_t C0 = ballot(r < t[0]), C1 = ballot(r < t[1]);
-        uint64_t A = F, A0;
-        if constexpr (R == 1) {
-            const uint64_t Q = C0 ^ C1, B = C0 ^ (AL & Q), D = Q & ~G::kFirst;
-            do {
-                A0 = A;
-                A = B ^ (D & (A << 1));
-            } while (A != A0);
+    uint64_t F, A;           // accepted sites, and the outcomes at the bins that they give
+    uint64_t l = AL, u = AU; // aligned left and up neighbours once the sites of F have flipped
+    uint32_t t[3];           // thresholds by the number of those two
+    auto read = [&](int32_t at) {
+#pragma unroll
+        for (int k = 0; k < (R == 1 ? 2 : 3); ++k)
+            t[k] = TLDS ? ((lds_u32 *)(uintptr_t)(uint32_t)at)[k * (COL / 4)]
+                        : ((const gu32 *)((uintptr_t)T + (uint32_t)at))[k * (COL / 4)];
+    };
+    auto flips = [&](uint64_t a) {
+        if constexpr (R == 1) { // nothing shifts into site 0
+            l = AL ^ (a << 1);
         } else {
-            const uint64_t Q1 = C0 ^ C1, Q2 = C0 ^ ballot(r < t[2]);
-            do {
-                A0 = A;
-                const uint64_t l = AL ^ ((A << 1) & ~G::kFirst), u = AU ^ (A << L);
-                A = C0 ^ ((l ^ u) & Q1) ^ ((l & u) & Q2);
-            } while (A != A0);
+            l = AL ^ ((a << 1) & ~G::kFirst);
+            u = AU ^ (a << L);
         }
-        if (A == F)
-            break;
-        F = A;
+    };
+    uint64_t C0 = 0ull, Q = 0ull; // R = 1: outcomes without an aligned left neighbour, and where one changes them
+    auto decide = [&]() {
+        if constexpr (R == 1) {
+            C0 = ballot(r < t[0]);
+            Q = C0 ^ ballot(r < t[1]);
+        }
+    };
+    auto outcomes = [&]() -> uint64_t {
+        if constexpr (R == 1) {
+            return C0 ^ (Q & l);
+        } else {
+            const uint32_t t0 = lane_bit(l) ? t[1] : t[0], t1 = lane_bit(l) ? t[2] : t[1];
+            return ballot(r < (lane_bit(u) ? t1 : t0));
+        }
+    };
+    // a few links of the chains of neighbours at once; whatever is left is
+    // found by the next pass
+    auto ahead = [&](uint64_t a) {
+#pragma unroll
+        for (int k = 0; k < kTileAhead<MODEL>; ++k) {
+            flips(a);
+            a = outcomes();
+        }
+        flips(a);
+        return a;
+    };
+    int32_t x, c;
+    auto pass = [&]() {
+        // bins that F gives.  A row's last site sees site 0 (its right
+        // neighbour) as F left it, the last row of a whole lattice the first
+        const uint64_t wr = (F << (L - 1)) & G::kLast, wd = G::kWhole ? F << UP : 0ull;
+        c = col + (lane_bit(wr) ? wrap_r : 0);
+        if constexpr (G::kWhole)
+            c += lane_bit(wd) ? wrap_d : 0;
+        if constexpr (MODEL == kMuma) // M grows where a -1 flips
+            x = below(F & ~S, b) - below(F & S, 0);
+        else // a flip with n aligned neighbours moves the bin by n - 2
+            x = below(F & l, below(F & u, below(F & (AR ^ wr), below(F & (AD ^ wd), b)))) - 2 * below(F, 0);
+        // a wrong guess may leave the table (the answer cannot): any row does
+        read(__mul24((int32_t)min((uint32_t)x, (uint32_t)(n_bins - 1)), ROW) + c);
+        decide();
+        return outcomes();
+    };
+    read(b * ROW + col); // first every lane at the tile's first bin
+    decide();
+    F = ahead(outcomes());
+    A = pass();
+    while (A != F) {
+        F = ahead(A);
+        A = pass();
     }
-    b = end;
+    if constexpr (MODEL == kMuma) {
+        b += __builtin_popcountll(F & ~S) - __builtin_popcountll(F & S);
+    } else { // the last site's own step is behind its lane's bin
+        int32_t n = add_bit((c >> 2) - ((TLDS ? tbase >> 2 : 0) + 2), l);
+        if constexpr (R > 1)
+            n = add_bit(n, u);
+        b = __builtin_amdgcn_readlane(x + (lane_bit(F) ? n : 0), TS - 1);
+    }
     return F;
 }
 
@@ -358,27 +399,29 @@ struct SpinChain {
 // ---------------------------------------------------------------------------
 // Potts
 // ---------------------------------------------------------------------------
-// (colour == old) - (colour == proposal): a neighbour's share of the change
-// in unsatisfied bonds.
-__device__ __forceinline__ int32_t potts_share(uint32_t colour, uint32_t old, uint32_t nw)
+// e + (colour == old) - (colour == proposal): the change in unsatisfied bonds
+// with one more neighbour counted.
+__device__ __forceinline__ int32_t potts_add(int32_t e, uint32_t colour, uint32_t old, uint32_t nw)
 {
-    return (colour == old ? 1 : 0) - (colour == nw ? 1 : 0);
+    e += colour == old ? 1 : 0;
+    e -= colour == nw ? 1 : 0;
+    return e;
 }
 
-// Threshold of the change dE from bin x.  Staged rows hold eight columns,
-// dE = -4..-1, 1..4 (dE = 0 always accepts and is not read); rows in global
-// memory nine.
+// Byte offset of the change dE in a bin's row.  Rows in global memory have
+// nine columns, dE = -4..4; staged rows eight (dE = 0 always accepts and is
+// not read), looked up by one byte permute with selector dE + 4: +4 selects
+// the sign of byte 1, which is zero.
 template <bool TLDS>
 __device__ __forceinline__ int32_t potts_col(int32_t dE)
 {
-    return TLDS ? 4 * (dE + 4 - (dE > 0 ? 1 : 0)) : 4 * (dE + 4);
+    if constexpr (TLDS)
+        return (int32_t)__builtin_amdgcn_perm(0x18141000u, 0x0C08041Cu, (uint32_t)(dE + 0x0C0C0C04));
+    return 4 * (dE + 4);
 }
 
-template <bool TLDS>
-__device__ __forceinline__ uint32_t potts_threshold(const uint32_t *T, int32_t row, int32_t col)
-{
-    return load_t<TLDS>(T, row + col);
-}
+// The global column of slot s of a staged row.
+__device__ __forceinline__ int potts_staged_column(int s) { return s == 0 ? 8 : (s == 7 ? 0 : s + (s >= 4 ? 1 : 0)); }
 
 // The attempts of one tile.  cur, above, below: colours of this tile, of the
 // tile above and of the tile below; (wp, r) proposal and acceptance words.
@@ -407,90 +450,113 @@ __device__ __forceinline__ uint64_t potts_tile(uint32_t cur, uint32_t above, uin
             v = lane < L ? below | (below << 8) : both;
         dn = (uint32_t)__builtin_amdgcn_ds_bpermute(down_l, (int)v);
     }
-    // shares of the neighbours before and after their own attempts in this
-    // tile; a neighbour that the order visits later, or that lies outside
-    // the tile, has one share
-    const bool col0 = lane_bit(G::kFirst), row0 = lane < L;
-    const int32_t l0 = potts_share(lf & 0xFFu, cur, p);
-    const int32_t l1 = col0 ? l0 : potts_share((lf >> 8) & 0xFFu, cur, p);
-    const int32_t u0 = potts_share(up & 0xFFu, cur, p);
-    int32_t u1 = u0;
-    if constexpr (R > 1)
-        u1 = row0 ? u0 : potts_share((up >> 8) & 0xFFu, cur, p);
-    const int32_t r0 = potts_share(rt & 0xFFu, cur, p), r1 = potts_share((rt >> 8) & 0xFFu, cur, p);
-    const int32_t d0 = potts_share(dn & 0xFFu, cur, p);
-    const int32_t d1 = G::kWhole ? potts_share((dn >> 8) & 0xFFu, cur, p) : d0;
-
-    uint64_t F = 0ull, wrap_r = 0ull, wrap_d = 0ull;
-    int32_t x = b, end = b;
-    int32_t e[4], c[4];    // dE and column by (left, up) accepted: 00, 10, 01, 11
-    uint64_t Z[4];         // dE = 0
+    // dE by the attempts of the left and up neighbours earlier in this tile:
+    // neither accepted, left, up, both.  A neighbour that the order visits
+    // later, or that lies outside the tile, has one colour.
     constexpr int NV = R > 1 ? 4 : 2;
-    auto variants = [&]() {
-        const int32_t s = (lane_bit(wrap_r) ? r1 : r0) + (G::kWhole && lane_bit(wrap_d) ? d1 : d0);
-        e[0] = s + l0 + u0;
-        e[1] = s + l1 + u0;
+    int32_t e[4], c[4]; // and the byte offset of its column
+    uint64_t Z[4];      // dE = 0
+    {
+        const bool col0 = lane_bit(G::kFirst);
+        int32_t s = potts_add(0, dn & 0xFFu, cur, p);
+        s = potts_add(s, rt & 0xFFu, cur, p);
+        const int32_t s0 = potts_add(s, up & 0xFFu, cur, p);
+        e[0] = potts_add(s0, lf & 0xFFu, cur, p);
+        e[1] = potts_add(s0, (lf >> 8) & 0xFFu, cur, p);
+        e[1] = col0 ? e[0] : e[1];
         if constexpr (R > 1) {
-            e[2] = s + l0 + u1;
-            e[3] = s + l1 + u1;
+            const bool row0 = lane < L;
+            int32_t s1 = potts_add(s, (up >> 8) & 0xFFu, cur, p);
+            s1 = row0 ? s0 : s1;
+            e[2] = potts_add(s1, lf & 0xFFu, cur, p);
+            e[3] = potts_add(s1, (lf >> 8) & 0xFFu, cur, p);
+            e[3] = col0 ? e[2] : e[3];
         }
+    }
+    auto columns = [&]() {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             c[v] = potts_col<TLDS>(e[v]);
             Z[v] = ballot(e[v] == 0) & G::kAll;
         }
     };
-    variants();
-    for (;;) {
-        if (F) {
-            // a row's last site sees site 0 as this pass's F left it, and
-            // the last row of a whole lattice the first one
-            const uint64_t wr = (F << (L - 1)) & G::kLast, wd = G::kWhole ? F << UP : 0ull;
-            if (wr != wrap_r || wd != wrap_d) {
-                wrap_r = wr;
-                wrap_d = wd;
-                variants();
-            }
-            const bool la = lane_bit(F << 1);
-            int32_t n = la ? e[1] : e[0];
-            if constexpr (R > 1) {
-                const int32_t m = la ? e[3] : e[2];
-                n = lane_bit(F << L) ? m : n;
-            }
-            n = lane_bit(F) ? n : 0;
-            x = prefix_from(b, n);
-            end = __builtin_amdgcn_readlane(x, TS - 1) + __builtin_amdgcn_readlane(n, TS - 1);
-            x = min(max(x, 0), n_bins - 1); // a wrong guess may leave the table; the answer cannot
+    columns();
+    // A row's last site sees site 0 (its right neighbour) as the accepted
+    // sites leave it, and the last row of a whole lattice the first one.
+    uint64_t wrap_r = 0ull, wrap_d = 0ull;
+    auto wraps = [&](uint64_t F) {
+        const uint64_t wr = (F << (L - 1)) & G::kLast, wd = G::kWhole ? F << UP : 0ull;
+        if (wr == wrap_r && wd == wrap_d)
+            return;
+        const uint32_t r_was = lane_bit(wrap_r) ? rt >> 8 : rt, r_now = lane_bit(wr) ? rt >> 8 : rt;
+        int32_t d = potts_add(0, r_now & 0xFFu, cur, p) - potts_add(0, r_was & 0xFFu, cur, p);
+        if constexpr (G::kWhole) {
+            const uint32_t d_was = lane_bit(wrap_d) ? dn >> 8 : dn, d_now = lane_bit(wd) ? dn >> 8 : dn;
+            d += potts_add(0, d_now & 0xFFu, cur, p) - potts_add(0, d_was & 0xFFu, cur, p);
         }
-        const int32_t row = TLDS ? tbase + 32 * x : 36 * x;
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            e[v] += d;
+        columns();
+        wrap_r = wr;
+        wrap_d = wd;
+    };
+    // Outcomes as the neighbours' outcomes enter them: B without an accepted
+    // left (up) neighbour, toggled by DL (DU) where it was accepted, and by
+    // DB more where both were.  Column 0 has one variant: no left neighbour
+    // toggles it.
+    uint64_t B, DL, DU = 0ull, DB = 0ull;
+    auto decide = [&](int32_t row) {
         uint32_t t[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v)
-            t[v] = potts_threshold<TLDS>(T, row, c[v]);
+            t[v] = load_t<TLDS>(T, row + c[v]);
         uint64_t C[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v)
             C[v] = ballot(r < t[v]) | Z[v];
-        uint64_t A = F, A0;
-        if constexpr (R == 1) {
-            const uint64_t D = C[0] ^ C[1]; // no bit in column 0: one variant there
-            do {
-                A0 = A;
-                A = C[0] ^ (D & (A << 1));
-            } while (A != A0);
-        } else {
-            const uint64_t D1 = C[0] ^ C[1], D2 = C[0] ^ C[2], D3 = D1 ^ C[2] ^ C[3];
-            do {
-                A0 = A;
-                const uint64_t l = A << 1, u = A << L;
-                A = C[0] ^ (l & D1) ^ (u & (D2 ^ (l & D3)));
-            } while (A != A0);
+        B = C[0];
+        DL = C[0] ^ C[1];
+        if constexpr (R > 1) {
+            DU = C[0] ^ C[2];
+            DB = DL ^ C[2] ^ C[3];
         }
-        if (A == F)
-            break;
-        F = A;
+    };
+    auto outcomes = [&](uint64_t A) -> uint64_t {
+        if constexpr (R == 1)
+            return B ^ (DL & (A << 1));
+        const uint64_t l = A << 1, u = A << (R > 1 ? L : 0);
+        return B ^ (l & DL) ^ (u & (DU ^ (l & DB)));
+    };
+    auto ahead = [&](uint64_t A) {
+#pragma unroll
+        for (int k = 0; k < kTileAhead<kPotts>; ++k)
+            A = outcomes(A);
+        return A;
+    };
+    int32_t x, n;
+    auto pass = [&](uint64_t F) {
+        wraps(F);
+        const bool la = lane_bit(F << 1);
+        n = la ? e[1] : e[0];
+        if constexpr (R > 1) {
+            const int32_t m = la ? e[3] : e[2];
+            n = lane_bit(F << L) ? m : n;
+        }
+        n = lane_bit(F) ? n : 0;
+        x = prefix_from(b, n);
+        // a wrong guess may leave the table (the answer cannot): any row does
+        const int32_t xr = (int32_t)min((uint32_t)x, (uint32_t)(n_bins - 1));
+        decide(TLDS ? tbase + 32 * xr : __mul24(xr, 36));
+        return outcomes(F);
+    };
+    decide(TLDS ? tbase + 32 * b : 36 * b); // first every lane at the tile's first bin
+    uint64_t F = ahead(B), A = pass(F);
+    while (A != F) {
+        F = ahead(A);
+        A = pass(F);
     }
-    b = end;
+    b = __builtin_amdgcn_readlane(x, TS - 1) + __builtin_amdgcn_readlane(n, TS - 1);
     return F;
 }
 
@@ -624,8 +690,7 @@ __device__ __forceinline__ void tile_block(const LatticeArgs &a, int c_first, in
         for (int i = threadIdx.x; i < a.n_bins * NCL; i += blockDim.x) {
             int src = i;
             if constexpr (MODEL == kPotts) { // the dE = 0 column is not staged
-                const int cc = i & 7;
-                src = (i >> 3) * 9 + cc + (cc >= 4 ? 1 : 0);
+                src = (i >> 3) * 9 + potts_staged_column(i & 7);
             }
             smem[i] = ((const gu32 *)a.thresholds)[src];
         }

@@ -88,13 +88,26 @@ static size_t align256(size_t x) { return (x + 255u) & ~(size_t)255u; }
 // ---------------------------------------------------------------------------
 // Most chains of a run that takes the one-wavefront-per-chain kernels by
 // default.  Their rate stops growing once every SIMD has four wavefronts
-// (4096 chains), that of 1 to 4 lanes per chain grows until the lanes fill
+// (4096 chains); that of 1 to 4 lanes per chain grows until the lanes fill
 // the chip.  Measured, 1e9 attempts/s, a wavefront / the best of 1, 2 and 4
-// lanes per chain: at 4096 chains Ising L = 64 206 / 100, L = 16 138 / 79,
-// MUMA L = 32 241 / 90, Potts q = 8 L = 48 170 / 59, L = 16 151 / 53; at 8192
-// Ising L = 64 182 / 200, L = 16 137 / 158, MUMA L = 32 251 / 179, Potts
-// L = 48 182 / 117, L = 16 158 / 107.
-static const long kTileMaxChains = 4096;
+// lanes per chain:
+//                  4096         8192         16384        32768
+//   Ising L = 64   280 / 100    244 / 199    299 / 396    310 / 618
+//   Ising L = 16   236 /  79    238 / 158    238 / 315
+//   MUMA  L = 32   399 /  90    413 / 179    417 / 356    417 / 562
+//   Potts L = 48   205 /  59    215 / 117    205 / 224    209 / 285
+//   Potts L = 24   130 /  53    134 / 106    134 / 210
+// and with the threshold table in global memory, whose latency few lanes per
+// chain hide worse,
+//   MUMA  L = 64   460 /  67    476 / 132    474 / 260    478 / 351
+//   Potts L = 64   243 /  51    242 / 101    233 / 195    244 / 242
+// The rates of few lanes per chain are linear in the chains between these
+// columns, which puts the lines near 1.1e4 (Ising), 1.2e4 (Potts) and 2.2e4
+// (MUMA), and about twice as far without a staged table.
+static long tile_max_chains(int model, bool staged)
+{
+    return (model == kIsing ? 10240 : model == kPotts ? 12288 : 20480) * (staged ? 1 : 2);
+}
 
 static int bin_step(int model) { return model == kIsing ? 4 : (model == kPotts ? 1 : 2); }
 
@@ -160,8 +173,6 @@ int muca_geometry(const muca_config *c, Geometry *g)
     if (lpc != 1 && lpc != 2 && lpc != 4 && lpc != 16)
         return muca_fail(MUCA_E_ARG, "lanes_per_chain %d not in {1, 2, 4, 16}", lpc);
     g->lpc = lpc;
-    if (c->lanes_per_chain == 16 || (c->lanes_per_chain == 0 && (long)g->c_pad <= kTileMaxChains))
-        g->tile_chains = 16;
     // default: 256-thread blocks, so a block that stages the threshold table
     // in LDS (one block per CU) still carries four wavefronts of work; at
     // init, 512 where that table leaves room for one block per CU and the
@@ -184,6 +195,9 @@ int muca_geometry(const muca_config *c, Geometry *g)
     if (hist_lds > 64u * 1024u)
         return muca_fail(MUCA_E_ARG, "%d bins exceed the LDS histogram", g->n_bins);
     g->table_in_lds = c->table_in_lds == 1 || (c->table_in_lds < 0 && g->lds_bytes <= 160u * 1024u);
+    if (c->lanes_per_chain == 16 ||
+        (c->lanes_per_chain == 0 && (long)g->c_pad <= tile_max_chains(g->model, g->table_in_lds)))
+        g->tile_chains = 16;
     if (g->cpb > 256 && !g->table_in_lds)
         return muca_fail(MUCA_E_ARG, "blocks of %d threads need the threshold table staged in LDS", g->cpb);
     // workspace carve

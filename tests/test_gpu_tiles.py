@@ -91,3 +91,20 @@ def test_workgroup_shapes_and_counter_flushes(chains_per_block):
     g.merge_update()
     assert np.array_equal(g.last_hist(), H)
     assert_same_state(o, g)
+
+
+@pytest.mark.parametrize("model,L,chains,tlds", [("ising", 8, 10240, 1), ("ising", 8, 10304, 1), ("potts", 8, 12288, 1),
+                                                 ("potts", 8, 24640, 0), ("muma", 8, 40960, 0), ("muma", 8, 20544, 1)])
+def test_default_kernel_on_either_side_of_its_line(model, L, chains, tlds):
+    """The default choice by chain count, against four lanes per chain."""
+    from paper_1312_2213_amd import muca
+    got = []
+    for lpc in (0, 4):
+        g = muca.Run(muca.muca_config_default(model, L, 3, chains, 5, lanes_per_chain=lpc, table_in_lds=tlds))
+        g.set_lnw(rough(model, g.n_bins, 0.3))
+        g.run_iteration(5)
+        st = g.merge_update()
+        s, b, _ = g.chain_state()
+        got.append((g.last_hist(), st["accept_rate"], s, b))
+    for x, y in zip(*got):
+        assert np.array_equal(x, y)
