@@ -16,6 +16,7 @@
 // kernel] once in a hipGraph and relaunches it every round after rewriting
 // the pinned descriptor buffer (sweep counters and sweeps change per round).
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -368,55 +369,75 @@ constexpr int kItemChains = 64, kTileItemChains = 16;
 
 static long items_of(const muca_run *r, int chains) { return (r->cfg.n_chains + chains - 1) / chains; }
 
-// Table placement and item cost of every run of a round, from the runs'
-// measured item times (muca_batch_tune), and whether the round takes one
-// wavefront per chain: the chip is taken as n_cus slots, each running one
-// work item at a time, and the round's length is estimated as max(longest
-// item, total item time / slots) for either kind of item.  Returns false if
-// some run is not tuned.
-static bool plan_tuned(muca_run *const *runs, int n, const int64_t *sweeps, int n_cus, bool *tiles, int *tlds,
-                       double *cost)
+// What the planner assumes of one work item of a run: its time with the
+// table placement it takes.  Measured (muca_batch_tune) when every run of the
+// round is tuned, else nominal: cycles per site of a workgroup alone on its
+// CU, about the mean over L of what the kernels measure.
+struct ItemTime {
+    double t[2]; // [four lanes per chain, 64 chains | a wavefront per chain, 16 chains]; < 0: not a candidate
+    int tlds[2];
+};
+
+static ItemTime item_time(const muca_run *r, int64_t sweeps, bool tuned)
 {
-    for (int i = 0; i < n; ++i)
-        if (!runs[i]->batch_tuned)
-            return false;
-    // per-item time of kind o (0: 4 lanes, 1: a wavefront) at the faster table placement
-    auto item_t = [&](int i, int o, int *tl) {
-        const double g = runs[i]->batch_us[o][0], l = runs[i]->batch_us[o][1];
-        const bool lds = l >= 0.0 && (g < 0.0 || l < g);
-        if (tl)
-            *tl = lds;
-        const double best = lds ? l : g;
-        return best < 0.0 ? -1.0 : best * (double)sweeps[i];
-    };
-    double est[2];
+    ItemTime x;
     for (int o = 0; o < 2; ++o) {
-        double total = 0.0, longest = 0.0;
-        for (int i = 0; i < n; ++i) {
-            const double t = item_t(i, o, nullptr);
-            if (t < 0.0)
-                return false;
-            total += t * (double)items_of(runs[i], o ? kTileItemChains : kItemChains);
-            longest = std::max(longest, t);
+        double best;
+        if (tuned) {
+            const double g = r->batch_us[o][0], l = r->batch_us[o][1];
+            x.tlds[o] = l >= 0.0 && (g < 0.0 || l < g);
+            best = x.tlds[o] ? l : g;
+        } else {
+            static const double cycles[3][2] = {{110.0, 34.0}, {180.0, 44.0}, {110.0, 21.0}}; // Ising, Potts, MUMA
+            best = cycles[r->g.model][o] * (double)r->g.n_sites;
+            x.tlds[o] = 1;
         }
-        est[o] = std::max(longest, total / (double)n_cus);
+        x.t[o] = best < 0.0 ? -1.0 : best * (double)sweeps;
     }
-    *tiles = est[1] <= est[0];
-    for (int i = 0; i < n; ++i)
-        cost[i] = item_t(i, *tiles ? 1 : 0, &tlds[i]);
-    return true;
+    return x;
 }
 
+// Workgroups of 8 and 4 wavefronts leave the CU's issue slots to fewer of
+// them: an item of 8 (4) chains takes this share of the time of one of 16
+// (Potts L = 48: 42, 31 and 23 cycles per site; Ising L = 64: 23, 18 and 13).
+static double tile_share(int chains) { return chains == 16 ? 1.0 : chains == 8 ? 0.75 : 0.55; }
+
+// Estimated length of a round on n_cus slots: all items spread evenly, and no
+// less than the slot that takes two items where they outnumber the slots.
+// Two workgroups of four lanes per chain side by side on a CU do 1.3 times
+// the work of one (Ising L = 32: 357 -> 479e9 attempts/s).
+struct RoundLength {
+    double longest = 0.0, shortest = 0.0, total = 0.0;
+    long items = 0;
+    void add(long k, double t)
+    {
+        longest = std::max(longest, t);
+        shortest = items ? std::min(shortest, t) : t;
+        total += (double)k * t;
+        items += k;
+    }
+    double estimate(int n_cus, double per_cu) const
+    {
+        const double rounds = std::ceil((double)items / (double)n_cus);
+        return std::max(std::max(longest, total / (double)n_cus), rounds * shortest) / per_cu;
+    }
+};
+
+struct RunPlan {
+    ItemTime x;
+    int chains;
+    double cost; // of one item
+};
+
 // Plans one batched round: checks the runs, moves each to stream s, chooses
-// the kind of work item (lpc_fixed, or when 0: from the measured item times
-// when every run is tuned, else one wavefront per chain) and the table
+// the kind of work item (lpc_fixed, or when 0 the one with the shorter
+// estimate of the round), the chains per item of every run and the table
 // placement, and writes the header, one descriptor per run and the work
-// items (longest first) into the host staging area `stage`.  `tlds` and
-// `cost` are caller-owned work arrays of n entries; nothing is allocated
-// here, so the entry point that must not allocate can use it.
-// Returns a muca_status.
+// items (longest first) into the host staging area `stage`.  `work` holds n
+// entries of the caller's; nothing is allocated here, so the entry point that
+// must not allocate can use it.  Returns a muca_status.
 static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int lpc_fixed, int max_runs, int max_items,
-                      int n_cus, int lds_limit, uint8_t *stage, int *tlds, double *cost, hipStream_t s, RoundPlan *out)
+                      int n_cus, int lds_limit, uint8_t *stage, RunPlan *work, hipStream_t s, RoundPlan *out)
 {
     if (n > max_runs)
         return muca_fail(MUCA_E_ARG, "%d runs exceed the batch capacity %d", n, max_runs);
@@ -435,34 +456,65 @@ static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int l
                 return muca_fail(MUCA_E_ARG, "run %d appears twice", i);
     }
     const size_t lds_budget = (size_t)std::min(lds_limit, 160 * 1024) - 256; // static LDS of the kernel
-    bool tiles = lpc_fixed != 4;
+    bool tuned = true;
+    for (int i = 0; i < n; ++i)
+        tuned = tuned && runs[i]->batch_tuned;
+    size_t lds4 = 0;
+    RoundLength len4, len16;
+    bool has[2] = {lpc_fixed != 16, lpc_fixed != 4};
     for (int i = 0; i < n; ++i) {
-        tlds[i] = 1;
-        // untuned: the per-site cost of Potts counted twice that of Ising
-        cost[i] = (runs[i]->g.model == kPotts ? 2.0 : 1.0) * (double)runs[i]->g.n_sites * (double)sweeps[i];
+        ItemTime &x = work[i].x;
+        x = item_time(runs[i], sweeps[i], tuned && lpc_fixed == 0);
+        for (int o = 0; o < 2; ++o) { // a placement in LDS must fit this device
+            x.tlds[o] = x.tlds[o] && runs[i]->g.table_in_lds && runs[i]->g.lds_bytes <= lds_budget;
+            has[o] = has[o] && x.t[o] >= 0.0;
+        }
+        lds4 = std::max(lds4, x.tlds[0] ? runs[i]->g.lds_bytes : (size_t)0);
+        len4.add(items_of(runs[i], kItemChains), x.t[0]);
+        len16.add(items_of(runs[i], kTileItemChains), x.t[1]);
     }
-    if (lpc_fixed == 0)
-        (void)plan_tuned(runs, n, sweeps, n_cus, &tiles, tlds, cost);
-    for (int i = 0; i < n; ++i) // a placement in LDS must fit this device
-        tlds[i] = tlds[i] && runs[i]->g.table_in_lds && runs[i]->g.lds_bytes <= lds_budget;
     // Work items cover the run's chains only: items made of padding chains
     // alone are not launched (padding chains are never histogrammed or read).
-    auto total_items = [&](int chains) {
-        long t = 0;
-        for (int i = 0; i < n; ++i)
-            t += items_of(runs[i], chains);
-        return t;
-    };
-    int chains = tiles ? kTileItemChains : kItemChains;
-    if (lpc_fixed == 0 && tiles && total_items(chains) > max_items) {
-        tiles = false; // the larger items fit where the smaller ones do not
-        chains = kItemChains;
+    if (lpc_fixed == 0) { // the larger items may fit where the smaller ones do not
+        has[1] = has[1] && len16.items <= max_items;
+        has[0] = has[0] || !has[1];
     }
-    if (total_items(chains) > max_items)
-        return muca_fail(MUCA_E_ARG, "%ld work items exceed the batch capacity %d", total_items(chains), max_items);
-    // few chains: smaller items, while every one still has a CU of its own
-    while (tiles && chains > 4 && total_items(chains / 2) <= std::min(n_cus, max_items))
-        chains /= 2;
+    const long n_min = has[1] ? len16.items : len4.items;
+    if (n_min > max_items)
+        return muca_fail(MUCA_E_ARG, "%ld work items exceed the batch capacity %d", n_min, max_items);
+    bool tiles = has[1];
+    if (tiles) {
+        // no item longer than the longest run's in items of 16, 8 or 4
+        // chains; every run takes its largest items within that
+        auto chains_within = [&](int i, double limit) {
+            int c = kTileItemChains;
+            while (c > 4 && work[i].x.t[1] * tile_share(c) > limit * 1.001)
+                c /= 2;
+            return c;
+        };
+        double best = -1.0, limit = len16.longest;
+        for (int c = kTileItemChains; c >= 4; c /= 2) {
+            RoundLength len;
+            for (int i = 0; i < n; ++i) {
+                const int k = chains_within(i, len16.longest * tile_share(c));
+                len.add(items_of(runs[i], k), work[i].x.t[1] * tile_share(k));
+            }
+            const double est = len.estimate(n_cus, 1.0);
+            if (len.items <= max_items && (best < 0.0 || est < 0.999 * best))
+                best = est, limit = len16.longest * tile_share(c);
+        }
+        for (int i = 0; i < n; ++i) {
+            work[i].chains = chains_within(i, limit);
+            work[i].cost = work[i].x.t[1] * tile_share(work[i].chains);
+        }
+        if (has[0] && len4.items <= max_items && len4.estimate(n_cus, lds4 <= 80u * 1024u ? 1.3 : 1.0) < best)
+            tiles = false;
+    }
+    if (!tiles)
+        for (int i = 0; i < n; ++i) {
+            work[i].chains = kItemChains;
+            work[i].cost = work[i].x.t[0];
+        }
     const StageLayout sl = stage_layout(max_runs, max_items);
     BatchHeader *hdr = (BatchHeader *)stage;
     BatchDesc *desc = (BatchDesc *)(stage + sl.desc_off);
@@ -474,14 +526,15 @@ static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int l
         if (int rc = muca_use_stream(r, s))
             return rc; // the run's last threshold upload may still be queued elsewhere
         const size_t hist = (size_t)lds_hist_words(r->g.n_bins) * 4u;
-        lds = std::max(lds, tlds[i] ? r->g.lds_bytes : hist);
-        fill_desc(desc[i], r, sweeps[i], tlds[i] != 0, tiles, chains);
-        for (int c0 = 0; c0 < r->cfg.n_chains; c0 += chains)
+        const bool tlds = work[i].x.tlds[tiles ? 1 : 0] != 0;
+        lds = std::max(lds, tlds ? r->g.lds_bytes : hist);
+        fill_desc(desc[i], r, sweeps[i], tlds, tiles, work[i].chains);
+        for (int c0 = 0; c0 < r->cfg.n_chains; c0 += work[i].chains)
             hitems[n_items++] = BatchItem{i, c0};
     }
     // longest first (per-item cost); equal costs keep the run and chain order
     std::sort(hitems, hitems + n_items, [&](const BatchItem &x, const BatchItem &y) {
-        const double cx = cost[x.inst], cy = cost[y.inst];
+        const double cx = work[x.inst].cost, cy = work[y.inst].cost;
         if (cx != cy)
             return cx > cy;
         return x.inst != y.inst ? x.inst < y.inst : x.c_first < y.c_first;
@@ -551,11 +604,10 @@ try {
         b->poisoned = true;
         return muca_fail(MUCA_E_HIP, "batched launch: %s", hipGetErrorString(e));
     }
-    std::vector<int> tlds(n);
-    std::vector<double> cost(n);
+    std::vector<RunPlan> work(n);
     RoundPlan plan;
     if (int rc = plan_round(runs, n, sweeps, b->lpc, b->max_runs, b->max_items, b->n_cus, b->lds_limit, sl.h_buf,
-                            tlds.data(), cost.data(), s, &plan))
+                            work.data(), s, &plan))
         return rc;
     e = set_lds(plan.tiles, plan.lds);
     if (e == hipSuccess && b->use_graph) {
@@ -670,12 +722,11 @@ try {
     }
     // host staging on the stack: the copy below is complete before return
     alignas(256) uint8_t stage[kScratchStage];
-    int tlds[kScratchRuns];
-    double cost[kScratchRuns];
+    RunPlan work[kScratchRuns];
     RoundPlan plan;
     hipStream_t s = (hipStream_t)stream;
     if (int rc = plan_round(runs, n, sweeps, lanes_per_chain, kScratchRuns, kScratchItems, n_cus, lds_limit, stage,
-                            tlds, cost, s, &plan))
+                            work, s, &plan))
         return rc;
     const StageLayout sl = stage_layout(kScratchRuns, kScratchItems);
     if (sl.bytes > kScratchStage)
