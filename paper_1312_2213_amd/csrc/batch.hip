@@ -34,8 +34,7 @@ namespace muca {
 struct BatchDesc {
     LatticeArgs a;
     int32_t variant;
-    int32_t chains; // of one work item
-    int32_t pad[2];
+    int32_t pad[3];
 };
 
 struct BatchItem {
@@ -102,11 +101,11 @@ __device__ __noinline__ void run_variant(const BatchDesc *d, int c_first)
 template <int V>
 __device__ __noinline__ void run_tile_variant(const BatchDesc *d, int c_first)
 {
-    extern __shared__ uint32_t smem[];
+    extern __shared__ __align__(16) uint32_t smem[];
     constexpr bool TLDS = V % 2;
     constexpr int L = kBatchLs[(V / 2) % 6];
     constexpr int MODEL = V / 12; // kIsing, kPotts, kMuma
-    tile_block<MODEL, L, TLDS>(uniform_args(d), uni(c_first), uni(d->chains), smem);
+    tile_block<MODEL, L, TLDS>(uniform_args(d), uni(c_first), uni(d->a.tile_chains), smem);
 }
 
 template <int... V>
@@ -359,7 +358,7 @@ static void fill_desc(BatchDesc &d, const muca_run *r, int64_t sweeps, bool tlds
     d.a.chain0 = r->cfg.chain0;
     d.a.accepts = r->d_hist + r->g.n_bins;
     d.a.layout = r->g.layout;
-    d.chains = chains;
+    d.a.tile_chains = chains;
     d.variant = variant_index(tiles ? r->g.model : kind_of(r), l_index(r->g.L), tlds ? 1 : 0);
 }
 

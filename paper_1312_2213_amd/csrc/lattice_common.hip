@@ -8,9 +8,9 @@ namespace muca {
 hipError_t launch_ising(int L, int layout, int lpc, int threads, const LatticeArgs &a, hipStream_t s);
 hipError_t launch_muma(int L, int layout, int lpc, int threads, const LatticeArgs &a, hipStream_t s);
 hipError_t launch_potts(int L, int lpc, int threads, const LatticeArgs &a, hipStream_t s);
-hipError_t launch_ising_tiles(int L, int chains, const LatticeArgs &a, hipStream_t s);
-hipError_t launch_muma_tiles(int L, int chains, const LatticeArgs &a, hipStream_t s);
-hipError_t launch_potts_tiles(int L, int chains, const LatticeArgs &a, hipStream_t s);
+hipError_t launch_ising_tiles(int L, const LatticeArgs &a, hipStream_t s);
+hipError_t launch_muma_tiles(int L, const LatticeArgs &a, hipStream_t s);
+hipError_t launch_potts_tiles(int L, const LatticeArgs &a, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // Initialisation: spin of site i of chain c from word (i & 3) of
@@ -117,14 +117,14 @@ hipError_t launch_lattice_sweeps(int model, int L, int layout, int lpc, int thre
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_lattice_tiles(int model, int L, int chains, const LatticeArgs &a, hipStream_t s)
+hipError_t launch_lattice_tiles(int model, int L, const LatticeArgs &a, hipStream_t s)
 {
     if (model == kIsing)
-        return launch_ising_tiles(L, chains, a, s);
+        return launch_ising_tiles(L, a, s);
     if (model == kMuma)
-        return launch_muma_tiles(L, chains, a, s);
+        return launch_muma_tiles(L, a, s);
     if (model == kPotts)
-        return launch_potts_tiles(L, chains, a, s);
+        return launch_potts_tiles(L, a, s);
     return hipErrorInvalidValue;
 }
 

@@ -8,8 +8,8 @@ hipError_t launch_muma(int L, int layout, int lpc, int threads, const LatticeArg
     return layout == kLayoutBit ? launch_model<kMuma, kLayoutBit>(L, lpc, threads, a, s)
                                 : launch_model<kMuma, kLayoutByte>(L, lpc, threads, a, s);
 }
-hipError_t launch_muma_tiles(int L, int chains, const LatticeArgs &a, hipStream_t s)
+hipError_t launch_muma_tiles(int L, const LatticeArgs &a, hipStream_t s)
 {
-    return launch_tile_model<kMuma>(L, chains, a, s);
+    return launch_tile_model<kMuma>(L, a, s);
 }
 } // namespace muca

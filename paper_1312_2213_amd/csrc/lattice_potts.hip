@@ -7,8 +7,8 @@ hipError_t launch_potts(int L, int lpc, int threads, const LatticeArgs &a, hipSt
 {
     return launch_model<kPotts, kLayoutByte>(L, lpc, threads, a, s);
 }
-hipError_t launch_potts_tiles(int L, int chains, const LatticeArgs &a, hipStream_t s)
+hipError_t launch_potts_tiles(int L, const LatticeArgs &a, hipStream_t s)
 {
-    return launch_tile_model<kPotts>(L, chains, a, s);
+    return launch_tile_model<kPotts>(L, a, s);
 }
 } // namespace muca

@@ -420,8 +420,8 @@ __device__ __forceinline__ int32_t potts_col(int32_t dE)
     return 4 * (dE + 4);
 }
 
-// The global column of slot s of a staged row.
-__device__ __forceinline__ int potts_staged_column(int s) { return s == 0 ? 8 : (s == 7 ? 0 : s + (s >= 4 ? 1 : 0)); }
+// The staged slot of a row's column c = dE + 4 (c = 4 has none).
+__device__ __forceinline__ int potts_staged_slot(int c) { return c == 8 ? 0 : (c == 0 ? 7 : c - (c > 4 ? 1 : 0)); }
 
 // The attempts of one tile.  cur, above, below: colours of this tile, of the
 // tile above and of the tile below; (wp, r) proposal and acceptance words.
@@ -671,6 +671,43 @@ struct PottsChain {
     }
 };
 
+// Copies the threshold table to LDS, 16 bytes per load: short launches wait
+// for it (82 KB for Ising L = 64, 147 KB for Potts L = 48).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) u32x4 gu32x4;
+
+template <int MODEL>
+__device__ __forceinline__ void stage_table(const uint32_t *T_, int n_bins, uint32_t *smem)
+{
+    constexpr int NC = Cols<MODEL>::value;
+    const gu32 *T = (const gu32 *)T_;
+    const int n = n_bins * NC, n4 = n / 4, step = (int)blockDim.x;
+#pragma unroll 8
+    for (int i = threadIdx.x; i < n4; i += step) {
+        const u32x4 v = ((const gu32x4 *)T_)[i];
+        if constexpr (MODEL != kPotts) {
+            *(u32x4 *)(smem + 4 * i) = v;
+        } else {
+            uint32_t row = __umulhi((uint32_t)(4 * i), 0x38E38E39u) >> 1; // 4 i / 9
+            uint32_t col = (uint32_t)(4 * i) - 9u * row;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (col != 4u) // dE = 0 is not staged
+                    smem[8u * row + (uint32_t)potts_staged_slot((int)col)] = v[k];
+                col = col == 8u ? 0u : col + 1u;
+                row += col == 0u ? 1u : 0u;
+            }
+        }
+    }
+    for (int i = 4 * n4 + (int)threadIdx.x; i < n; i += step) {
+        if constexpr (MODEL != kPotts) {
+            smem[i] = T[i];
+        } else if (i % 9 != 4) {
+            smem[8 * (i / 9) + potts_staged_slot(i % 9)] = T[i];
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // One block: wave w runs chain c_first + w (w < n_c).  The threshold table is
 // staged in LDS once for all of them (TLDS), the sweeps are counted in packed
@@ -687,13 +724,7 @@ __device__ __forceinline__ void tile_block(const LatticeArgs &a, int c_first, in
         lhist[i] = 0u;
     int32_t tbase = 0;
     if constexpr (TLDS) {
-        for (int i = threadIdx.x; i < a.n_bins * NCL; i += blockDim.x) {
-            int src = i;
-            if constexpr (MODEL == kPotts) { // the dE = 0 column is not staged
-                src = (i >> 3) * 9 + potts_staged_column(i & 7);
-            }
-            smem[i] = ((const gu32 *)a.thresholds)[src];
-        }
+        stage_table<MODEL>(a.thresholds, a.n_bins, smem);
         tbase = (int32_t)(uint32_t)(uintptr_t)(lds_u32 *)smem;
     }
     __syncthreads();
@@ -747,17 +778,20 @@ __device__ __forceinline__ void tile_block(const LatticeArgs &a, int c_first, in
 template <int MODEL, int L, bool TLDS>
 __global__ __launch_bounds__(1024) void lattice_tiles(LatticeArgs a)
 {
-    extern __shared__ uint32_t smem[];
-    const int n_c = (int)(blockDim.x >> 6);
-    tile_block<MODEL, L, TLDS>(a, (int)blockIdx.x * n_c, n_c, smem);
+    extern __shared__ __align__(16) uint32_t smem[];
+    tile_block<MODEL, L, TLDS>(a, (int)blockIdx.x * a.tile_chains, a.tile_chains, smem);
 }
 
 template <int MODEL, int L>
-static hipError_t launch_tiles(int chains, const LatticeArgs &a, hipStream_t s)
+static hipError_t launch_tiles(const LatticeArgs &a, hipStream_t s)
 {
+    const int chains = a.tile_chains;
     if (chains < 1 || chains > 16)
         return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((a.n_chains + chains - 1) / chains)), block((unsigned)(64 * chains));
+    // a large table is staged by sixteen wavefronts, however few carry chains
+    const size_t table = a.table_in_lds ? (size_t)a.n_bins * lds_table_cols(MODEL) * 4u : 0u;
+    const int waves = table > 16384u ? 16 : chains;
+    const dim3 grid((unsigned)((a.n_chains + chains - 1) / chains)), block((unsigned)(64 * waves));
     size_t lds = (size_t)lds_hist_words(a.n_bins) * 4u;
     if (a.table_in_lds) {
         lds += (size_t)a.n_bins * lds_table_cols(MODEL) * 4u;
@@ -774,18 +808,18 @@ static hipError_t launch_tiles(int chains, const LatticeArgs &a, hipStream_t s)
     return hipGetLastError();
 }
 
-// One wavefront per chain, `chains` of them per block.
+// One wavefront per chain, a.tile_chains of them per block.
 template <int MODEL>
-static hipError_t launch_tile_model(int L, int chains, const LatticeArgs &a, hipStream_t s)
+static hipError_t launch_tile_model(int L, const LatticeArgs &a, hipStream_t s)
 {
     switch (L) {
-    case 4: return launch_tiles<MODEL, 4>(chains, a, s);
-    case 8: return launch_tiles<MODEL, 8>(chains, a, s);
-    case 16: return launch_tiles<MODEL, 16>(chains, a, s);
-    case 24: return launch_tiles<MODEL, 24>(chains, a, s);
-    case 32: return launch_tiles<MODEL, 32>(chains, a, s);
-    case 48: return launch_tiles<MODEL, 48>(chains, a, s);
-    case 64: return launch_tiles<MODEL, 64>(chains, a, s);
+    case 4: return launch_tiles<MODEL, 4>(a, s);
+    case 8: return launch_tiles<MODEL, 8>(a, s);
+    case 16: return launch_tiles<MODEL, 16>(a, s);
+    case 24: return launch_tiles<MODEL, 24>(a, s);
+    case 32: return launch_tiles<MODEL, 32>(a, s);
+    case 48: return launch_tiles<MODEL, 48>(a, s);
+    case 64: return launch_tiles<MODEL, 64>(a, s);
     default: return hipErrorInvalidValue;
     }
 }

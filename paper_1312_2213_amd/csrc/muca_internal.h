@@ -35,7 +35,9 @@ struct LatticeArgs {
     // (chains [k * h, (k + 1) * h)), for jackknife errors
     unsigned long long *hist_blocks;
     int32_t hist_block_chains;
-    int32_t layout;             // storage of Ising / MUMA spins (tile kernels)
+    // one wavefront per chain (lattice_tile.h):
+    int32_t tile_chains;        // chains per workgroup, 1..16
+    int32_t layout;             // storage of Ising / MUMA spins
 };
 
 struct LatticeInitArgs {
@@ -89,8 +91,8 @@ hipError_t launch_lattice_init(const LatticeInitArgs &a, hipStream_t s);
 // threads per block in {64, 128, 256, 512}; lpc lanes per chain in {1, 2, 4}
 hipError_t launch_lattice_sweeps(int model, int L, int layout, int lpc, int threads, const LatticeArgs &a,
                                  hipStream_t s);
-// one wavefront per chain, `chains` (1..16) of them per block
-hipError_t launch_lattice_tiles(int model, int L, int chains, const LatticeArgs &a, hipStream_t s);
+// one wavefront per chain, a.tile_chains of them per block
+hipError_t launch_lattice_tiles(int model, int L, const LatticeArgs &a, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, hipStream_t s);
 // host: device address of page-locked host memory (hipHostGetDevicePointer)
 hipError_t launch_drain_u64(unsigned long long *p, unsigned long long *host, int64_t n, hipStream_t s);

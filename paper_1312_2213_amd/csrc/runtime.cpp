@@ -491,8 +491,9 @@ int muca_enqueue_sweeps(muca_run *r, int64_t sweeps, bool record, hipStream_t s,
         a.hist_blocks = hist_blocks;
         a.hist_block_chains = g.cpb / g.lpc;
         a.layout = g.layout;
+        a.tile_chains = g.tile_chains;
         if (g.tile_chains)
-            HIP_OR_POISON(r, launch_lattice_tiles(g.model, g.L, g.tile_chains, a, s));
+            HIP_OR_POISON(r, launch_lattice_tiles(g.model, g.L, a, s));
         else
             HIP_OR_POISON(r, launch_lattice_sweeps(g.model, g.L, g.layout, g.lpc, g.cpb, a, s));
         r->sweep += (uint32_t)n;
