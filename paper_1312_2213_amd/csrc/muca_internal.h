@@ -74,6 +74,20 @@ struct PolymerConsts {
 
 hipError_t launch_polymer_sweeps(const PolymerArgs &a, const PolymerConsts &k, hipStream_t s);
 
+// The B x B threshold matrix on the device, in tiles of kTableRows x
+// kTableCols entries.  An entry whose 2^32 e^D is so close to an integer that
+// two implementations of exp may floor it differently is listed in its tile's
+// segment of `unsure` (pinned host memory): [count, local index ...], count
+// above kTableUnsure where the segment could not hold them all.
+constexpr int kTableRows = 128, kTableCols = 256, kTableUnsure = 4095;
+inline int table_tiles(int n_bins)
+{
+    return ((n_bins + kTableRows - 1) / kTableRows) * ((n_bins + kTableCols - 1) / kTableCols);
+}
+hipError_t launch_polymer_table(const double *lnW, uint32_t *T, int n_bins, uint32_t *unsure, hipStream_t s);
+// T[pairs[2 i]] = pairs[2 i + 1] for i < n; `pairs` is pinned host memory.
+hipError_t launch_patch_table(uint32_t *T, const uint32_t *pairs, int n, hipStream_t s);
+
 // LDS staging of one block: the threshold table (Potts keeps 8 of its 9
 // columns: the dE = 0 column always accepts) and a histogram of 16-bit
 // counters packed two per word.  A block adds its counters to the global

@@ -618,6 +618,72 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
     }
 }
 
+// One tile of the threshold matrix T[b][b'] = floor(2^32 e^D), D = lnW[b'] -
+// lnW[b] (all ones for D >= 0 and from 2^32 - 1 on).  lnW is pinned host
+// memory: a tile reads its rows' and columns' weights once.  The host's exp
+// decides what the table holds; this one and the host's are within one unit
+// in the last place of e^D each, so entries within eight units of an integer
+// are listed for the host and all others are the host's.  Bound by FP64 issue
+// (an exp per entry): the 2500 x 2500 matrix takes about 30 us, where sixteen
+// host threads and the upload of 25 MB took 3.5 to 8 ms.
+__global__ __launch_bounds__(1024) void polymer_table(const double *lnW, uint32_t *T, int B, uint32_t *unsure)
+{
+    __shared__ double wr[kTableRows], wc[kTableCols];
+    __shared__ uint32_t count;
+    const int r0 = (int)blockIdx.y * kTableRows, c0 = (int)blockIdx.x * kTableCols;
+    const int rows = min(kTableRows, B - r0), cols = min(kTableCols, B - c0);
+    uint32_t *list = unsure + (size_t)(blockIdx.y * gridDim.x + blockIdx.x) * (kTableUnsure + 1);
+    const int tid = (int)threadIdx.x;
+    if (tid < cols)
+        wc[tid] = lnW[c0 + tid];
+    else if (tid >= kTableCols && tid - kTableCols < rows)
+        wr[tid - kTableCols] = lnW[r0 + tid - kTableCols];
+    if (tid == 0)
+        count = 0u;
+    __syncthreads();
+    const int c = tid % kTableCols;
+    if (c < cols) {
+        for (int r = tid / kTableCols; r < rows; r += 1024 / kTableCols) {
+            const double D = wc[c] - wr[r];
+            uint32_t t = D >= 0.0 ? 0xFFFFFFFFu : 0u;
+            if (!(D >= 0.0) && !(D < -23.0)) { // D < -23: 2^32 e^D < 1
+                const double v = exp(D) * 4294967296.0;
+                t = v >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)v;
+                const double n = rint(v);
+                if (!(fabs(v - n) > v * 0x1p-49) && !(n == 0.0) && !(v >= 4294967295.5)) {
+                    const uint32_t k = atomicAdd(&count, 1u);
+                    if (k < (uint32_t)kTableUnsure)
+                        list[1 + k] = (uint32_t)(r * kTableCols + c);
+                }
+            }
+            T[(size_t)(r0 + r) * (size_t)B + (size_t)(c0 + c)] = t;
+        }
+    }
+    __syncthreads();
+    if (tid == 0)
+        list[0] = count;
+}
+
+__global__ void patch_table(uint32_t *T, const uint32_t *pairs, int n)
+{
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i < n)
+        T[pairs[2 * i]] = pairs[2 * i + 1];
+}
+
+hipError_t launch_polymer_table(const double *lnW, uint32_t *T, int n_bins, uint32_t *unsure, hipStream_t s)
+{
+    const dim3 grid((unsigned)((n_bins + kTableCols - 1) / kTableCols), (unsigned)((n_bins + kTableRows - 1) / kTableRows));
+    hipLaunchKernelGGL(polymer_table, grid, dim3(1024), 0, s, lnW, T, n_bins, unsure);
+    return hipGetLastError();
+}
+
+hipError_t launch_patch_table(uint32_t *T, const uint32_t *pairs, int n, hipStream_t s)
+{
+    hipLaunchKernelGGL(patch_table, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, T, pairs, n);
+    return hipGetLastError();
+}
+
 // The cache is used when four blocks of it still fit one CU's 160 KB of
 // LDS: the occupancy the kernel without it reaches at one chain per wave
 // and four waves per SIMD.

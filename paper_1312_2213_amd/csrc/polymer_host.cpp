@@ -6,9 +6,9 @@
 // FENE -(K/2) R^2 ln(1 - ((r - r0)/R)^2) on bonds.  The initial total energy
 // is summed over pairs i < j in ascending order; bins are
 // floor((E - x_lo) * n_bins / (x_hi - x_lo)) on [x_lo, x_hi).
+#include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <thread>
 #include <vector>
 
 #include "muca_internal.h"
@@ -17,6 +17,26 @@
 using namespace muca;
 
 static size_t align256(size_t x) { return (x + 255u) & ~(size_t)255u; }
+
+// Matrices of fewer bins are built on the host: 64 x 64 entries take about
+// 40 us there, as long as the kernel and the wait for it.
+constexpr int kHostTableBins = 64;
+constexpr int kPatchPairs = 32768;
+
+// Pinned staging of a matrix built on the device: the weights, the segments
+// of entries left to the host, and the values that it sends back.
+struct TableStaging {
+    size_t unsure, pairs, bytes;
+};
+
+static TableStaging table_staging(int n_bins)
+{
+    TableStaging s;
+    s.unsure = align256((size_t)n_bins * 8u);
+    s.pairs = s.unsure + align256((size_t)table_tiles(n_bins) * (kTableUnsure + 1) * 4u);
+    s.bytes = s.pairs + (size_t)kPatchPairs * 8u;
+    return s;
+}
 
 static PolymerConsts consts_of(const muca_config *c)
 {
@@ -153,11 +173,21 @@ int muca_polymer_init(muca_run *r, const float *h_pos)
     r->d_table = (uint32_t *)(r->ws + g.off_table);
     r->d_hist = (unsigned long long *)(r->ws + g.off_hist);
     r->mask.assign(g.n_bins, 0);
-    try {
-        r->T.assign((size_t)g.n_bins * g.n_bins, 0u);
-    } catch (const std::bad_alloc &) {
-        return muca_fail(MUCA_E_NOMEM, "polymer init: pinned host memory for the %d x %d threshold table", g.n_bins,
-                         g.n_bins);
+    if (g.n_bins < kHostTableBins) {
+        try {
+            r->T.assign((size_t)g.n_bins * g.n_bins, 0u);
+        } catch (const std::bad_alloc &) {
+            return muca_fail(MUCA_E_NOMEM, "polymer init: pinned host memory for the %d x %d threshold table",
+                             g.n_bins, g.n_bins);
+        }
+    } else {
+        hipError_t e = hipHostMalloc((void **)&r->h_table, table_staging(g.n_bins).bytes,
+                                     hipHostMallocMapped | hipHostMallocCoherent);
+        if (e != hipSuccess || !r->h_table)
+            return muca_fail(MUCA_E_NOMEM, "polymer init: pinned host memory for the threshold table's staging");
+        e = hipHostGetDevicePointer((void **)&r->h_table_dev, r->h_table, 0);
+        if (e != hipSuccess)
+            return muca_fail(MUCA_E_HIP, "polymer init: %s", hipGetErrorString(e));
     }
     hipError_t e = hipMemcpy(r->d_words, pos.data(), pos.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess)
@@ -170,30 +200,59 @@ int muca_polymer_init(muca_run *r, const float *h_pos)
         e = hipStreamSynchronize(r->stream);
     if (e != hipSuccess)
         return muca_fail(MUCA_E_HIP, "polymer init: %s", hipGetErrorString(e));
-    muca_polymer_build(r);
-    return muca_upload_thresholds(r);
+    return muca_rebuild_thresholds(r);
 }
 
-// T[b][b'] = threshold of lnW(b') - lnW(b); rows built in parallel threads
-// (each entry is the same pure function of two doubles).
-void muca_polymer_build(muca_run *r)
+// T[b][b'] = threshold of lnW(b') - lnW(b).  Small matrices are built in the
+// host mirror; the others on the device, except the entries that it leaves to
+// the host's exp (a few in a million of measured weights; more where weights
+// are ratios of small counts, whose 2^32 e^D can be whole numbers).
+int muca_polymer_build(muca_run *r)
 {
     const int B = r->g.n_bins;
     const double *lnW = r->lnW.data();
-    uint32_t *T = r->T.data();
-    unsigned nt = std::thread::hardware_concurrency();
-    nt = nt < 1 ? 1 : (nt > 16 ? 16 : nt);
-    auto work = [&](unsigned t) {
-        for (int b = (int)t; b < B; b += (int)nt)
+    if (!r->T.empty()) {
+        for (int b = 0; b < B; ++b)
             for (int bp = 0; bp < B; ++bp)
-                T[(size_t)b * B + bp] = muca_threshold_of(lnW[bp] - lnW[b]);
+                r->T[(size_t)b * B + bp] = muca_threshold_of(lnW[bp] - lnW[b]);
+        return MUCA_OK;
+    }
+    const TableStaging st = table_staging(B);
+    std::memcpy(r->h_table, lnW, (size_t)B * 8u);
+    uint32_t *unsure = (uint32_t *)(r->h_table + st.unsure), *pairs = (uint32_t *)(r->h_table + st.pairs);
+    const uint32_t *pairs_dev = (const uint32_t *)(r->h_table_dev + st.pairs);
+    HIP_OR_POISON(r, launch_polymer_table((const double *)r->h_table_dev, r->d_table, B,
+                                          (uint32_t *)(r->h_table_dev + st.unsure), r->stream));
+    HIP_OR_POISON(r, hipStreamSynchronize(r->stream));
+    int n = 0;
+    auto set = [&](int row, int col) -> int {
+        if (n == kPatchPairs) {
+            HIP_OR_POISON(r, launch_patch_table(r->d_table, pairs_dev, n, r->stream));
+            HIP_OR_POISON(r, hipStreamSynchronize(r->stream));
+            n = 0;
+        }
+        pairs[2 * n] = (uint32_t)((size_t)row * B + col);
+        pairs[2 * n + 1] = muca_threshold_of(lnW[col] - lnW[row]);
+        ++n;
+        return MUCA_OK;
     };
-    std::vector<std::thread> th;
-    for (unsigned t = 1; t < nt; ++t)
-        th.emplace_back(work, t);
-    work(0);
-    for (auto &x : th)
-        x.join();
+    const int tx = (B + kTableCols - 1) / kTableCols;
+    for (int t = 0; t < table_tiles(B); ++t) {
+        const uint32_t *list = unsure + (size_t)t * (kTableUnsure + 1);
+        const int r0 = t / tx * kTableRows, c0 = t % tx * kTableCols;
+        const int rows = std::min(kTableRows, B - r0), cols = std::min(kTableCols, B - c0);
+        const bool whole = list[0] > (uint32_t)kTableUnsure; // the list is cut short
+        const int count = whole ? rows * cols : (int)list[0];
+        for (int k = 0; k < count; ++k) {
+            const int row = whole ? k / cols : (int)list[1 + k] / kTableCols;
+            const int col = whole ? k % cols : (int)list[1 + k] % kTableCols;
+            if (int rc = set(r0 + row, c0 + col))
+                return rc;
+        }
+    }
+    if (n)
+        HIP_OR_POISON(r, launch_patch_table(r->d_table, pairs_dev, n, r->stream));
+    return MUCA_OK;
 }
 
 int muca_polymer_enqueue(muca_run *r, int64_t sweeps, bool record, hipStream_t s)

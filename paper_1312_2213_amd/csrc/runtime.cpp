@@ -296,6 +296,8 @@ muca_run::~muca_run()
         (void)hipEventDestroy(merge_ev);
     if (h_hist)
         (void)hipHostFree(h_hist);
+    if (h_table)
+        (void)hipHostFree(h_table);
 }
 
 // The table goes out from its pinned host mirror without a wait: the next
@@ -308,11 +310,15 @@ int muca_upload_thresholds(muca_run *r)
     return MUCA_OK;
 }
 
+int64_t muca_table_size(const muca_run *r) { return (int64_t)r->g.n_bins * r->g.n_cols; }
+
 int muca_rebuild_thresholds(muca_run *r)
 {
-    if (r->g.model == kPolymer)
-        muca_polymer_build(r);
-    else
+    if (r->g.model == kPolymer) {
+        const int rc = muca_polymer_build(r);
+        if (rc || r->T.empty())
+            return rc;
+    } else
         muca_lattice_thresholds(r->g.model, r->cfg.beta, r->g.n_bins, r->g.n_cols, r->lnW.data(), r->T.data());
     return muca_upload_thresholds(r);
 }
@@ -387,16 +393,14 @@ try {
     r->P.assign(g.n_bins, 0.0);
     r->H_last.assign(g.n_bins, 0u);
     r->lnW_last.assign(g.n_bins, 0.0);
-    if (g.model != kPolymer) {
-        // coherent: the merge's drain kernel writes it directly
-        hipError_t e = hipHostMalloc((void **)&r->h_hist, (size_t)(g.n_bins + 1) * 8u,
-                                     hipHostMallocMapped | hipHostMallocCoherent);
-        if (e == hipSuccess)
-            e = hipHostGetDevicePointer((void **)&r->h_hist_dev, r->h_hist, 0);
-        if (e != hipSuccess) {
-            delete r;
-            return muca_fail(MUCA_E_HIP, "init: pinned staging: %s", hipGetErrorString(e));
-        }
+    // coherent: the merge's drain kernel writes it directly
+    hipError_t e = hipHostMalloc((void **)&r->h_hist, (size_t)(g.n_bins + 1) * 8u,
+                                 hipHostMallocMapped | hipHostMallocCoherent);
+    if (e == hipSuccess)
+        e = hipHostGetDevicePointer((void **)&r->h_hist_dev, r->h_hist, 0);
+    if (e != hipSuccess) {
+        delete r;
+        return muca_fail(MUCA_E_HIP, "init: pinned staging: %s", hipGetErrorString(e));
     }
     if (g.model == kPolymer) {
         rc = muca_polymer_init(r, h_pos);
@@ -429,7 +433,7 @@ try {
     a.model = g.model;
     a.layout = g.layout;
     a.chain0 = c->chain0;
-    hipError_t e = launch_lattice_init(a, r->stream);
+    e = launch_lattice_init(a, r->stream);
     if (e == hipSuccess)
         e = launch_fill_u64(r->d_hist, g.n_bins + 1, r->stream);
     std::vector<int32_t> bins(g.c_pad);
@@ -674,15 +678,13 @@ try {
         return rc;
     if (r->pending <= 0)
         return muca_fail(MUCA_E_STATE, "merge without sweeps since the last merge");
-    if (r->h_hist) {
-        // the histogram and the accepted-move count behind it are written to
-        // pinned host memory and cleared by one kernel queued behind the
-        // sweeps; the event behind it is all that muca_merge_finish waits for
-        if (!r->merge_ev)
-            HIP_OR_POISON(r, hipEventCreateWithFlags(&r->merge_ev, hipEventDisableTiming));
-        HIP_OR_POISON(r, launch_drain_u64(r->d_hist, r->h_hist_dev, r->g.n_bins + 1, r->stream));
-        HIP_OR_POISON(r, hipEventRecord(r->merge_ev, r->stream));
-    }
+    // the histogram and the accepted-move count behind it are written to
+    // pinned host memory and cleared by one kernel queued behind the
+    // sweeps; the event behind it is all that muca_merge_finish waits for
+    if (!r->merge_ev)
+        HIP_OR_POISON(r, hipEventCreateWithFlags(&r->merge_ev, hipEventDisableTiming));
+    HIP_OR_POISON(r, launch_drain_u64(r->d_hist, r->h_hist_dev, r->g.n_bins + 1, r->stream));
+    HIP_OR_POISON(r, hipEventRecord(r->merge_ev, r->stream));
     r->merge_begun = true;
     return MUCA_OK;
 }
@@ -698,18 +700,10 @@ try {
     if (!r->merge_begun)
         return muca_fail(MUCA_E_STATE, "muca_merge_finish without muca_merge_begin");
     r->merge_begun = false;
-    const int B = r->g.n_bins;
-    if (r->h_hist) {
-        // the read-back is behind the sweeps and behind the last threshold
-        // upload, so the pinned mirror may be rewritten once it has completed
-        HIP_OR_POISON(r, hipEventSynchronize(r->merge_ev));
-        return muca_finish_iteration(r, r->h_hist, r->h_hist[B], st);
-    }
-    std::vector<uint64_t> H(B + 1); // the histogram and the accepted-move count behind it
-    HIP_OR_POISON(r, hipStreamSynchronize(r->stream));
-    HIP_OR_POISON(r, hipMemcpy(H.data(), r->d_hist, (size_t)(B + 1) * 8u, hipMemcpyDeviceToHost));
-    HIP_OR_POISON(r, launch_fill_u64(r->d_hist, B + 1, r->stream));
-    return muca_finish_iteration(r, H.data(), H[B], st);
+    // the read-back is behind the sweeps and behind the last threshold
+    // upload, so the pinned mirror may be rewritten once it has completed
+    HIP_OR_POISON(r, hipEventSynchronize(r->merge_ev));
+    return muca_finish_iteration(r, r->h_hist, r->h_hist[r->g.n_bins], st);
 }
 MUCA_ABI_CATCH
 
@@ -916,10 +910,16 @@ MUCA_ABI_CATCH
 
 extern "C" int muca_get_thresholds(const muca_run *r, uint32_t *h, int64_t count)
 try {
-    if (!r || !h || count != (int64_t)r->T.size())
+    if (!r || !h || count != muca_table_size(r))
         return muca_fail(MUCA_E_ARG, "bad arguments");
-    std::memcpy(h, r->T.data(), (size_t)count * 4u);
-    return MUCA_OK;
+    if (!r->T.empty()) {
+        std::memcpy(h, r->T.data(), (size_t)count * 4u);
+        return MUCA_OK;
+    }
+    hipError_t e = hipStreamSynchronize(r->stream);
+    if (e == hipSuccess)
+        e = hipMemcpy(h, r->d_table, (size_t)count * 4u, hipMemcpyDeviceToHost);
+    return e == hipSuccess ? MUCA_OK : muca_fail(MUCA_E_HIP, "thresholds: %s", hipGetErrorString(e));
 }
 MUCA_ABI_CATCH
 
@@ -941,9 +941,13 @@ try {
     int rc = check_run(r);
     if (rc)
         return rc;
-    if (!h || count != (int64_t)r->T.size())
+    if (!h || count != muca_table_size(r))
         return muca_fail(MUCA_E_ARG, "bad arguments");
     HIP_OR_POISON(r, hipStreamSynchronize(r->stream));
+    if (r->T.empty()) {
+        HIP_OR_POISON(r, hipMemcpy(r->d_table, h, (size_t)count * 4u, hipMemcpyHostToDevice));
+        return MUCA_OK;
+    }
     std::memcpy(r->T.data(), h, (size_t)count * 4u);
     return muca_upload_thresholds(r);
 }
@@ -1075,7 +1079,16 @@ try {
     put_vec(o, r->lnR);
     put_vec(o, r->P);
     put_vec(o, r->mask);
-    put_vec(o, r->T);
+    if (r->T.empty()) { // the matrix is on the device only
+        std::vector<uint32_t> T((size_t)muca_table_size(r));
+        if (h_buf) {
+            HIP_OR_POISON(r, hipStreamSynchronize(r->stream));
+            HIP_OR_POISON(r, hipMemcpy(T.data(), r->d_table, T.size() * 4u, hipMemcpyDeviceToHost));
+        }
+        put_vec(o, T);
+    } else {
+        put_vec(o, r->T);
+    }
     put_vec(o, r->H_last);
     put_vec(o, r->lnW_last);
     const uint64_t ws = r->g.ws_bytes;
@@ -1121,7 +1134,7 @@ try {
     const uint64_t B = r->g.n_bins;
     bool ok = rd.pod(sweep) && rd.pod(iteration) && rd.pod(pending) && rd.pod(have_last) &&
               rd.vec(lnW, B) && rd.vec(lnR, B) && rd.vec(P, B) && rd.vec(mask, r->mask.size()) &&
-              rd.vec(T, r->T.size()) && rd.vec(H_last, B) && rd.vec(lnW_last, B);
+              rd.vec(T, (uint64_t)muca_table_size(r)) && rd.vec(H_last, B) && rd.vec(lnW_last, B);
     uint64_t ws = 0;
     ok = ok && rd.pod(ws) && ws == r->g.ws_bytes && rd.left == ws;
     if (!ok)
@@ -1136,7 +1149,8 @@ try {
     r->lnR = lnR;
     r->P = P;
     r->mask = mask;
-    std::copy(T.begin(), T.end(), r->T.begin());
+    if (!r->T.empty()) // else the table is in the workspace just restored
+        std::copy(T.begin(), T.end(), r->T.begin());
     r->H_last = H_last;
     r->lnW_last = lnW_last;
     return MUCA_OK;

@@ -67,8 +67,13 @@ struct muca_run {
     std::vector<double> lnW, lnR, P;
     std::vector<uint8_t> mask;     // bins linked by the recursion / measured for flatness
     // host mirror of the thresholds, the source of their asynchronous upload:
-    // rewritten only after the run's stream was synchronised
+    // rewritten only after the run's stream was synchronised.  Empty for
+    // polymer runs whose matrix is built on the device.
     std::vector<uint32_t, PinnedAllocator<uint32_t>> T;
+    // polymer runs without that mirror: pinned host memory that the device
+    // reads and writes while it builds the matrix (weights in, entries left
+    // to the host out, their values back in)
+    uint8_t *h_table = nullptr, *h_table_dev = nullptr;
     std::vector<uint64_t> H_last;  // last merged histogram H^(n)
     std::vector<double> lnW_last;  // lnW^(n) that produced H_last
     uint32_t sweep = 0;            // global sweep counter (Philox counter word 1)
@@ -76,8 +81,8 @@ struct muca_run {
     int64_t pending = 0;           // recorded sweeps since the last merge
     bool have_last = false;
     bool poisoned = false;
-    // pinned host staging (lattice runs): the histogram and accepted-move
-    // count read back at a merge, and its device-side address
+    // pinned host staging: the histogram and accepted-move count read back at
+    // a merge, and its device-side address
     uint64_t *h_hist = nullptr;
     unsigned long long *h_hist_dev = nullptr;
     // measured time of one batched work item per sweep (microseconds), by
@@ -151,7 +156,10 @@ int muca_finish_iteration(muca_run *r, const uint64_t *H, uint64_t accepted, muc
 // polymer.cpp
 int muca_polymer_geometry(const muca_config *c, muca::Geometry *g);
 int muca_polymer_init(muca_run *r, const float *h_pos);
-void muca_polymer_build(muca_run *r);
+// Builds the B x B matrix from lnW on the device (or in the host mirror,
+// which the caller uploads); the caller has synchronised the run's stream.
+int muca_polymer_build(muca_run *r);
+int64_t muca_table_size(const muca_run *r);
 // queues the upload of the host threshold mirror on the run's stream
 int muca_upload_thresholds(muca_run *r);
 int muca_polymer_enqueue(muca_run *r, int64_t sweeps, bool record, hipStream_t s);
