@@ -8,14 +8,15 @@
 // Philox(c, g, i, SWEEP): words 0..2 give the displacement
 // ((w >> 8) 2^-24 - 1/2) * step per axis (float), word 3 the acceptance.
 //
-// Mapping: one chain per wavefront, lane j holds bead j and the energy of
-// bond (j, j+1), and for 64 < N <= 128 also bead j + 64 and its bond.  At the start of a sweep lane j computes bead j's
+// Mapping: one chain per wavefront, lane j holds bead j (and for 64 < N <= 128
+// also bead j + 64).  At the start of a sweep lane j computes bead j's
 // proposal and the FENE energies of its new bonds (the backward one for both
-// outcomes of the previous bead's move).  For a move of bead i every lane
-// computes its pair term new - old in FP64 (the two bonded partners take the
-// precomputed bond energies); the terms are summed by a fixed binary tree
-// (lane k += lane k + s for s = 32, 16, ..., 1) built from lane permutes and
-// DPP moves, so the sum is the same number on every run.  The acceptance
+// outcomes of the previous bead's move), and from them what each neighbour's
+// move will change in its own bond.  For a move of bead i every lane computes
+// its pair term new - old in FP64 (the two bonded partners take the
+// precomputed changes); the terms are summed by a fixed binary tree (lane k
+// += lane k + s for s = 32, 16, ..., 1) built from lane permutes and DPP
+// moves, so the sum is the same number on every run.  The acceptance
 // threshold T[b][b'] of the bin change is one load from the B x B matrix.
 //
 // With the paper's move set (moves = 1) each sweep continues with a
@@ -73,13 +74,13 @@ __device__ __forceinline__ double dist2(float ax, float ay, float az, float bx, 
     return dx * dx + dy * dy + dz * dz;
 }
 
-// The same squared distance with the first position already in FP64 (a
-// float converts to double exactly).
-__device__ __forceinline__ double dist2d(double ax, double ay, double az, float bx, float by, float bz)
+// The same squared distance with both positions already in FP64 (a float
+// converts to double exactly).
+__device__ __forceinline__ double dist2d(double ax, double ay, double az, double bx, double by, double bz)
 {
-    const double dx = ax - (double)bx;
-    const double dy = ay - (double)by;
-    const double dz = az - (double)bz;
+    const double dx = ax - bx;
+    const double dy = ay - by;
+    const double dz = az - bz;
     return dx * dx + dy * dy + dz * dz;
 }
 
@@ -217,18 +218,53 @@ __device__ __forceinline__ void quat_rotate(double w, double x, double y, double
 __host__ __device__ inline int pair_row(int a, int N) { return a * N - a * (a + 1) / 2 - a - 1; }
 __host__ __device__ inline int pair_slots(int N) { return N * (N - 1) / 2; }
 
+typedef __attribute__((address_space(3))) const double lds_f64;
+typedef __attribute__((address_space(3))) double lds_f64_out;
+
+// A bead as every lane reads it (one LDS broadcast instead of a lane read per
+// word): while shifts run, its proposal and, without the cache, where it is;
+// while rotations run, where it is.
+struct alignas(16) BeadRecord {
+    double x, y, z;
+    uint32_t w, pad; // acceptance word
+};
+
+__host__ __device__ inline size_t hist_bytes(int n_bins) { return (size_t)((n_bins + 3) & ~3) * 4u; }
+// LDS of one chain: [pair terms | records].
+__host__ __device__ inline size_t chain_cache_bytes(int N) { return (size_t)((pair_slots(N) + 1) & ~1) * 8u; }
+__host__ __device__ inline size_t chain_lds(int N, bool cache)
+{
+    return (cache ? chain_cache_bytes(N) : (size_t)N * sizeof(BeadRecord)) + (size_t)N * sizeof(BeadRecord);
+}
+
+__device__ __forceinline__ bool lane_bit(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// Bound by instruction issue: a move is one serial chain (squared distance,
+// pair term, six-level tree sum, bin, threshold) of about 150 instructions
+// whose dependent FP64 operations a single wavefront cannot overlap; with
+// four or more per SIMD the vector pipe itself is full.  What a sweep knows
+// beforehand is therefore taken out of the moves: proposals, words and bond
+// changes are computed for all beads at once (the first read back by LDS
+// broadcast, the others already in the lane that adds them to the sum), the
+// lanes of a move are scalar masks shifted along the chain, and the cache is
+// addressed by two precomputed offsets per lane.  Moves/s, against lane reads
+// per word, masks from comparisons and the cache for up to 64 beads only:
+//   N = 40, 4096 chains, shifts    3.1e9 -> 4.4e9    full set  1.5e9 -> 2.1e9
+//   N = 40,  512 chains, shifts    9.3e8 -> 1.1e9
+//   N = 80, 4096 chains, shifts    1.9e9 -> 2.6e9    full set  1.15e9 -> 1.55e9
+//   N = 80,  512 chains                              full set  4.3e8 -> 5.4e8
+//
 // One chain per wavefront.  Lane j holds bead j and, with TWO (64 < N <= 128),
 // bead j + 64 (register set 1).  A pair sum slot is lane j's term plus, with
 // TWO, the term of bead j + 64.  MOVES: the paper's full move set (a
 // separate variant, so the shift-only kernel carries none of its registers).
-// CACHE (N <= 64 only): a shift or rotation reads the old pair term from the
-// cache instead of recomputing it, and an accepted move writes the new ones;
-// an accepted double bridging renumbers beads and refills the cache.
+// CACHE: a shift or rotation reads the old pair term from the cache instead
+// of recomputing it, and an accepted move writes the new ones; an accepted
+// double bridging renumbers beads and refills the cache.
 template <bool TWO, bool MOVES, bool CACHE>
 __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams p)
 {
-    static_assert(!CACHE || !TWO, "the pair cache serves N <= 64");
-    extern __shared__ uint32_t lhist[];
+    extern __shared__ __align__(16) uint32_t lhist[];
     for (int i = threadIdx.x; i < a.n_bins; i += blockDim.x)
         lhist[i] = 0u;
     __syncthreads();
@@ -236,294 +272,352 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
     constexpr int NS = TWO ? 2 : 1; // beads per lane
     constexpr int SLOTS = 64 * NS;  // bead slots per chain in memory
     const int j = (int)(threadIdx.x & 63u);
-    const int c = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c = (int)(blockIdx.x * (blockDim.x >> 6)) + wave;
     const int N = a.n_beads;
     float4 *pos = a.pos + (size_t)c * SLOTS;
     double *bond = a.bond + (size_t)c * SLOTS;
-    float4 x[NS];
-    // the shift-only kernel for N <= 64 also keeps x in FP64 for the pair
-    // distances (the other variants have no registers to spare for it)
-    constexpr bool XD = !TWO && !MOVES;
-    double xd[NS], yd[NS], zd[NS];
-    auto own_d2 = [&](int s, float bx, float by, float bz) {
-        if constexpr (XD)
-            return dist2d(xd[s], yd[s], zd[s], bx, by, bz);
-        else
-            return dist2(x[s].x, x[s].y, x[s].z, bx, by, bz);
-    };
-    auto set_xd = [&](int s) {
-        if constexpr (XD)
-            xd[s] = x[s].x, yd[s] = x[s].y, zd[s] = x[s].z;
-    };
-    double ub[NS]; // energy of bond (bead, bead + 1)
+    double xd[NS], yd[NS], zd[NS]; // positions (each a float, exactly)
+    double ub[NS];                 // energy of bond (bead, bead + 1)
+    uint64_t valid[NS];            // lanes that hold a bead
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int bd = j + 64 * s;
-        x[s] = bd < N ? pos[bd] : make_float4(0.f, 0.f, 0.f, 0.f);
-        set_xd(s);
+        const float4 v = bd < N ? pos[bd] : make_float4(0.f, 0.f, 0.f, 0.f);
+        xd[s] = v.x, yd[s] = v.y, zd[s] = v.z;
         ub[s] = bd < N - 1 ? bond[bd] : 0.0;
+        const int n = N - 64 * s;
+        valid[s] = n >= 64 ? ~0ull : (1ull << n) - 1ull;
     }
-    double E = a.energy[c];
-    int32_t b = a.bins[c];
+    double E = a.energy[c]; // from the first accepted move on valid in lane 0 only
+    int32_t b = __builtin_amdgcn_readfirstlane(a.bins[c]);
     const uint32_t chain = (uint32_t)(a.chain0 + c);
-    const bool counts = a.record && c < a.n_chains && j == 0;
     const uint32_t B = (uint32_t)a.n_bins;
     const int up_l = (j + 1) & 63, dn_l = (j + 63) & 63;
     uint64_t nacc = 0u; // accepted moves of the recorded sweeps (wave-uniform)
-    // CACHE: the wave's pair terms; lane j's slot for the moving bead i is
-    // f(j) + i when j < i and f(i) + j when j > i
-    double *cache = nullptr;
-    int c_lo = 0;
-    // every pair term at the current positions; the lanes of one wave
-    // exchange terms through LDS, whose accesses from one wave complete in
-    // order: the fence only keeps the compiler from moving them
+
+    uint8_t *mine = (uint8_t *)lhist + hist_bytes(a.n_bins) + (size_t)wave * chain_lds(N, CACHE);
+    double *cache = (double *)mine; // CACHE
+    BeadRecord *was = (BeadRecord *)mine, *rec = (BeadRecord *)(mine + (CACHE ? chain_cache_bytes(N) : (size_t)N * sizeof(BeadRecord)));
+    // lanes of one wave exchange data through LDS, whose accesses from one
+    // wave complete in order: the fence only keeps the compiler from moving
+    // them
+    auto lds_fence = [] { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); };
+    auto readlane_bead = [&](int k, double &px, double &py, double &pz) {
+        const bool h = TWO && k >= 64;
+        px = readlane_f64(h ? xd[NS - 1] : xd[0], k & 63);
+        py = readlane_f64(h ? yd[NS - 1] : yd[0], k & 63);
+        pz = readlane_f64(h ? zd[NS - 1] : zd[0], k & 63);
+    };
+    auto bond_of = [&](int k) { return readlane_f64((TWO && k >= 64) ? ub[NS - 1] : ub[0], k & 63); };
+    auto lane_of = [](int s, int bead) -> uint64_t { // the lane that holds `bead` in set s
+        const int l = bead - 64 * s;
+        return (l >= 0 && l < 64) ? 1ull << l : 0ull;
+    };
+    // every pair term at the current positions
     auto fill_cache = [&]() {
         for (int k = 0; k + 2 < N; ++k) {
-            const float kx = readlane_f32(x[0].x, k), ky = readlane_f32(x[0].y, k), kz = readlane_f32(x[0].z, k);
-            if (j >= k + 2 && j < N)
-                cache[pair_row(k, N) + j] = lj_energy(p, own_d2(0, kx, ky, kz));
+            double kx, ky, kz;
+            readlane_bead(k, kx, ky, kz);
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int bd = j + 64 * s;
+                if (bd >= k + 2 && bd < N)
+                    cache[pair_row(k, N) + bd] = lj_energy(p, dist2d(xd[s], yd[s], zd[s], kx, ky, kz));
+            }
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        lds_fence();
     };
-    if constexpr (CACHE) {
-        cache = (double *)(lhist + ((a.n_bins + 1) & ~1)) + (size_t)(threadIdx.x >> 6) * pair_slots(N);
-        c_lo = pair_row(j, N);
+    if constexpr (CACHE)
         fill_cache();
+
+    // byte addresses of this lane's pair terms with bead i: lo + 8 i for the
+    // beads before it, hi + 8 pair_row(i) for those behind it
+    const uint32_t cache_at = (uint32_t)(uintptr_t)(lds_f64 *)cache;
+    uint32_t lo[NS], hi[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const int bd = j + 64 * s;
+        lo[s] = cache_at + 8u * (uint32_t)pair_row(bd, N);
+        hi[s] = cache_at + 8u * (uint32_t)bd;
     }
+    uint32_t row_at = 4u * B * (uint32_t)b; // byte offset of the present bin's thresholds (below 2^28)
+
+    // A move of bead i to (nx, ny, nz); me: the bead's lane.  The pair terms'
+    // changes are summed over the lanes, with dup in the lane of bead i + 1
+    // and ddn in that of i - 1 (the changes of its two bonds); then the bin
+    // and the acceptance by word w.  An accepted move changes the position,
+    // the cached terms, E and b.
+    auto attempt = [&](int i, const uint64_t (&me)[NS], double nx, double ny, double nz, const double (&dup)[NS],
+                       const double (&ddn)[NS], uint32_t w) -> bool {
+        uint64_t up[NS], dn[NS], pairs[NS];
+        up[0] = me[0] << 1;
+        dn[0] = me[0] >> 1;
+        if constexpr (TWO) {
+            up[NS - 1] = (me[NS - 1] << 1) | (me[0] >> 63);
+            dn[NS - 1] = me[NS - 1] >> 1;
+            dn[0] |= me[NS - 1] << 63;
+        }
+        double wx = 0.0, wy = 0.0, wz = 0.0;
+        if constexpr (!CACHE)
+            wx = was[i].x, wy = was[i].y, wz = was[i].z;
+        double t = 0.0;
+        double lnew[NS]; // CACHE: the new pair terms
+        uint32_t at[NS]; // and where they belong
+        const uint32_t row = 8u * (uint32_t)pair_row(i, N);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            pairs[s] = valid[s] & ~(me[s] | up[s] | dn[s]);
+            double ts = 0.0;
+            lnew[s] = 0.0;
+            at[s] = 0u;
+            if (lane_bit(pairs[s])) {
+                if constexpr (CACHE) {
+                    at[s] = j + 64 * s < i ? lo[s] + 8u * (uint32_t)i : hi[s] + row;
+                    // the read first, its latency covered by the new term
+                    const double old = *(lds_f64 *)(uintptr_t)at[s];
+                    __builtin_amdgcn_sched_barrier(0);
+                    lnew[s] = lj_energy(p, dist2d(xd[s], yd[s], zd[s], nx, ny, nz));
+                    ts = lnew[s] - old;
+                } else {
+                    ts = lj_energy(p, dist2d(xd[s], yd[s], zd[s], nx, ny, nz)) -
+                         lj_energy(p, dist2d(xd[s], yd[s], zd[s], wx, wy, wz));
+                }
+            }
+            ts = lane_bit(up[s]) ? dup[s] : ts;
+            ts = lane_bit(dn[s]) ? ddn[s] : ts;
+            t = s == 0 ? ts : t + ts;
+        }
+        const double En = E + tree_sum(t); // in lane 0
+        const uint64_t inside = __builtin_amdgcn_ballot_w64(En >= p.x_lo) & __builtin_amdgcn_ballot_w64(En < p.x_hi);
+        // (inside the range the quotient is not negative: truncation is floor)
+        const uint32_t bn = (uint32_t)__builtin_amdgcn_readlane((int)((En - p.x_lo) * p.scale), 0);
+        if (!(inside & 1ull) || bn >= B)
+            return false;
+        const uint32_t T = *(const uint32_t *)((const uint8_t *)a.thresholds + (row_at + 4u * bn));
+        if (!(__builtin_amdgcn_ballot_w64(w < T) & 1ull))
+            return false;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (lane_bit(me[s]))
+                xd[s] = nx, yd[s] = ny, zd[s] = nz;
+            if constexpr (CACHE) {
+                if (lane_bit(pairs[s]))
+                    *(lds_f64_out *)(uintptr_t)at[s] = lnew[s];
+            }
+        }
+        if constexpr (CACHE)
+            lds_fence();
+        E = En;
+        b = (int32_t)bn;
+        row_at = 4u * B * bn;
+        return true;
+    };
 
     for (int s_ = 0; s_ < a.n_sweeps; ++s_) {
         const uint32_t g = a.g0 + (uint32_t)s_;
         float pnx[NS], pny[NS], pnz[NS];
-        uint32_t racc[NS], flags[NS];
-        double f_fwd[NS], f_rej[NS], f_acc[NS];
         // Each bead's proposal: no earlier move of the sweep changes the bead.
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const Words4 w = philox4x32_10(chain, g, (uint32_t)(j + 64 * s), kTagSweep, a.k0, a.k1);
-            pnx[s] = x[s].x + ((float)(w.w[0] >> 8) * 5.9604644775390625e-08f - 0.5f) * a.step;
-            pny[s] = x[s].y + ((float)(w.w[1] >> 8) * 5.9604644775390625e-08f - 0.5f) * a.step;
-            pnz[s] = x[s].z + ((float)(w.w[2] >> 8) * 5.9604644775390625e-08f - 0.5f) * a.step;
-            racc[s] = min(w.w[3], 0xFFFFFFFEu); // accept iff racc < T
+            pnx[s] = (float)xd[s] + ((float)(w.w[0] >> 8) * 5.9604644775390625e-08f - 0.5f) * a.step;
+            pny[s] = (float)yd[s] + ((float)(w.w[1] >> 8) * 5.9604644775390625e-08f - 0.5f) * a.step;
+            pnz[s] = (float)zd[s] + ((float)(w.w[2] >> 8) * 5.9604644775390625e-08f - 0.5f) * a.step;
+            if (j + 64 * s < N) {
+                // accept iff min(word, 2^32 - 2) < T
+                rec[j + 64 * s] = BeadRecord{pnx[s], pny[s], pnz[s], min(w.w[3], 0xFFFFFFFEu), 0u};
+                if constexpr (!CACHE)
+                    was[j + 64 * s] = BeadRecord{xd[s], yd[s], zd[s], 0u, 0u};
+            }
         }
+        lds_fence();
         // The new bond energies of each bead's move, all known now: bead + 1
         // has not moved when the bead moves, and bead - 1 sits either where
         // the sweep found it (its move rejected) or at its proposal
-        // (accepted).  Bonds whose stretch leaves the FENE domain are flagged.
-        float rx[NS], ry[NS], rz[NS], lx[NS], ly[NS], lz[NS], qx[NS], qy[NS], qz[NS];
+        // (accepted).  Bonds whose stretch leaves the FENE domain break the
+        // move: bits of brk_f (forward), brk_r, brk_a (backward).
+        double f_fwd[NS], f_rej[NS], f_acc[NS];
+        uint64_t brk_f[NS], brk_r[NS], brk_a[NS];
+        {
+            float rx[NS], ry[NS], rz[NS], lx[NS], ly[NS], lz[NS], qx[NS], qy[NS], qz[NS];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            rx[s] = from_lane(x[s].x, up_l), ry[s] = from_lane(x[s].y, up_l), rz[s] = from_lane(x[s].z, up_l);
-            lx[s] = from_lane(x[s].x, dn_l), ly[s] = from_lane(x[s].y, dn_l), lz[s] = from_lane(x[s].z, dn_l);
-            qx[s] = from_lane(pnx[s], dn_l), qy[s] = from_lane(pny[s], dn_l), qz[s] = from_lane(pnz[s], dn_l);
-        }
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const int bd = j + 64 * s;
-            // bead + 1 is in the next lane of the same set, or lane 0 of the next set
-            const int rs = (j == 63) ? s + 1 : s;
-            // bead - 1 is in the previous lane of the same set, or lane 63 of the previous set
-            const int ls = (j == 0) ? s - 1 : s;
-            f_fwd[s] = f_rej[s] = f_acc[s] = 0.0;
-            flags[s] = 0u; // bit 0: forward broken, 1: back broken (rejected), 2: back broken (accepted)
-            if (bd + 1 < N && rs < NS) {
-                bool br = false;
-                const float ax = rs == s ? rx[s] : rx[NS - 1], ay = rs == s ? ry[s] : ry[NS - 1],
-                            az = rs == s ? rz[s] : rz[NS - 1];
-                f_fwd[s] = fene_energy(p, dist2(ax, ay, az, pnx[s], pny[s], pnz[s]), &br);
-                flags[s] |= br ? 1u : 0u;
+            for (int s = 0; s < NS; ++s) {
+                const float x = (float)xd[s], y = (float)yd[s], z = (float)zd[s];
+                rx[s] = from_lane(x, up_l), ry[s] = from_lane(y, up_l), rz[s] = from_lane(z, up_l);
+                lx[s] = from_lane(x, dn_l), ly[s] = from_lane(y, dn_l), lz[s] = from_lane(z, dn_l);
+                qx[s] = from_lane(pnx[s], dn_l), qy[s] = from_lane(pny[s], dn_l), qz[s] = from_lane(pnz[s], dn_l);
             }
-            if (bd >= 1 && bd < N && ls >= 0) {
-                bool br = false, ba = false;
-                const float ax = ls == s ? lx[s] : lx[0], ay = ls == s ? ly[s] : ly[0], az = ls == s ? lz[s] : lz[0];
-                const float bx = ls == s ? qx[s] : qx[0], by = ls == s ? qy[s] : qy[0], bz = ls == s ? qz[s] : qz[0];
-                f_rej[s] = fene_energy(p, dist2(ax, ay, az, pnx[s], pny[s], pnz[s]), &br);
-                f_acc[s] = fene_energy(p, dist2(bx, by, bz, pnx[s], pny[s], pnz[s]), &ba);
-                flags[s] |= (br ? 2u : 0u) | (ba ? 4u : 0u);
-            }
-        }
-        bool prev_acc = false;
-        for (int i = 0; i < N; ++i) {
-            const int li = i & 63;
-            const bool hi = TWO && i >= 64; // the moving bead's register set
-            auto pick = [&](auto v0, auto v1) { return hi ? v1 : v0; };
-            const float nx = readlane_f32(pick(pnx[0], pnx[NS - 1]), li);
-            const float ny = readlane_f32(pick(pny[0], pny[NS - 1]), li);
-            const float nz = readlane_f32(pick(pnz[0], pnz[NS - 1]), li);
-            const float xi = readlane_f32(pick(x[0].x, x[NS - 1].x), li);
-            const float yi = readlane_f32(pick(x[0].y, x[NS - 1].y), li);
-            const float zi = readlane_f32(pick(x[0].z, x[NS - 1].z), li);
-            const uint32_t w3 = __builtin_amdgcn_readlane(pick(racc[0], racc[NS - 1]), li);
-            const uint32_t fl = __builtin_amdgcn_readlane(pick(flags[0], flags[NS - 1]), li);
-            const double fb_i = readlane_f64(prev_acc ? pick(f_acc[0], f_acc[NS - 1]) : pick(f_rej[0], f_rej[NS - 1]),
-                                             li);                       // new bond (i - 1, i)
-            const double ff_i = readlane_f64(pick(f_fwd[0], f_fwd[NS - 1]), li); // new bond (i, i + 1)
-            const double ub_i = readlane_f64(pick(ub[0], ub[NS - 1]), li);       // bond (i, i + 1), before
-            double t = 0.0;
-            double lnew = 0.0; // CACHE: this lane's new pair term
-            int slot = 0;
-            const bool paired = j < N && (j > i + 1 || j + 1 < i);
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const int bd = j + 64 * s;
-                const int sep = bd > i ? bd - i : i - bd;
-                double ts = 0.0;
-                if (bd < N && sep >= 2) {
-                    if constexpr (CACHE) {
-                        slot = bd < i ? c_lo + i : pair_row(i, N) + bd;
-                        const double old = cache[slot];
-                        lnew = lj_energy(p, own_d2(s, nx, ny, nz));
-                        // the read first, its latency covered by the new term
-                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x2, 200, 0);
-                        ts = lnew - old;
-                    } else {
-                        const double r2n = own_d2(s, nx, ny, nz);
-                        const double r2o = own_d2(s, xi, yi, zi);
-                        ts = lj_energy(p, r2n) - lj_energy(p, r2o);
-                    }
+                // bead + 1 is in the next lane of the same set, or lane 0 of the next set
+                const int rs = (j == 63) ? s + 1 : s;
+                // bead - 1 is in the previous lane of the same set, or lane 63 of the previous set
+                const int ls = (j == 0) ? s - 1 : s;
+                f_fwd[s] = f_rej[s] = f_acc[s] = 0.0;
+                bool bf = false, br = false, ba = false;
+                if (bd + 1 < N && rs < NS) {
+                    const float ax = rs == s ? rx[s] : rx[NS - 1], ay = rs == s ? ry[s] : ry[NS - 1],
+                                az = rs == s ? rz[s] : rz[NS - 1];
+                    f_fwd[s] = fene_energy(p, dist2(ax, ay, az, pnx[s], pny[s], pnz[s]), &bf);
                 }
-                if (bd == i + 1)
-                    ts = ff_i - ub_i;
-                if (bd == i - 1)
-                    ts = fb_i - ub[s];
-                t = s == 0 ? ts : t + ts;
+                if (bd >= 1 && bd < N && ls >= 0) {
+                    const float ax = ls == s ? lx[s] : lx[0], ay = ls == s ? ly[s] : ly[0], az = ls == s ? lz[s] : lz[0];
+                    const float bx = ls == s ? qx[s] : qx[0], by = ls == s ? qy[s] : qy[0], bz = ls == s ? qz[s] : qz[0];
+                    f_rej[s] = fene_energy(p, dist2(ax, ay, az, pnx[s], pny[s], pnz[s]), &br);
+                    f_acc[s] = fene_energy(p, dist2(bx, by, bz, pnx[s], pny[s], pnz[s]), &ba);
+                }
+                brk_f[s] = __builtin_amdgcn_ballot_w64(bf);
+                brk_r[s] = __builtin_amdgcn_ballot_w64(br);
+                brk_a[s] = __builtin_amdgcn_ballot_w64(ba);
             }
-            const double dE = readlane_f64(tree_sum(t), 0);
-            const bool any_broken = (i + 1 < N && (fl & 1u)) || (i >= 1 && (fl & (prev_acc ? 4u : 2u)));
-            const double En = E + dE;
-            const int32_t bn = energy_bin(p, En, a.n_bins);
-            bool acc = false;
-            if (!any_broken && bn >= 0) {
-                const uint32_t T = a.thresholds[(size_t)b * B + (uint32_t)bn];
-                acc = w3 < T;
-            }
-            if (acc) {
+        }
+        // What a neighbour's move changes in this lane's terms: when bead - 1
+        // moves (bond (bead - 1, bead): its new energy minus the present
+        // one), and when bead + 1 moves (bond (bead, bead + 1), whose present
+        // energy depends on this bead's own move).
+        double dup[NS], ddn_r[NS], ddn_a[NS], next_r[NS], next_a[NS];
+        {
+            double fwd_from[NS], rej_from[NS], acc_from[NS];
 #pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const int bd = j + 64 * s;
-                    if (bd == i) {
-                        x[s].x = nx;
-                        x[s].y = ny;
-                        x[s].z = nz;
-                        set_xd(s);
-                        if (i + 1 < N)
-                            ub[s] = ff_i;
-                    }
-                    if (bd == i - 1)
-                        ub[s] = fb_i;
-                }
-                if constexpr (CACHE) {
-                    if (paired)
-                        cache[slot] = lnew;
-                }
-                E = En;
-                b = bn;
-                nacc += a.record ? 1u : 0u;
+            for (int s = 0; s < NS; ++s) {
+                fwd_from[s] = from_lane_f64(f_fwd[s] - ub[s], dn_l);
+                rej_from[s] = from_lane_f64(f_rej[s], up_l);
+                acc_from[s] = from_lane_f64(f_acc[s], up_l);
             }
-            if constexpr (CACHE)
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            prev_acc = acc;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                dup[s] = (TWO && s == 1 && j == 0) ? fwd_from[0] : fwd_from[s];
+                next_r[s] = (TWO && s == 0 && j == 63) ? rej_from[NS - 1] : rej_from[s];
+                next_a[s] = (TWO && s == 0 && j == 63) ? acc_from[NS - 1] : acc_from[s];
+                ddn_r[s] = next_r[s] - ub[s];
+                ddn_a[s] = next_a[s] - f_fwd[s];
+            }
+        }
+        uint64_t done[NS]; // accepted beads
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            done[s] = 0ull;
+        bool prev_acc = false;
+        uint64_t me[NS];
+        me[0] = 1ull;
+        if constexpr (TWO)
+            me[NS - 1] = 0ull;
+        BeadRecord next = rec[0];
+        for (int i = 0; i < N; ++i) {
+            const BeadRecord r = next;
+            next = rec[i + 1 < N ? i + 1 : i]; // its latency beside this move's arithmetic
+            uint64_t broken = 0ull; // no forward bond at the last bead, no backward one at the first: bits clear
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                broken |= me[s] & (brk_f[s] | (prev_acc ? brk_a[s] : brk_r[s]));
+            if (broken) {
+                prev_acc = false;
+            } else {
+                double ddn[NS];
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    ddn[s] = prev_acc ? ddn_a[s] : ddn_r[s];
+                prev_acc = attempt(i, me, r.x, r.y, r.z, dup, ddn, r.w);
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    done[s] |= prev_acc ? me[s] : 0ull;
+            }
+            if constexpr (TWO)
+                me[NS - 1] = (me[NS - 1] << 1) | (me[0] >> 63);
+            me[0] <<= 1;
+        }
+        if (a.record) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                nacc += (uint64_t)__builtin_popcountll(done[s]);
+        }
+        // the bonds as the accepted moves left them
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const uint64_t after = (done[s] >> 1) | (TWO && s == 0 ? done[NS - 1] << 63 : 0ull); // bead + 1 accepted
+            const double own = lane_bit(done[s]) ? f_fwd[s] : ub[s];
+            const double both = lane_bit(done[s]) ? next_a[s] : next_r[s];
+            ub[s] = lane_bit(after) ? both : own;
         }
         if constexpr (MOVES) {
-            // position of bead k, the same in every lane
-            auto bead = [&](int k, float &px, float &py, float &pz) {
-                const int l = k & 63;
-                const bool h = TWO && k >= 64;
-                px = readlane_f32(h ? x[NS - 1].x : x[0].x, l);
-                py = readlane_f32(h ? x[NS - 1].y : x[0].y, l);
-                pz = readlane_f32(h ? x[NS - 1].z : x[0].z, l);
-            };
-            auto bond_of = [&](int k) { return readlane_f64((TWO && k >= 64) ? ub[NS - 1] : ub[0], k & 63); };
-            // spherical rotations, beads 0..N-1 in order
+            // spherical rotations, beads 0..N-1 in order.  The random numbers
+            // of all beads at once; positions by LDS broadcast, one bead
+            // ahead (a rotation of bead i reads i - 1, i and i + 1, and only
+            // i - 1 can have moved since the phase began).
+            double tau[NS];
+            uint32_t axis[NS];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const Words4 w = philox4x32_10(chain, g, (uint32_t)(j + 64 * s), kTagRotate, a.k0, a.k1);
+                tau[s] = rot_tau(w.w[0]);
+                axis[s] = (uint32_t)(((uint64_t)w.w[1] * 3u) >> 32);
+                if (j + 64 * s < N) {
+                    rec[j + 64 * s] = BeadRecord{xd[s], yd[s], zd[s], min(w.w[3], 0xFFFFFFFEu), 0u};
+                    if constexpr (!CACHE)
+                        was[j + 64 * s] = BeadRecord{xd[s], yd[s], zd[s], 0u, 0u};
+                }
+            }
+            lds_fence();
+            double lx = 0.0, ly = 0.0, lz = 0.0;
+            BeadRecord self = rec[0], right = rec[1], ahead = rec[N > 2 ? 2 : 1];
             for (int i = 0; i < N; ++i) {
-                const Words4 w = philox4x32_10(chain, g, (uint32_t)i, kTagRotate, a.k0, a.k1);
-                float xi, yi, zi, lx = 0.f, ly = 0.f, lz = 0.f, rx = 0.f, ry = 0.f, rz = 0.f;
-                bead(i, xi, yi, zi);
-                if (i >= 1)
-                    bead(i - 1, lx, ly, lz);
-                if (i + 1 < N)
-                    bead(i + 1, rx, ry, rz);
+                const double xi = self.x, yi = self.y, zi = self.z, rx = right.x, ry = right.y, rz = right.z;
+                const uint32_t w3 = self.w;
+                const double tau_i = readlane_f64((TWO && i >= 64) ? tau[NS - 1] : tau[0], i & 63);
                 double ax, ay, az, cx, cy, cz;
                 if (i > 0 && i < N - 1) { // about the line through both neighbours
-                    ax = (double)rx - (double)lx;
-                    ay = (double)ry - (double)ly;
-                    az = (double)rz - (double)lz;
+                    ax = rx - lx;
+                    ay = ry - ly;
+                    az = rz - lz;
                     cx = lx, cy = ly, cz = lz;
                 } else { // an end bead: about a coordinate axis through its neighbour
-                    const uint32_t axis = (uint32_t)(((uint64_t)w.w[1] * 3u) >> 32);
-                    ax = axis == 0u ? 1.0 : 0.0;
-                    ay = axis == 1u ? 1.0 : 0.0;
-                    az = axis == 2u ? 1.0 : 0.0;
+                    const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)((TWO && i >= 64) ? axis[NS - 1] : axis[0]), i & 63);
+                    ax = k == 0u ? 1.0 : 0.0;
+                    ay = k == 1u ? 1.0 : 0.0;
+                    az = k == 2u ? 1.0 : 0.0;
                     cx = i == 0 ? rx : lx, cy = i == 0 ? ry : ly, cz = i == 0 ? rz : lz;
                 }
                 double ox, oy, oz;
-                quat_rotate(rot_tau(w.w[0]), ax, ay, az, (double)xi - cx, (double)yi - cy, (double)zi - cz, ox, oy,
-                            oz);
-                const float nx = (float)(cx + ox), ny = (float)(cy + oy), nz = (float)(cz + oz);
-                bool brl = false, brr = false;
-                const double fl = i >= 1 ? fene_energy(p, dist2(lx, ly, lz, nx, ny, nz), &brl) : 0.0;
-                const double fr = i + 1 < N ? fene_energy(p, dist2(rx, ry, rz, nx, ny, nz), &brr) : 0.0;
-                const double ub_i = bond_of(i);
-                double t = 0.0;
-                double lnew = 0.0; // CACHE: this lane's new pair term
-                int slot = 0;
-                const bool paired = j < N && (j > i + 1 || j + 1 < i);
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const int bd = j + 64 * s;
-                    const int sep = bd > i ? bd - i : i - bd;
-                    double ts = 0.0;
-                    if (bd < N && sep >= 2) {
-                        if constexpr (CACHE) {
-                            slot = bd < i ? c_lo + i : pair_row(i, N) + bd;
-                            const double old = cache[slot];
-                            lnew = lj_energy(p, own_d2(s, nx, ny, nz));
-                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                            __builtin_amdgcn_sched_group_barrier(0x2, 200, 0);
-                            ts = lnew - old;
-                        } else {
-                            const double r2n = own_d2(s, nx, ny, nz);
-                            const double r2o = own_d2(s, xi, yi, zi);
-                            ts = lj_energy(p, r2n) - lj_energy(p, r2o);
-                        }
-                    }
-                    if (bd == i + 1)
-                        ts = fr - ub_i;
-                    if (bd == i - 1)
-                        ts = fl - ub[s];
-                    t = s == 0 ? ts : t + ts;
-                }
-                const double dE = readlane_f64(tree_sum(t), 0);
-                const double En = E + dE;
-                const int32_t bn = energy_bin(p, En, a.n_bins);
+                quat_rotate(tau_i, ax, ay, az, xi - cx, yi - cy, zi - cz, ox, oy, oz);
+                const double nx = (float)(cx + ox), ny = (float)(cy + oy), nz = (float)(cz + oz);
+                // both new bonds at once: the right one in odd lanes, the left
+                // one in even lanes
+                const bool odd = lane_bit(0xAAAAAAAAAAAAAAAAull);
+                bool broken = false;
+                const double f = fene_energy(
+                    p, dist2d(odd ? rx : lx, odd ? ry : ly, odd ? rz : lz, nx, ny, nz), &broken);
+                const uint64_t br = __builtin_amdgcn_ballot_w64(broken);
                 bool acc = false;
-                if (!brl && !brr && bn >= 0)
-                    acc = min(w.w[3], 0xFFFFFFFEu) < a.thresholds[(size_t)b * B + (uint32_t)bn];
-                if (acc) {
+                if (!((i >= 1 && (br & 1ull)) || (i + 1 < N && (br & 2ull)))) {
+                    const double fl = i >= 1 ? readlane_f64(f, 0) : 0.0, fr = i + 1 < N ? readlane_f64(f, 1) : 0.0;
+                    const double up = fr - bond_of(i);
+                    double rdup[NS], rddn[NS];
 #pragma unroll
                     for (int s = 0; s < NS; ++s) {
-                        const int bd = j + 64 * s;
-                        if (bd == i) {
-                            x[s].x = nx;
-                            x[s].y = ny;
-                            x[s].z = nz;
-                            set_xd(s);
-                            if (i + 1 < N)
-                                ub[s] = fr;
+                        rdup[s] = up;
+                        rddn[s] = fl - ub[s];
+                    }
+                    const uint64_t me[2] = {lane_of(0, i), lane_of(1, i)};
+                    uint64_t own[NS];
+#pragma unroll
+                    for (int s = 0; s < NS; ++s)
+                        own[s] = me[s];
+                    acc = attempt(i, own, nx, ny, nz, rdup, rddn, w3);
+                    if (acc) {
+                        nacc += a.record ? 1u : 0u;
+#pragma unroll
+                        for (int s = 0; s < NS; ++s) {
+                            ub[s] = lane_bit(lane_of(s, i + 1 < N ? i : -1)) ? fr : ub[s];
+                            ub[s] = lane_bit(lane_of(s, i - 1)) ? fl : ub[s];
                         }
-                        if (bd == i - 1)
-                            ub[s] = fl;
                     }
-                    if constexpr (CACHE) {
-                        if (paired)
-                            cache[slot] = lnew;
-                    }
-                    E = En;
-                    b = bn;
-                    nacc += a.record ? 1u : 0u;
                 }
-                if constexpr (CACHE)
-                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                lx = acc ? nx : xi, ly = acc ? ny : yi, lz = acc ? nz : zi;
+                self = right;
+                right = ahead;
+                ahead = rec[i + 3 < N ? i + 3 : N - 1];
             }
             // one double bridging: bonds (bi, bi+1), (bj, bj+1) -> (bi, bj), (bi+1, bj+1)
             const Words4 w = philox4x32_10(chain, g, 0u, kTagBridge, a.k0, a.k1);
@@ -535,79 +629,77 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
                 bj = tmp;
             }
             if (N >= 4 && bj - bi >= 2) {
-                float ix, iy, iz, kx, ky, kz, jx, jy, jz, mx, my, mz; // beads bi, bi+1, bj, bj+1
-                bead(bi, ix, iy, iz);
-                bead(bi + 1, kx, ky, kz);
-                bead(bj, jx, jy, jz);
-                bead(bj + 1, mx, my, mz);
+                double ix, iy, iz, kx, ky, kz, jx, jy, jz, mx, my, mz; // beads bi, bi+1, bj, bj+1
+                readlane_bead(bi, ix, iy, iz);
+                readlane_bead(bi + 1, kx, ky, kz);
+                readlane_bead(bj, jx, jy, jz);
+                readlane_bead(bj + 1, mx, my, mz);
                 bool br = false;
-                const double fij = fene_energy(p, dist2(ix, iy, iz, jx, jy, jz), &br);
-                const double fkl = fene_energy(p, dist2(kx, ky, kz, mx, my, mz), &br);
+                const double fij = fene_energy(p, dist2d(ix, iy, iz, jx, jy, jz), &br);
+                const double fkl = fene_energy(p, dist2d(kx, ky, kz, mx, my, mz), &br);
                 if (!br) {
                     const double fik = bond_of(bi), fjl = bond_of(bj);
-                    const double lij = lj_energy(p, dist2(ix, iy, iz, jx, jy, jz));
-                    const double lkl = lj_energy(p, dist2(kx, ky, kz, mx, my, mz));
-                    const double lik = lj_energy(p, dist2(ix, iy, iz, kx, ky, kz));
-                    const double ljl = lj_energy(p, dist2(jx, jy, jz, mx, my, mz));
+                    const double lij = lj_energy(p, dist2d(ix, iy, iz, jx, jy, jz));
+                    const double lkl = lj_energy(p, dist2d(kx, ky, kz, mx, my, mz));
+                    const double lik = lj_energy(p, dist2d(ix, iy, iz, kx, ky, kz));
+                    const double ljl = lj_energy(p, dist2d(jx, jy, jz, mx, my, mz));
                     const double dF = ((fij + fkl) - fik) - fjl;
                     const double dL = ((lik + ljl) - lij) - lkl;
-                    const double En = E + (dF + dL);
+                    const double En = readlane_f64(E, 0) + (dF + dL);
                     const int32_t bn = energy_bin(p, En, a.n_bins);
                     if (bn >= 0 && min(w.w[3], 0xFFFFFFFEu) < a.thresholds[(size_t)b * B + (uint32_t)bn]) {
                         // beads bi+1 .. bj in reverse order; the bonds between them reversed
-                        float4 nxs[NS];
-                        double nub[NS];
+                        double nx[NS], ny[NS], nz[NS], nub[NS];
 #pragma unroll
                         for (int s = 0; s < NS; ++s) {
                             const int bd = j + 64 * s;
                             const int sx = (bd > bi && bd <= bj) ? bi + 1 + bj - bd : bd;
                             const int su = (bd > bi && bd < bj) ? bi + bj - bd : bd;
-                            float4 v0, v1 = make_float4(0.f, 0.f, 0.f, 0.f);
-                            v0.x = from_lane(x[0].x, sx & 63), v0.y = from_lane(x[0].y, sx & 63);
-                            v0.z = from_lane(x[0].z, sx & 63), v0.w = 0.f;
-                            double u0 = from_lane_f64(ub[0], su & 63), u1 = 0.0;
+                            // (a position is a float, exactly)
+                            float vx = from_lane((float)xd[0], sx & 63), vy = from_lane((float)yd[0], sx & 63),
+                                  vz = from_lane((float)zd[0], sx & 63);
+                            double u = from_lane_f64(ub[0], su & 63);
                             if constexpr (TWO) {
-                                v1.x = from_lane(x[NS - 1].x, sx & 63), v1.y = from_lane(x[NS - 1].y, sx & 63);
-                                v1.z = from_lane(x[NS - 1].z, sx & 63);
-                                u1 = from_lane_f64(ub[NS - 1], su & 63);
+                                const float hx = from_lane((float)xd[NS - 1], sx & 63),
+                                            hy = from_lane((float)yd[NS - 1], sx & 63),
+                                            hz = from_lane((float)zd[NS - 1], sx & 63);
+                                const double hu = from_lane_f64(ub[NS - 1], su & 63);
+                                vx = sx >= 64 ? hx : vx, vy = sx >= 64 ? hy : vy, vz = sx >= 64 ? hz : vz;
+                                u = su >= 64 ? hu : u;
                             }
-                            nxs[s] = sx >= 64 ? v1 : v0;
-                            nub[s] = su >= 64 ? u1 : u0;
-                            if (bd == bi)
-                                nub[s] = fij;
-                            if (bd == bj)
-                                nub[s] = fkl;
+                            nx[s] = vx, ny[s] = vy, nz[s] = vz;
+                            nub[s] = bd == bi ? fij : (bd == bj ? fkl : u);
                         }
 #pragma unroll
                         for (int s = 0; s < NS; ++s) {
-                            x[s] = nxs[s];
-                            set_xd(s);
+                            xd[s] = nx[s], yd[s] = ny[s], zd[s] = nz[s];
                             ub[s] = nub[s];
                         }
                         if constexpr (CACHE)
                             fill_cache(); // the pair terms under the new numbering
                         E = En;
-                        b = bn;
+                        b = __builtin_amdgcn_readfirstlane(bn);
+                        row_at = 4u * B * (uint32_t)b;
                         nacc += a.record ? 1u : 0u;
                     }
                 }
             }
         }
-        if (counts)
+        if (a.record && c < a.n_chains && j == 0)
             atomicAdd(&lhist[b], 1u);
     }
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
         const int bd = j + 64 * s;
         if (bd < N)
-            pos[bd] = x[s];
+            pos[bd] = make_float4((float)xd[s], (float)yd[s], (float)zd[s], 0.f);
         if (bd < N - 1)
             bond[bd] = ub[s];
     }
     if (j == 0) {
         a.energy[c] = E;
         a.bins[c] = b;
-        if (counts && a.accepts && nacc)
+        if (a.record && c < a.n_chains && a.accepts && nacc)
             atomicAdd(a.accepts, (unsigned long long)nacc);
     }
     __syncthreads();
@@ -684,10 +776,38 @@ hipError_t launch_patch_table(uint32_t *T, const uint32_t *pairs, int n, hipStre
     return hipGetLastError();
 }
 
-// The cache is used when four blocks of it still fit one CU's 160 KB of
-// LDS: the occupancy the kernel without it reaches at one chain per wave
-// and four waves per SIMD.
-static bool polymer_pair_cache_fits(size_t lds_bytes) { return lds_bytes * 4u <= 160u * 1024u; }
+// The cache is used when its LDS does not cost wavefronts: a CU still holds
+// four per SIMD with it, or every workgroup of a small grid has its place at
+// once.  Measured, moves/s with the cache and without (shifts | full set):
+//   N = 64, 2048 chains (512 workgroups, two per CU)  3.69e9 | 1.91e9  ->  cache
+//   N = 64, 2052 chains          2.30e9 | 1.24e9      2.63e9 | 1.31e9
+//   N = 64, 4096 chains          3.69e9 | 2.01e9      4.02e9 | 2.00e9
+//   N = 80, 1024 chains (one per CU)                  1.70e9 | 1.08e9  ->  cache
+//   N = 80, 2048 chains          1.68e9 | 1.08e9      2.23e9 | 1.39e9
+static bool polymer_cache_fits(size_t lds, int chains_per_block, long blocks, int cus)
+{
+    const long room = (long)(160u * 1024u / lds);
+    return room * chains_per_block >= 16 || (room >= 1 && room * cus >= blocks);
+}
+
+template <bool TWO, bool MOVES>
+static hipError_t launch_polymer(const PolymerArgs &a, const PolyParams &p, int cus, hipStream_t s)
+{
+    const int n_c = a.chains_per_block;
+    const dim3 grid((unsigned)(a.c_pad / n_c)), block((unsigned)(64 * n_c));
+    const size_t cached = hist_bytes(a.n_bins) + (size_t)n_c * chain_lds(a.n_beads, true);
+    const size_t plain = hist_bytes(a.n_bins) + (size_t)n_c * chain_lds(a.n_beads, false);
+    const bool cache = polymer_cache_fits(cached, n_c, (long)grid.x, cus);
+    const size_t lds = cache ? cached : plain;
+    auto k = cache ? polymer_sweeps<TWO, MOVES, true> : polymer_sweeps<TWO, MOVES, false>;
+    if (lds > 65536u) {
+        hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess)
+            return e;
+    }
+    hipLaunchKernelGGL(k, grid, block, lds, s, a, p);
+    return hipGetLastError();
+}
 
 hipError_t launch_polymer_sweeps(const PolymerArgs &a, const PolymerConsts &k, hipStream_t s)
 {
@@ -702,28 +822,14 @@ hipError_t launch_polymer_sweeps(const PolymerArgs &a, const PolymerConsts &k, h
     p.x_lo = k.x_lo;
     p.x_hi = k.x_hi;
     p.scale = k.scale;
-    const int chains_per_block = a.chains_per_block;
-    if (chains_per_block < 1 || chains_per_block > 4 || a.c_pad % chains_per_block)
+    if (a.chains_per_block < 1 || a.chains_per_block > 4 || a.c_pad % a.chains_per_block)
         return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(a.c_pad / chains_per_block)), block((unsigned)(64 * chains_per_block));
-    const size_t lds = (size_t)a.n_bins * 4u;
-    const size_t lds_cached = (size_t)((a.n_bins + 1) & ~1) * 4u + (size_t)chains_per_block * pair_slots(a.n_beads) * 8u;
-    if (a.n_beads > 64) {
-        if (a.moves)
-            hipLaunchKernelGGL((polymer_sweeps<true, true, false>), grid, block, lds, s, a, p);
-        else
-            hipLaunchKernelGGL((polymer_sweeps<true, false, false>), grid, block, lds, s, a, p);
-    } else if (a.moves) {
-        if (polymer_pair_cache_fits(lds_cached))
-            hipLaunchKernelGGL((polymer_sweeps<false, true, true>), grid, block, lds_cached, s, a, p);
-        else
-            hipLaunchKernelGGL((polymer_sweeps<false, true, false>), grid, block, lds, s, a, p);
-    } else if (polymer_pair_cache_fits(lds_cached)) {
-        hipLaunchKernelGGL((polymer_sweeps<false, false, true>), grid, block, lds_cached, s, a, p);
-    } else {
-        hipLaunchKernelGGL((polymer_sweeps<false, false, false>), grid, block, lds, s, a, p);
-    }
-    return hipGetLastError();
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess)
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (a.n_beads > 64)
+        return a.moves ? launch_polymer<true, true>(a, p, cus, s) : launch_polymer<true, false>(a, p, cus, s);
+    return a.moves ? launch_polymer<false, true>(a, p, cus, s) : launch_polymer<false, false>(a, p, cus, s);
 }
 
 } // namespace muca
