@@ -222,19 +222,32 @@ typedef __attribute__((address_space(3))) const double lds_f64;
 typedef __attribute__((address_space(3))) double lds_f64_out;
 
 // A bead as every lane reads it (one LDS broadcast instead of a lane read per
-// word): while shifts run, its proposal and, without the cache, where it is;
-// while rotations run, where it is.
+// word): its proposal while shifts run and, without the cache, where it is.
 struct alignas(16) BeadRecord {
     double x, y, z;
     uint32_t w, pad; // acceptance word
 };
 
+// A planned rotation: where it puts the bead, its acceptance word (all ones:
+// a bond breaks, nothing to try) and the energies of the bead's two new bonds
+// (to the bead before it, to the one after).
+struct alignas(16) RotateRecord {
+    float x, y, z;
+    uint32_t w;
+    double f[2];
+};
+
+// Rotations are planned for kPlanBeads beads and up to kPlanRuns - 1 accepted
+// ones before each of them (see the kernel).
+constexpr int kPlanBeads = 16, kPlanRuns = 4;
+
 __host__ __device__ inline size_t hist_bytes(int n_bins) { return (size_t)((n_bins + 3) & ~3) * 4u; }
-// LDS of one chain: [pair terms | records].
+// LDS of one chain: [pair terms, or where its beads are | records or plan].
 __host__ __device__ inline size_t chain_cache_bytes(int N) { return (size_t)((pair_slots(N) + 1) & ~1) * 8u; }
-__host__ __device__ inline size_t chain_lds(int N, bool cache)
+__host__ __device__ inline size_t chain_lds(int N, bool cache, bool moves)
 {
-    return (cache ? chain_cache_bytes(N) : (size_t)N * sizeof(BeadRecord)) + (size_t)N * sizeof(BeadRecord);
+    const size_t beads = (size_t)N * sizeof(BeadRecord), plan = kPlanBeads * kPlanRuns * sizeof(RotateRecord);
+    return (cache ? chain_cache_bytes(N) : beads) + (moves && beads < plan ? plan : beads);
 }
 
 __device__ __forceinline__ bool lane_bit(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
@@ -249,10 +262,10 @@ __device__ __forceinline__ bool lane_bit(uint64_t mask) { return __builtin_amdgc
 // lanes of a move are scalar masks shifted along the chain, and the cache is
 // addressed by two precomputed offsets per lane.  Moves/s, against lane reads
 // per word, masks from comparisons and the cache for up to 64 beads only:
-//   N = 40, 4096 chains, shifts    3.1e9 -> 4.4e9    full set  1.5e9 -> 2.1e9
+//   N = 40, 4096 chains, shifts    3.1e9 -> 4.4e9    full set  1.5e9 -> 2.5e9
 //   N = 40,  512 chains, shifts    9.3e8 -> 1.1e9
-//   N = 80, 4096 chains, shifts    1.9e9 -> 2.6e9    full set  1.15e9 -> 1.55e9
-//   N = 80,  512 chains                              full set  4.3e8 -> 5.4e8
+//   N = 80, 4096 chains, shifts    1.9e9 -> 2.6e9    full set  1.15e9 -> 1.8e9
+//   N = 80,  512 chains                              full set  4.3e8 -> 6.3e8
 //
 // One chain per wavefront.  Lane j holds bead j and, with TWO (64 < N <= 128),
 // bead j + 64 (register set 1).  A pair sum slot is lane j's term plus, with
@@ -296,7 +309,7 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
     const int up_l = (j + 1) & 63, dn_l = (j + 63) & 63;
     uint64_t nacc = 0u; // accepted moves of the recorded sweeps (wave-uniform)
 
-    uint8_t *mine = (uint8_t *)lhist + hist_bytes(a.n_bins) + (size_t)wave * chain_lds(N, CACHE);
+    uint8_t *mine = (uint8_t *)lhist + hist_bytes(a.n_bins) + (size_t)wave * chain_lds(N, CACHE, MOVES);
     double *cache = (double *)mine; // CACHE
     BeadRecord *was = (BeadRecord *)mine, *rec = (BeadRecord *)(mine + (CACHE ? chain_cache_bytes(N) : (size_t)N * sizeof(BeadRecord)));
     // lanes of one wave exchange data through LDS, whose accesses from one
@@ -310,10 +323,6 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
         pz = readlane_f64(h ? zd[NS - 1] : zd[0], k & 63);
     };
     auto bond_of = [&](int k) { return readlane_f64((TWO && k >= 64) ? ub[NS - 1] : ub[0], k & 63); };
-    auto lane_of = [](int s, int bead) -> uint64_t { // the lane that holds `bead` in set s
-        const int l = bead - 64 * s;
-        return (l >= 0 && l < 64) ? 1ull << l : 0ull;
-    };
     // every pair term at the current positions
     auto fill_cache = [&]() {
         for (int k = 0; k + 2 < N; ++k) {
@@ -542,82 +551,138 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
             ub[s] = lane_bit(after) ? both : own;
         }
         if constexpr (MOVES) {
-            // spherical rotations, beads 0..N-1 in order.  The random numbers
-            // of all beads at once; positions by LDS broadcast, one bead
-            // ahead (a rotation of bead i reads i - 1, i and i + 1, and only
-            // i - 1 can have moved since the phase began).
-            double tau[NS];
-            uint32_t axis[NS];
+            // Spherical rotations, beads 0..N-1 in order.  A proposal needs
+            // the bead, the next one (which has not moved yet) and the one
+            // before it, which is where the phase found it if its own
+            // rotation was rejected, and else where that put it.  So the
+            // proposals and bond energies of the next 16 beads are planned
+            // at once, two lanes per bead (one bond each): plan[0] for the
+            // case that the bead before was rejected, plan[k] for exactly k
+            // accepted before, whose proposals are those of plan[k - 1].  A
+            // plan ends with its beads or with the first four accepted in a
+            // row; the next one starts from the positions then.  Three of
+            // four rotations are accepted in earnest: a plan serves about
+            // eight moves, and its FP64 chain of divisions, square root and
+            // logarithm, which each move had to itself, is paid once (N = 80,
+            // 512 chains: 5.4e8 -> 6.3e8 moves/s).  Six or eight runs serve
+            // little more and cost LDS (N = 40, 4096 chains, four, six and
+            // eight: 2.48e9, 2.19e9, 2.19e9; N = 80, 512 chains: 6.31e8,
+            // 6.51e8, 6.26e8).
+            if constexpr (!CACHE) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const Words4 w = philox4x32_10(chain, g, (uint32_t)(j + 64 * s), kTagRotate, a.k0, a.k1);
-                tau[s] = rot_tau(w.w[0]);
-                axis[s] = (uint32_t)(((uint64_t)w.w[1] * 3u) >> 32);
-                if (j + 64 * s < N) {
-                    rec[j + 64 * s] = BeadRecord{xd[s], yd[s], zd[s], min(w.w[3], 0xFFFFFFFEu), 0u};
-                    if constexpr (!CACHE)
+                for (int s = 0; s < NS; ++s)
+                    if (j + 64 * s < N)
                         was[j + 64 * s] = BeadRecord{xd[s], yd[s], zd[s], 0u, 0u};
-                }
             }
-            lds_fence();
-            double lx = 0.0, ly = 0.0, lz = 0.0;
-            BeadRecord self = rec[0], right = rec[1], ahead = rec[N > 2 ? 2 : 1];
-            for (int i = 0; i < N; ++i) {
-                const double xi = self.x, yi = self.y, zi = self.z, rx = right.x, ry = right.y, rz = right.z;
-                const uint32_t w3 = self.w;
-                const double tau_i = readlane_f64((TWO && i >= 64) ? tau[NS - 1] : tau[0], i & 63);
-                double ax, ay, az, cx, cy, cz;
-                if (i > 0 && i < N - 1) { // about the line through both neighbours
-                    ax = rx - lx;
-                    ay = ry - ly;
-                    az = rz - lz;
-                    cx = lx, cy = ly, cz = lz;
-                } else { // an end bead: about a coordinate axis through its neighbour
-                    const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)((TWO && i >= 64) ? axis[NS - 1] : axis[0]), i & 63);
-                    ax = k == 0u ? 1.0 : 0.0;
-                    ay = k == 1u ? 1.0 : 0.0;
-                    az = k == 2u ? 1.0 : 0.0;
-                    cx = i == 0 ? rx : lx, cy = i == 0 ? ry : ly, cz = i == 0 ? rz : lz;
-                }
-                double ox, oy, oz;
-                quat_rotate(tau_i, ax, ay, az, xi - cx, yi - cy, zi - cz, ox, oy, oz);
-                const double nx = (float)(cx + ox), ny = (float)(cy + oy), nz = (float)(cz + oz);
-                // both new bonds at once: the right one in odd lanes, the left
-                // one in even lanes
-                const bool odd = lane_bit(0xAAAAAAAAAAAAAAAAull);
-                bool broken = false;
-                const double f = fene_energy(
-                    p, dist2d(odd ? rx : lx, odd ? ry : ly, odd ? rz : lz, nx, ny, nz), &broken);
-                const uint64_t br = __builtin_amdgcn_ballot_w64(broken);
-                bool acc = false;
-                if (!((i >= 1 && (br & 1ull)) || (i + 1 < N && (br & 2ull)))) {
-                    const double fl = i >= 1 ? readlane_f64(f, 0) : 0.0, fr = i + 1 < N ? readlane_f64(f, 1) : 0.0;
-                    const double up = fr - bond_of(i);
-                    double rdup[NS], rddn[NS];
-#pragma unroll
-                    for (int s = 0; s < NS; ++s) {
-                        rdup[s] = up;
-                        rddn[s] = fl - ub[s];
+            RotateRecord *plan = (RotateRecord *)rec;
+            const int slot = (j >> 1) & (kPlanBeads - 1);
+            const bool right = lane_bit(0xAAAAAAAAAAAAAAAAull); // odd lanes: the bond to the bead after
+            me[0] = 1ull;
+            if constexpr (TWO)
+                me[NS - 1] = 0ull;
+            for (int i = 0; i < N;) {
+                const int bd = i + slot;
+                auto at = [&](int k, double &x, double &y, double &z) {
+                    float fx = from_lane((float)xd[0], k & 63), fy = from_lane((float)yd[0], k & 63),
+                          fz = from_lane((float)zd[0], k & 63);
+                    if constexpr (TWO) {
+                        const float hx = from_lane((float)xd[NS - 1], k & 63), hy = from_lane((float)yd[NS - 1], k & 63),
+                                    hz = from_lane((float)zd[NS - 1], k & 63);
+                        fx = k >= 64 ? hx : fx, fy = k >= 64 ? hy : fy, fz = k >= 64 ? hz : fz;
                     }
-                    const uint64_t me[2] = {lane_of(0, i), lane_of(1, i)};
-                    uint64_t own[NS];
+                    x = fx, y = fy, z = fz;
+                };
+                double xi, yi, zi, lx, ly, lz, rx, ry, rz;
+                at(bd, xi, yi, zi);
+                at(bd - 1, lx, ly, lz);
+                at(bd + 1, rx, ry, rz);
+                const Words4 w = philox4x32_10(chain, g, (uint32_t)bd, kTagRotate, a.k0, a.k1);
+                const double tau = rot_tau(w.w[0]);
+                const uint32_t axis = (uint32_t)(((uint64_t)w.w[1] * 3u) >> 32);
+                const bool first = bd == 0, inner = bd > 0 && bd < N - 1;
+                const bool upper = lane_bit(0xFFFFFFFF00000000ull);
+                const int dn2 = (j + 62) & 63; // a lane of the bead before
+                const bool bonded = right ? bd + 1 < N : bd > 0;
+                // the proposals, run by run, in every lane pair of the bead;
+                // of two runs the lower half of the wave keeps the first, the
+                // upper half the second
+                float px[kPlanRuns / 2], py[kPlanRuns / 2], pz[kPlanRuns / 2];
+                double fx[kPlanRuns / 2], fy[kPlanRuns / 2], fz[kPlanRuns / 2]; // the bonded neighbour
 #pragma unroll
-                    for (int s = 0; s < NS; ++s)
-                        own[s] = me[s];
-                    acc = attempt(i, own, nx, ny, nz, rdup, rddn, w3);
-                    if (acc) {
-                        nacc += a.record ? 1u : 0u;
+                for (int k = 0; k < kPlanRuns; ++k) {
+                    // an inner bead: about the line through both neighbours;
+                    // an end bead: about a coordinate axis through its neighbour
+                    const double ax = inner ? rx - lx : (axis == 0u ? 1.0 : 0.0);
+                    const double ay = inner ? ry - ly : (axis == 1u ? 1.0 : 0.0);
+                    const double az = inner ? rz - lz : (axis == 2u ? 1.0 : 0.0);
+                    const double cx = first ? rx : lx, cy = first ? ry : ly, cz = first ? rz : lz;
+                    double ox, oy, oz;
+                    quat_rotate(tau, ax, ay, az, xi - cx, yi - cy, zi - cz, ox, oy, oz);
+                    const float nx = (float)(cx + ox), ny = (float)(cy + oy), nz = (float)(cz + oz);
+                    const bool keep = (k & 1) == 0 || upper;
+                    const int m = k / 2;
+                    px[m] = keep ? nx : px[m], py[m] = keep ? ny : py[m], pz[m] = keep ? nz : pz[m];
+                    fx[m] = keep ? (right ? rx : lx) : fx[m];
+                    fy[m] = keep ? (right ? ry : ly) : fy[m];
+                    fz[m] = keep ? (right ? rz : lz) : fz[m];
+                    if (k + 1 < kPlanRuns)
+                        lx = from_lane(nx, dn2), ly = from_lane(ny, dn2), lz = from_lane(nz, dn2);
+                }
+                // the bonds of all runs together
+                lds_fence();
+#pragma unroll
+                for (int m = 0; m < kPlanRuns / 2; ++m) {
+                    bool broken = false;
+                    const double f = fene_energy(p, dist2d(fx[m], fy[m], fz[m], px[m], py[m], pz[m]), &broken);
+                    const int out = broken && bonded ? 1 : 0;
+                    const int other = __builtin_amdgcn_update_dpp(0, out, 0xB1, 0xF, 0xF, true); // quad_perm 1 0 3 2
+                    RotateRecord *r = plan + (2 * m + (upper ? 1 : 0)) * kPlanBeads + slot;
+                    if (!right)
+                        r->x = px[m], r->y = py[m], r->z = pz[m], r->w = (out | other) ? 0xFFFFFFFFu : min(w.w[3], 0xFFFFFFFEu);
+                    r->f[right ? 1 : 0] = f;
+                }
+                lds_fence();
+                const int end = min(i + kPlanBeads, N);
+                int run = 0;
+                RotateRecord next = plan[0];
+                for (int t = 0; i < end && run < kPlanRuns; ++i, ++t) {
+                    const RotateRecord r = next;
+                    // both continuations, their latency beside this move's arithmetic
+                    const int t1 = min(t + 1, kPlanBeads - 1), run1 = min(run + 1, kPlanRuns - 1);
+                    const RotateRecord if_rej = plan[t1], if_acc = plan[run1 * kPlanBeads + t1];
+                    bool acc = false;
+                    if (__builtin_amdgcn_readfirstlane((int)r.w) != -1) {
+                        const double up = i + 1 < N ? r.f[1] - bond_of(i) : 0.0;
+                        double rdup[NS], rddn[NS];
 #pragma unroll
                         for (int s = 0; s < NS; ++s) {
-                            ub[s] = lane_bit(lane_of(s, i + 1 < N ? i : -1)) ? fr : ub[s];
-                            ub[s] = lane_bit(lane_of(s, i - 1)) ? fl : ub[s];
+                            rdup[s] = up;
+                            rddn[s] = r.f[0] - ub[s];
+                        }
+                        acc = attempt(i, me, r.x, r.y, r.z, rdup, rddn, r.w);
+                        if (acc) {
+                            nacc += a.record ? 1u : 0u;
+                            uint64_t dn[NS];
+                            dn[0] = me[0] >> 1;
+                            if constexpr (TWO) {
+                                dn[0] |= me[NS - 1] << 63;
+                                dn[NS - 1] = me[NS - 1] >> 1;
+                            }
+#pragma unroll
+                            for (int s = 0; s < NS; ++s) {
+                                ub[s] = lane_bit(i + 1 < N ? me[s] : 0ull) ? r.f[1] : ub[s];
+                                ub[s] = lane_bit(dn[s]) ? r.f[0] : ub[s];
+                            }
                         }
                     }
+                    next.x = acc ? if_acc.x : if_rej.x, next.y = acc ? if_acc.y : if_rej.y;
+                    next.z = acc ? if_acc.z : if_rej.z, next.w = acc ? if_acc.w : if_rej.w;
+                    next.f[0] = acc ? if_acc.f[0] : if_rej.f[0], next.f[1] = acc ? if_acc.f[1] : if_rej.f[1];
+                    run = acc ? run + 1 : 0;
+                    if constexpr (TWO)
+                        me[NS - 1] = (me[NS - 1] << 1) | (me[0] >> 63);
+                    me[0] <<= 1;
                 }
-                lx = acc ? nx : xi, ly = acc ? ny : yi, lz = acc ? nz : zi;
-                self = right;
-                right = ahead;
-                ahead = rec[i + 3 < N ? i + 3 : N - 1];
             }
             // one double bridging: bonds (bi, bi+1), (bj, bj+1) -> (bi, bj), (bi+1, bj+1)
             const Words4 w = philox4x32_10(chain, g, 0u, kTagBridge, a.k0, a.k1);
@@ -777,17 +842,20 @@ hipError_t launch_patch_table(uint32_t *T, const uint32_t *pairs, int n, hipStre
 }
 
 // The cache is used when its LDS does not cost wavefronts: a CU still holds
-// four per SIMD with it, or every workgroup of a small grid has its place at
-// once.  Measured, moves/s with the cache and without (shifts | full set):
-//   N = 64, 2048 chains (512 workgroups, two per CU)  3.69e9 | 1.91e9  ->  cache
-//   N = 64, 2052 chains          2.30e9 | 1.24e9      2.63e9 | 1.31e9
-//   N = 64, 4096 chains          3.69e9 | 2.01e9      4.02e9 | 2.00e9
-//   N = 80, 1024 chains (one per CU)                  1.70e9 | 1.08e9  ->  cache
-//   N = 80, 2048 chains          1.68e9 | 1.08e9      2.23e9 | 1.39e9
+// three per SIMD with it (the registers of the full move set allow no more),
+// or every workgroup of a small grid has its place at once.  Measured, moves/s
+// with the cache and without (shifts | full set):
+//   N = 50, 4096 chains (three workgroups per CU)   4.03e9 | 2.67e9   4.03e9 | 2.48e9   cache
+//   N = 54, 4096 chains (two per CU)                3.70e9 | 2.47e9   4.04e9 | 2.46e9
+//   N = 64, 2048 chains (two per CU, all at once)   3.69e9 | 2.39e9                     cache
+//   N = 64, 2052 chains                             2.33e9 | 1.55e9   2.65e9 | 1.71e9
+//   N = 64, 4096 chains                             3.74e9 | 2.49e9   4.11e9 | 2.51e9
+//   N = 80, 1024 chains (one per CU, all at once)   1.70e9 | 1.24e9                     cache
+//   N = 80, 2048 chains                             1.68e9 | 1.24e9   2.23e9 | 1.60e9
 static bool polymer_cache_fits(size_t lds, int chains_per_block, long blocks, int cus)
 {
     const long room = (long)(160u * 1024u / lds);
-    return room * chains_per_block >= 16 || (room >= 1 && room * cus >= blocks);
+    return room * chains_per_block >= 12 || (room >= 1 && room * cus >= blocks);
 }
 
 template <bool TWO, bool MOVES>
@@ -795,8 +863,8 @@ static hipError_t launch_polymer(const PolymerArgs &a, const PolyParams &p, int 
 {
     const int n_c = a.chains_per_block;
     const dim3 grid((unsigned)(a.c_pad / n_c)), block((unsigned)(64 * n_c));
-    const size_t cached = hist_bytes(a.n_bins) + (size_t)n_c * chain_lds(a.n_beads, true);
-    const size_t plain = hist_bytes(a.n_bins) + (size_t)n_c * chain_lds(a.n_beads, false);
+    const size_t cached = hist_bytes(a.n_bins) + (size_t)n_c * chain_lds(a.n_beads, true, MOVES);
+    const size_t plain = hist_bytes(a.n_bins) + (size_t)n_c * chain_lds(a.n_beads, false, MOVES);
     const bool cache = polymer_cache_fits(cached, n_c, (long)grid.x, cus);
     const size_t lds = cache ? cached : plain;
     auto k = cache ? polymer_sweeps<TWO, MOVES, true> : polymer_sweeps<TWO, MOVES, false>;
