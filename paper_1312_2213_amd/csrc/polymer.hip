@@ -12,12 +12,15 @@
 // also bead j + 64).  At the start of a sweep lane j computes bead j's
 // proposal and the FENE energies of its new bonds (the backward one for both
 // outcomes of the previous bead's move), and from them what each neighbour's
-// move will change in its own bond.  For a move of bead i every lane computes
-// its pair term new - old in FP64 (the two bonded partners take the
-// precomputed changes); the terms are summed by a fixed binary tree (lane k
-// += lane k + s for s = 32, 16, ..., 1) built from lane permutes and DPP
-// moves, so the sum is the same number on every run.  The acceptance
-// threshold T[b][b'] of the bin change is one load from the B x B matrix.
+// move will change in its own bond.  Moves are then taken two at a time: every
+// lane computes its pair terms new - old of both in FP64 (the bonded partners
+// take the precomputed changes), and the three sums that the outcomes can
+// ask for (the first move; the second after a rejection and after an
+// acceptance of the first) are taken together by a fixed binary tree (lane k
+// += lane k + s for s = 32, 16, ..., 1) built from lane swaps and DPP moves,
+// so that each sum is the same number on every run.  The acceptance
+// thresholds T[b][b'] of the three bin changes are one load from the B x B
+// matrix.
 //
 // With the paper's move set (moves = 1) each sweep continues with a
 // spherical rotation of every bead (an inner bead about the line through its
@@ -25,8 +28,8 @@
 // both by the quaternion (tau, axis) with tau symmetric about zero: only +,
 // -, *, / in FP64, so the proposal is bit-identical everywhere) and one
 // double bridging (two bonds swapped for two new ones, the beads between
-// renumbered in reverse by one lane permute); the energy change of a
-// rotation is the same lane-parallel tree sum as for a shift.
+// renumbered in reverse by one lane permute); rotations go in pairs like
+// shifts, the second planned for the likelier outcome of the first.
 #include <utility>
 
 #include "muca_internal.h"
@@ -44,13 +47,38 @@ struct PolyParams {
     double x_lo, x_hi, scale; // bins: floor((E - x_lo) * scale) on [x_lo, x_hi)
 };
 
+// 4 eps ((sigma^2/r2)^6 - (sigma^2/r2)^3) - shift inside the cutoff.  The
+// quotient is the correctly rounded one: Newton steps on the reciprocal, then
+// the quotient corrected by its exact remainder.  The compiler's division
+// scales its operands first, against exponents near the ends of the range; a
+// squared distance of two floats is 0 or between 2^-298 and 2^258, and where
+// sigma^2 takes the quotient itself to an end, the powers below are 0 or not
+// finite either way.
+//
+// Two at once, step by step: one's latency covers the other's.
+__device__ __forceinline__ void lj_energy2(const PolyParams &p, double ra, double rb, double &ua, double &ub)
+{
+    double ya = __builtin_amdgcn_rcp(ra), yb = __builtin_amdgcn_rcp(rb);
+    double ea = __builtin_fma(-ra, ya, 1.0), eb = __builtin_fma(-rb, yb, 1.0);
+    ya = __builtin_fma(ya, ea, ya), yb = __builtin_fma(yb, eb, yb);
+    ea = __builtin_fma(-ra, ya, 1.0), eb = __builtin_fma(-rb, yb, 1.0);
+    ya = __builtin_fma(ya, ea, ya), yb = __builtin_fma(yb, eb, yb);
+    const double qa = p.sig2 * ya, qb = p.sig2 * yb;
+    ea = __builtin_fma(-ra, qa, p.sig2), eb = __builtin_fma(-rb, qb, p.sig2);
+    const double sa = __builtin_fma(ea, ya, qa), sb = __builtin_fma(eb, yb, qb);
+    double ta = sa * sa, tb = sb * sb;
+    ta = ta * sa, tb = tb * sb;
+    ua = p.lj_eps4 * (ta * ta - ta) - p.lj_shift;
+    ub = p.lj_eps4 * (tb * tb - tb) - p.lj_shift;
+    ua = ra < p.rc2 ? ua : 0.0;
+    ub = rb < p.rc2 ? ub : 0.0;
+}
+
 __device__ __forceinline__ double lj_energy(const PolyParams &p, double r2)
 {
-    if (!(r2 < p.rc2))
-        return 0.0;
-    const double sr2 = p.sig2 / r2;
-    const double sr6 = sr2 * sr2 * sr2;
-    return p.lj_eps4 * (sr6 * sr6 - sr6) - p.lj_shift;
+    double u, v;
+    lj_energy2(p, r2, r2, u, v);
+    return u;
 }
 
 // FENE energy; sets *broken when the bond leaves (r0 - R, r0 + R)
@@ -82,6 +110,18 @@ __device__ __forceinline__ double dist2d(double ax, double ay, double az, double
     const double dy = ay - by;
     const double dz = az - bz;
     return dx * dx + dy * dy + dz * dz;
+}
+
+// (x, y, z) = (nx, ny, nz) in the lanes of m; every lane of the wave is active
+__device__ __forceinline__ void set_bead(uint64_t m, double &x, double &y, double &z, double nx, double ny, double nz)
+{
+    asm volatile("s_mov_b64 exec, %3\n\t"
+        "v_mov_b64 %0, %4\n\t"
+        "v_mov_b64 %1, %5\n\t"
+        "v_mov_b64 %2, %6\n\t"
+        "s_mov_b64 exec, -1"
+        : "+v"(x), "+v"(y), "+v"(z)
+        : "s"(m), "v"(nx), "v"(ny), "v"(nz));
 }
 
 __device__ __forceinline__ double readlane_f64(double v, int lane)
@@ -130,7 +170,8 @@ __device__ __forceinline__ double tree_level_swap(double t)
 {
     const uint64_t u = __double_as_longlong(t);
     uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
-    const uint32_t junk_lo = __builtin_nondeterministic_value(lo), junk_hi = __builtin_nondeterministic_value(hi);
+    uint32_t junk_lo, junk_hi;
+    asm("" : "=v"(junk_lo), "=v"(junk_hi));
     uint32_t plo, phi;
     if constexpr (S == 32) {
         const auto rl = __builtin_amdgcn_permlane32_swap(lo, junk_lo, false, false);
@@ -144,17 +185,45 @@ __device__ __forceinline__ double tree_level_swap(double t)
     return __longlong_as_double(((uint64_t)hi << 32) | lo) + __longlong_as_double(((uint64_t)phi << 32) | plo);
 }
 
-// The fixed summation tree over 64 slots: slot k += slot k + s for
-// s = 32, 16, ..., 1; the sum ends in lane 0.
-__device__ __forceinline__ double tree_sum(double t)
+// Exchange between two registers: rows 2-3 of a with rows 0-1 of b (S = 32),
+// or the odd rows of a with the even rows of b (S = 16); their sum after.
+template <int S>
+__device__ __forceinline__ double swap_sum(double a, double b)
 {
-    t = tree_level_swap<32>(t);
-    t = tree_level_swap<16>(t);
+    const uint64_t ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+    uint32_t al, ah, bl, bh;
+    if constexpr (S == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)ua, (uint32_t)ub, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+        al = l[0], bl = l[1], ah = h[0], bh = h[1];
+    } else {
+        const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)ua, (uint32_t)ub, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+        al = l[0], bl = l[1], ah = h[0], bh = h[1];
+    }
+    return __longlong_as_double(((uint64_t)ah << 32) | al) + __longlong_as_double(((uint64_t)bh << 32) | bl);
+}
+
+// The fixed summation tree over 64 slots (slot k += slot k + s for
+// s = 32, 16, ..., 1) of three values at once: level 32 of a and b fills the two
+// halves of one register, level 16 the four rows; the sums of a, b and c end
+// in lanes 0, 32 and 16.
+__device__ __forceinline__ double tree_sum3(double a, double b, double c)
+{
+    double t = swap_sum<16>(swap_sum<32>(a, b), tree_level_swap<32>(c));
     t = t + from_lane_above<8>(t);
     t = t + from_lane_above<4>(t);
     t = t + from_lane_above<2>(t);
     t = t + from_lane_above<1>(t);
     return t;
+}
+
+// v_cvt_i32_f64: truncates, saturates, and takes NaN to 0
+__device__ __forceinline__ int cvt_i32(double v)
+{
+    int r;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(v));
+    return r;
 }
 
 __device__ __forceinline__ int32_t energy_bin(const PolyParams &p, double E, int32_t nb)
@@ -243,7 +312,7 @@ constexpr int kPlanBeads = 16, kPlanRuns = 4;
 
 __host__ __device__ inline size_t hist_bytes(int n_bins) { return (size_t)((n_bins + 3) & ~3) * 4u; }
 // LDS of one chain: [pair terms, or where its beads are | records or plan].
-__host__ __device__ inline size_t chain_cache_bytes(int N) { return (size_t)((pair_slots(N) + 1) & ~1) * 8u; }
+__host__ __device__ inline size_t chain_cache_bytes(int N) { return (size_t)((pair_slots(N) + 2) & ~1) * 8u; }
 __host__ __device__ inline size_t chain_lds(int N, bool cache, bool moves)
 {
     const size_t beads = (size_t)N * sizeof(BeadRecord), plan = kPlanBeads * kPlanRuns * sizeof(RotateRecord);
@@ -252,20 +321,23 @@ __host__ __device__ inline size_t chain_lds(int N, bool cache, bool moves)
 
 __device__ __forceinline__ bool lane_bit(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
 
-// Bound by instruction issue: a move is one serial chain (squared distance,
-// pair term, six-level tree sum, bin, threshold) of about 150 instructions
-// whose dependent FP64 operations a single wavefront cannot overlap; with
-// four or more per SIMD the vector pipe itself is full.  What a sweep knows
-// beforehand is therefore taken out of the moves: proposals, words and bond
-// changes are computed for all beads at once (the first read back by LDS
-// broadcast, the others already in the lane that adds them to the sum), the
-// lanes of a move are scalar masks shifted along the chain, and the cache is
-// addressed by two precomputed offsets per lane.  Moves/s, against lane reads
-// per word, masks from comparisons and the cache for up to 64 beads only:
-//   N = 40, 4096 chains, shifts    3.1e9 -> 4.4e9    full set  1.5e9 -> 2.5e9
-//   N = 40,  512 chains, shifts    9.3e8 -> 1.1e9
-//   N = 80, 4096 chains, shifts    1.9e9 -> 2.6e9    full set  1.15e9 -> 1.8e9
-//   N = 80,  512 chains                              full set  4.3e8 -> 6.3e8
+// Bound by instruction issue and, with one wavefront per SIMD, by the latency
+// of one serial chain of FP64 operations: squared distance, quotient, pair
+// term, six-level tree sum, bin, threshold load, decision.  So what a sweep
+// knows beforehand is taken out of the moves (proposals and words are one LDS
+// broadcast, bond changes wait in the lanes that add them, lanes of a move
+// are scalar masks shifted along the chain, cache addresses are stepped), and
+// two moves share the chain: their pair terms overlap, and tree, bins,
+// thresholds and decisions are paid once.  About 75 vector instructions a
+// shift, where single moves took 96 and lane reads, masks from comparisons
+// and 64-bit addresses 142.  Moves/s, with those / single moves / pairs:
+//   N = 40, 4096 chains, shifts    3.1e9 / 4.4e9 / 4.6e9    full set  1.5e9 / 2.5e9 / 2.6e9
+//   N = 40,  512 chains, shifts    9.3e8 / 1.1e9 / 1.4e9
+//   N = 80, 4096 chains, shifts    1.9e9 / 2.7e9 / 2.6e9    full set  1.15e9 / 1.8e9 / 1.9e9
+//   N = 80,  512 chains                                     full set  4.3e8 / 6.3e8 / 6.8e8
+//   N = 100, 512 chains, shifts    6.6e8 / 7.9e8 / 9.4e8
+// (N = 80, 4096 chains, without the cache: 143 registers leave three
+// wavefronts per SIMD, 121 left four; held to 128 it spills and gains nothing.)
 //
 // One chain per wavefront.  Lane j holds bead j and, with TWO (64 < N <= 128),
 // bead j + 64 (register set 1).  A pair sum slot is lane j's term plus, with
@@ -302,7 +374,7 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
         const int n = N - 64 * s;
         valid[s] = n >= 64 ? ~0ull : (1ull << n) - 1ull;
     }
-    double E = a.energy[c]; // from the first accepted move on valid in lane 0 only
+    double E = readlane_f64(a.energy[c], 0);
     int32_t b = __builtin_amdgcn_readfirstlane(a.bins[c]);
     const uint32_t chain = (uint32_t)(a.chain0 + c);
     const uint32_t B = (uint32_t)a.n_bins;
@@ -310,7 +382,7 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
     uint64_t nacc = 0u; // accepted moves of the recorded sweeps (wave-uniform)
 
     uint8_t *mine = (uint8_t *)lhist + hist_bytes(a.n_bins) + (size_t)wave * chain_lds(N, CACHE, MOVES);
-    double *cache = (double *)mine; // CACHE
+    double *cache = (double *)mine + 1; // CACHE (pair_row(0) + 0 is slot -1: read, never used)
     BeadRecord *was = (BeadRecord *)mine, *rec = (BeadRecord *)(mine + (CACHE ? chain_cache_bytes(N) : (size_t)N * sizeof(BeadRecord)));
     // lanes of one wave exchange data through LDS, whose accesses from one
     // wave complete in order: the fence only keeps the compiler from moving
@@ -340,89 +412,142 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
     if constexpr (CACHE)
         fill_cache();
 
-    // byte addresses of this lane's pair terms with bead i: lo + 8 i for the
-    // beads before it, hi + 8 pair_row(i) for those behind it
-    const uint32_t cache_at = (uint32_t)(uintptr_t)(lds_f64 *)cache;
-    uint32_t lo[NS], hi[NS];
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int bd = j + 64 * s;
-        lo[s] = cache_at + 8u * (uint32_t)pair_row(bd, N);
-        hi[s] = cache_at + 8u * (uint32_t)bd;
-    }
     uint32_t row_at = 4u * B * (uint32_t)b; // byte offset of the present bin's thresholds (below 2^28)
 
-    // A move of bead i to (nx, ny, nz); me: the bead's lane.  The pair terms'
-    // changes are summed over the lanes, with dup in the lane of bead i + 1
-    // and ddn in that of i - 1 (the changes of its two bonds); then the bin
-    // and the acceptance by word w.  An accepted move changes the position,
-    // the cached terms, E and b.
-    auto attempt = [&](int i, const uint64_t (&me)[NS], double nx, double ny, double nz, const double (&dup)[NS],
-                       const double (&ddn)[NS], uint32_t w) -> bool {
-        uint64_t up[NS], dn[NS], pairs[NS];
-        up[0] = me[0] << 1;
-        dn[0] = me[0] >> 1;
+    // Where a pass over the beads is: bead i, its lane, the lanes of the beads
+    // up to it, and the LDS address of each lane's pair term with it (row i
+    // of the triangle in lanes behind it, the lane's own row before).
+    struct Place {
+        int i;
+        uint64_t me[NS], upto[NS];
+        uint32_t at[NS];
+    };
+    auto start = [&]() {
+        Place q;
+        q.i = 0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            q.me[s] = q.upto[s] = s == 0 ? 1ull : 0ull;
+            // lanes without a bead follow the last one
+            q.at[s] = (uint32_t)(uintptr_t)(lds_f64 *)cache + 8u * (uint32_t)(min(j + 64 * s, N - 1) - 1);
+        }
+        return q;
+    };
+    auto next_lane = [](const uint64_t (&m)[NS], uint64_t (&r)[NS]) {
+        if constexpr (TWO)
+            r[NS - 1] = (m[NS - 1] << 1) | (m[0] >> 63);
+        r[0] = m[0] << 1;
+    };
+    auto after = [&](const Place &q) {
+        Place r;
+        r.i = q.i + 1;
+        next_lane(q.me, r.me);
+        const uint32_t step = 8u * (uint32_t)(N - q.i - 2); // pair_row(i + 1) - pair_row(i)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            r.upto[s] = q.upto[s] | r.me[s];
+            r.at[s] = q.at[s] + (lane_bit(q.upto[s]) ? 8u : step);
+        }
+        return r;
+    };
+    struct Move {
+        double x, y, z;
+        uint32_t w;
+    };
+    constexpr uint64_t kA = 1ull, kB1 = 1ull << 16, kB0 = 1ull << 32;
+    // Two moves at once, A of bead qa.i, then B of the next bead (at qb).  The
+    // two are bonded, so B's pair terms do not depend on A's outcome: only
+    // the change of the bond between them does (ddn0 if A is rejected, ddn1 if
+    // accepted), and B's start.  The terms, summed over the lanes with the
+    // bond changes in the lanes of the bonded partners (dup: the bond to the
+    // bead after, ddn: to the bead before), are three sums: A, B after a
+    // rejection, B after an acceptance; bin, threshold and decision of all
+    // three are taken together, in lanes 0, 32 and 16.  can: the lanes of
+    // those that may be accepted (no bond breaks, there is a bead).  Accepted
+    // moves change positions, cached terms, E and b; acc_a, acc_b: which.
+    auto attempt2 = [&](const Place &qa, const Place &qb, uint64_t can, const Move &A, const double (&dup_a)[NS],
+                        const double (&ddn_a)[NS], const Move &Bm, const double (&dup_b)[NS],
+                        const double (&ddn0)[NS], const double (&ddn1)[NS], uint32_t &acc_a, uint32_t &acc_b) {
+        uint64_t mc[NS], mz[NS], pa[NS], pb[NS]; // the lanes after B's and before A's; the pair terms of A, B
+        next_lane(qb.me, mc);
+        mz[0] = qa.me[0] >> 1;
         if constexpr (TWO) {
-            up[NS - 1] = (me[NS - 1] << 1) | (me[0] >> 63);
-            dn[NS - 1] = me[NS - 1] >> 1;
-            dn[0] |= me[NS - 1] << 63;
+            mz[0] |= qa.me[NS - 1] << 63;
+            mz[NS - 1] = qa.me[NS - 1] >> 1;
         }
-        double wx = 0.0, wy = 0.0, wz = 0.0;
-        if constexpr (!CACHE)
-            wx = was[i].x, wy = was[i].y, wz = was[i].z;
-        double t = 0.0;
-        double lnew[NS]; // CACHE: the new pair terms
-        uint32_t at[NS]; // and where they belong
-        const uint32_t row = 8u * (uint32_t)pair_row(i, N);
+        double old_a[NS], old_b[NS];
+        if constexpr (CACHE) {
+            // the reads first, their latency covered by the new terms
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            pairs[s] = valid[s] & ~(me[s] | up[s] | dn[s]);
-            double ts = 0.0;
-            lnew[s] = 0.0;
-            at[s] = 0u;
-            if (lane_bit(pairs[s])) {
-                if constexpr (CACHE) {
-                    at[s] = j + 64 * s < i ? lo[s] + 8u * (uint32_t)i : hi[s] + row;
-                    // the read first, its latency covered by the new term
-                    const double old = *(lds_f64 *)(uintptr_t)at[s];
-                    __builtin_amdgcn_sched_barrier(0);
-                    lnew[s] = lj_energy(p, dist2d(xd[s], yd[s], zd[s], nx, ny, nz));
-                    ts = lnew[s] - old;
-                } else {
-                    ts = lj_energy(p, dist2d(xd[s], yd[s], zd[s], nx, ny, nz)) -
-                         lj_energy(p, dist2d(xd[s], yd[s], zd[s], wx, wy, wz));
-                }
+            for (int s = 0; s < NS; ++s) {
+                old_a[s] = *(lds_f64 *)(uintptr_t)qa.at[s];
+                old_b[s] = *(lds_f64 *)(uintptr_t)qb.at[s];
             }
-            ts = lane_bit(up[s]) ? dup[s] : ts;
-            ts = lane_bit(dn[s]) ? ddn[s] : ts;
-            t = s == 0 ? ts : t + ts;
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            const BeadRecord wa = was[qa.i], wb = was[min(qb.i, N - 1)];
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                lj_energy2(p, dist2d(xd[s], yd[s], zd[s], wa.x, wa.y, wa.z), dist2d(xd[s], yd[s], zd[s], wb.x, wb.y, wb.z),
+                           old_a[s], old_b[s]);
+            }
         }
-        const double En = E + tree_sum(t); // in lane 0
-        const uint64_t inside = __builtin_amdgcn_ballot_w64(En >= p.x_lo) & __builtin_amdgcn_ballot_w64(En < p.x_hi);
-        // (inside the range the quotient is not negative: truncation is floor)
-        const uint32_t bn = (uint32_t)__builtin_amdgcn_readlane((int)((En - p.x_lo) * p.scale), 0);
-        if (!(inside & 1ull) || bn >= B)
-            return false;
-        const uint32_t T = *(const uint32_t *)((const uint8_t *)a.thresholds + (row_at + 4u * bn));
-        if (!(__builtin_amdgcn_ballot_w64(w < T) & 1ull))
-            return false;
+        double ta = 0.0, tb0 = 0.0, tb1 = 0.0;
+        double la[NS], lb[NS]; // the new pair terms
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            if (lane_bit(me[s]))
-                xd[s] = nx, yd[s] = ny, zd[s] = nz;
+            pa[s] = valid[s] & ~(mz[s] | qa.me[s] | qb.me[s]);
+            pb[s] = valid[s] & ~(qa.me[s] | qb.me[s] | mc[s]);
+            lj_energy2(p, dist2d(xd[s], yd[s], zd[s], A.x, A.y, A.z), dist2d(xd[s], yd[s], zd[s], Bm.x, Bm.y, Bm.z), la[s],
+                       lb[s]);
+            double ea = lane_bit(pa[s]) ? la[s] - old_a[s] : 0.0;
+            ea = lane_bit(qb.me[s]) ? dup_a[s] : ea;
+            ea = lane_bit(mz[s]) ? ddn_a[s] : ea;
+            double eb = lane_bit(pb[s]) ? lb[s] - old_b[s] : 0.0;
+            eb = lane_bit(mc[s]) ? dup_b[s] : eb;
+            const double eb0 = lane_bit(qa.me[s]) ? ddn0[s] : eb, eb1 = lane_bit(qa.me[s]) ? ddn1[s] : eb;
+            ta = s == 0 ? ea : ta + ea;
+            tb0 = s == 0 ? eb0 : tb0 + eb0;
+            tb1 = s == 0 ? eb1 : tb1 + eb1;
+        }
+        const double t = tree_sum3(ta, tb0, tb1);
+        const double Ea = E + readlane_f64(t, 0);
+        const double En = (lane_bit(kB1) ? Ea : E) + t;
+        const uint32_t bn = (uint32_t)cvt_i32((En - p.x_lo) * p.scale);
+        // (inside the range the quotient is not negative: truncation is floor)
+        const uint64_t ok = can & __builtin_amdgcn_ballot_w64(En >= p.x_lo) & __builtin_amdgcn_ballot_w64(En < p.x_hi) &
+                            __builtin_amdgcn_ballot_w64(bn < B);
+        const uint32_t row1 = 4u * B * min((uint32_t)__builtin_amdgcn_readlane((int)bn, 0), B - 1u);
+        const uint32_t w = lane_bit(kA) ? A.w : Bm.w;
+        // (one load for all lanes: those without a move read the first entry)
+        const uint32_t entry = lane_bit(ok) ? (lane_bit(kB1) ? row1 : row_at) + 4u * bn : 0u;
+        const uint32_t T = *(const uint32_t *)((const uint8_t *)a.thresholds + entry);
+        const uint64_t acc = ok & __builtin_amdgcn_ballot_w64(w < T);
+        acc_a = (uint32_t)acc & 1u;
+        acc_b = (acc_a ? (uint32_t)acc >> 16 : (uint32_t)(acc >> 32)) & 1u;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            set_bead(acc_a ? qa.me[s] : 0ull, xd[s], yd[s], zd[s], A.x, A.y, A.z);
+            set_bead(acc_b ? qb.me[s] : 0ull, xd[s], yd[s], zd[s], Bm.x, Bm.y, Bm.z);
             if constexpr (CACHE) {
-                if (lane_bit(pairs[s]))
-                    *(lds_f64_out *)(uintptr_t)at[s] = lnew[s];
+                if (lane_bit(acc_a ? pa[s] : 0ull))
+                    *(lds_f64_out *)(uintptr_t)qa.at[s] = la[s];
+                if (lane_bit(acc_b ? pb[s] : 0ull))
+                    *(lds_f64_out *)(uintptr_t)qb.at[s] = lb[s];
             }
         }
         if constexpr (CACHE)
             lds_fence();
-        E = En;
-        b = (int32_t)bn;
-        row_at = 4u * B * bn;
-        return true;
+        const int from = (int)((acc_a ? 16u : 32u) * acc_b);
+        const uint32_t any = acc_a | acc_b;
+        const double Et = readlane_f64(En, from);
+        const int32_t bt = __builtin_amdgcn_readlane((int)bn, from);
+        E = any ? Et : E;
+        b = any ? bt : b;
+        row_at = 4u * B * (uint32_t)b;
     };
 
+    int trend = 0; // of the rotations' outcomes
     for (int s_ = 0; s_ < a.n_sweeps; ++s_) {
         const uint32_t g = a.g0 + (uint32_t)s_;
         float pnx[NS], pny[NS], pnz[NS];
@@ -508,34 +633,46 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
 #pragma unroll
         for (int s = 0; s < NS; ++s)
             done[s] = 0ull;
-        bool prev_acc = false;
-        uint64_t me[NS];
-        me[0] = 1ull;
-        if constexpr (TWO)
-            me[NS - 1] = 0ull;
-        BeadRecord next = rec[0];
-        for (int i = 0; i < N; ++i) {
-            const BeadRecord r = next;
-            next = rec[i + 1 < N ? i + 1 : i]; // its latency beside this move's arithmetic
-            uint64_t broken = 0ull; // no forward bond at the last bead, no backward one at the first: bits clear
+        uint32_t prev_acc = 0u;
+        auto shift2 = [&](Place &q, const Move &A, const Move &Bm) {
+            const Place qb = after(q);
+            uint64_t brk = 0ull, brk0 = 0ull, brk1 = 0ull; // no forward bond at the last bead, no backward one at the first: bits clear
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
-                broken |= me[s] & (brk_f[s] | (prev_acc ? brk_a[s] : brk_r[s]));
-            if (broken) {
-                prev_acc = false;
-            } else {
+            for (int s = 0; s < NS; ++s) {
+                brk |= q.me[s] & (brk_f[s] | (prev_acc ? brk_a[s] : brk_r[s]));
+                brk0 |= qb.me[s] & (brk_f[s] | brk_r[s] | ~valid[s]);
+                brk1 |= qb.me[s] & (brk_f[s] | brk_a[s] | ~valid[s]);
+            }
+            uint32_t acc_a = 0u, acc_b = 0u;
+            if (!brk || !brk0) {
                 double ddn[NS];
 #pragma unroll
                 for (int s = 0; s < NS; ++s)
                     ddn[s] = prev_acc ? ddn_a[s] : ddn_r[s];
-                prev_acc = attempt(i, me, r.x, r.y, r.z, dup, ddn, r.w);
+                attempt2(q, qb, (brk ? 0ull : kA) | (brk0 ? 0ull : kB0) | (brk1 ? 0ull : kB1), A, dup, ddn, Bm, dup, ddn_r,
+                         ddn_a, acc_a, acc_b);
 #pragma unroll
                 for (int s = 0; s < NS; ++s)
-                    done[s] |= prev_acc ? me[s] : 0ull;
+                    done[s] |= (acc_a ? q.me[s] : 0ull) | (acc_b ? qb.me[s] : 0ull);
             }
-            if constexpr (TWO)
-                me[NS - 1] = (me[NS - 1] << 1) | (me[0] >> 63);
-            me[0] <<= 1;
+            prev_acc = acc_b;
+            q = after(qb);
+        };
+        auto move_of = [&](int k) {
+            const BeadRecord &r = rec[min(k, N - 1)];
+            return Move{r.x, r.y, r.z, r.w};
+        };
+        Place q = start();
+        Move a0 = move_of(0), b0 = move_of(1);
+        for (;;) { // two pairs a turn, each read while the other is under way
+            const Move a1 = move_of(q.i + 2), b1 = move_of(q.i + 3);
+            shift2(q, a0, b0);
+            if (q.i >= N)
+                break;
+            a0 = move_of(q.i + 2), b0 = move_of(q.i + 3);
+            shift2(q, a1, b1);
+            if (q.i >= N)
+                break;
         }
         if (a.record) {
 #pragma unroll
@@ -564,7 +701,7 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
             // four rotations are accepted in earnest: a plan serves about
             // eight moves, and its FP64 chain of divisions, square root and
             // logarithm, which each move had to itself, is paid once (N = 80,
-            // 512 chains: 5.4e8 -> 6.3e8 moves/s).  Six or eight runs serve
+            // 512 chains: 5.4e8 -> 6.3e8 moves/s, moves one at a time).  Six or eight runs serve
             // little more and cost LDS (N = 40, 4096 chains, four, six and
             // eight: 2.48e9, 2.19e9, 2.19e9; N = 80, 512 chains: 6.31e8,
             // 6.51e8, 6.26e8).
@@ -577,10 +714,9 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
             RotateRecord *plan = (RotateRecord *)rec;
             const int slot = (j >> 1) & (kPlanBeads - 1);
             const bool right = lane_bit(0xAAAAAAAAAAAAAAAAull); // odd lanes: the bond to the bead after
-            me[0] = 1ull;
-            if constexpr (TWO)
-                me[NS - 1] = 0ull;
-            for (int i = 0; i < N;) {
+            q = start();
+            while (q.i < N) {
+                const int i = q.i;
                 const int bd = i + slot;
                 auto at = [&](int k, double &x, double &y, double &z) {
                     float fx = from_lane((float)xd[0], k & 63), fy = from_lane((float)yd[0], k & 63),
@@ -644,44 +780,54 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
                 lds_fence();
                 const int end = min(i + kPlanBeads, N);
                 int run = 0;
-                RotateRecord next = plan[0];
-                for (int t = 0; i < end && run < kPlanRuns; ++i, ++t) {
-                    const RotateRecord r = next;
-                    // both continuations, their latency beside this move's arithmetic
-                    const int t1 = min(t + 1, kPlanBeads - 1), run1 = min(run + 1, kPlanRuns - 1);
-                    const RotateRecord if_rej = plan[t1], if_acc = plan[run1 * kPlanBeads + t1];
-                    bool acc = false;
-                    if (__builtin_amdgcn_readfirstlane((int)r.w) != -1) {
-                        const double up = i + 1 < N ? r.f[1] - bond_of(i) : 0.0;
-                        double rdup[NS], rddn[NS];
+                // Rotations in pairs as well, B's the one planned for the
+                // likelier outcome of A: after the other outcome B is left
+                // for the next turn.
+                while (q.i < end && run < kPlanRuns) {
+                    const RotateRecord ra = plan[run * kPlanBeads + q.i - i];
+                    const bool guess = trend >= 0 && run + 1 < kPlanRuns;
+                    const bool two = q.i + 1 < end;
+                    const RotateRecord rb = plan[(guess ? run + 1 : 0) * kPlanBeads + (two ? q.i + 1 - i : 0)];
+                    const Place qb = after(q);
+                    const bool can_a = __builtin_amdgcn_readfirstlane((int)ra.w) != -1;
+                    const bool can_b = two && __builtin_amdgcn_readfirstlane((int)rb.w) != -1;
+                    uint32_t acc_a = 0u, acc_b = 0u;
+                    if (can_a || (can_b && !guess)) {
+                        const bool last_a = q.i + 1 == N, last_b = q.i + 2 >= N;
+                        const double ua = bond_of(q.i), ub_ = bond_of(min(q.i + 1, N - 1));
+                        double dup_a[NS], ddn_a2[NS], dup_b[NS], ddn0[NS], ddn1[NS];
 #pragma unroll
                         for (int s = 0; s < NS; ++s) {
-                            rdup[s] = up;
-                            rddn[s] = r.f[0] - ub[s];
+                            dup_a[s] = last_a ? 0.0 : ra.f[1] - ua;
+                            ddn_a2[s] = ra.f[0] - ub[s];
+                            dup_b[s] = last_b ? 0.0 : rb.f[1] - ub_;
+                            ddn0[s] = rb.f[0] - ua;
+                            ddn1[s] = rb.f[0] - ra.f[1];
                         }
-                        acc = attempt(i, me, r.x, r.y, r.z, rdup, rddn, r.w);
-                        if (acc) {
-                            nacc += a.record ? 1u : 0u;
-                            uint64_t dn[NS];
-                            dn[0] = me[0] >> 1;
-                            if constexpr (TWO) {
-                                dn[0] |= me[NS - 1] << 63;
-                                dn[NS - 1] = me[NS - 1] >> 1;
-                            }
+                        attempt2(q, qb, (can_a ? kA : 0ull) | (can_b ? (guess ? kB1 : kB0) : 0ull),
+                                 Move{ra.x, ra.y, ra.z, ra.w}, dup_a, ddn_a2, Move{rb.x, rb.y, rb.z, rb.w}, dup_b, ddn0,
+                                 ddn1, acc_a, acc_b);
+                        nacc += a.record ? acc_a + acc_b : 0u;
 #pragma unroll
-                            for (int s = 0; s < NS; ++s) {
-                                ub[s] = lane_bit(i + 1 < N ? me[s] : 0ull) ? r.f[1] : ub[s];
-                                ub[s] = lane_bit(dn[s]) ? r.f[0] : ub[s];
-                            }
+                        for (int s = 0; s < NS; ++s) {
+                            uint64_t mz = q.me[s] >> 1;
+                            if (TWO && s == 0)
+                                mz |= q.me[NS - 1] << 63;
+                            // bond i by A's forward bond, then by B's backward one
+                            ub[s] = lane_bit(acc_a ? mz : 0ull) ? ra.f[0] : ub[s];
+                            ub[s] = lane_bit(acc_a && !last_a ? q.me[s] : 0ull) ? ra.f[1] : ub[s];
+                            ub[s] = lane_bit(acc_b ? q.me[s] : 0ull) ? rb.f[0] : ub[s];
+                            ub[s] = lane_bit(acc_b && !last_b ? qb.me[s] : 0ull) ? rb.f[1] : ub[s];
                         }
                     }
-                    next.x = acc ? if_acc.x : if_rej.x, next.y = acc ? if_acc.y : if_rej.y;
-                    next.z = acc ? if_acc.z : if_rej.z, next.w = acc ? if_acc.w : if_rej.w;
-                    next.f[0] = acc ? if_acc.f[0] : if_rej.f[0], next.f[1] = acc ? if_acc.f[1] : if_rej.f[1];
-                    run = acc ? run + 1 : 0;
-                    if constexpr (TWO)
-                        me[NS - 1] = (me[NS - 1] << 1) | (me[0] >> 63);
-                    me[0] <<= 1;
+                    trend = max(-4, min(3, trend + (acc_a ? 1 : -1)));
+                    if (two && (acc_a != 0u) == guess) {
+                        run = acc_b ? (acc_a ? run + 2 : 1) : 0;
+                        q = after(qb);
+                    } else {
+                        run = acc_a ? run + 1 : 0;
+                        q = qb;
+                    }
                 }
             }
             // one double bridging: bonds (bi, bi+1), (bj, bj+1) -> (bi, bj), (bi+1, bj+1)
@@ -710,7 +856,7 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
                     const double ljl = lj_energy(p, dist2d(jx, jy, jz, mx, my, mz));
                     const double dF = ((fij + fkl) - fik) - fjl;
                     const double dL = ((lik + ljl) - lij) - lkl;
-                    const double En = readlane_f64(E, 0) + (dF + dL);
+                    const double En = E + (dF + dL);
                     const int32_t bn = energy_bin(p, En, a.n_bins);
                     if (bn >= 0 && min(w.w[3], 0xFFFFFFFEu) < a.thresholds[(size_t)b * B + (uint32_t)bn]) {
                         // beads bi+1 .. bj in reverse order; the bonds between them reversed
@@ -841,21 +987,20 @@ hipError_t launch_patch_table(uint32_t *T, const uint32_t *pairs, int n, hipStre
     return hipGetLastError();
 }
 
-// The cache is used when its LDS does not cost wavefronts: a CU still holds
-// three per SIMD with it (the registers of the full move set allow no more),
-// or every workgroup of a small grid has its place at once.  Measured, moves/s
+// The cache is used when a CU still holds two wavefronts per SIMD with it, or
+// every workgroup of a small grid has its place at once.  Measured, moves/s
 // with the cache and without (shifts | full set):
-//   N = 50, 4096 chains (three workgroups per CU)   4.03e9 | 2.67e9   4.03e9 | 2.48e9   cache
-//   N = 54, 4096 chains (two per CU)                3.70e9 | 2.47e9   4.04e9 | 2.46e9
-//   N = 64, 2048 chains (two per CU, all at once)   3.69e9 | 2.39e9                     cache
-//   N = 64, 2052 chains                             2.33e9 | 1.55e9   2.65e9 | 1.71e9
-//   N = 64, 4096 chains                             3.74e9 | 2.49e9   4.11e9 | 2.51e9
-//   N = 80, 1024 chains (one per CU, all at once)   1.70e9 | 1.24e9                     cache
-//   N = 80, 2048 chains                             1.68e9 | 1.24e9   2.23e9 | 1.60e9
+//   N = 50, 4096 chains (three workgroups per CU)   4.48e9 | 2.83e9   4.08e9 | 2.50e9   cache
+//   N = 54, 4096 chains (two per CU)                4.19e9 | 2.64e9   4.11e9 | 2.56e9   cache
+//   N = 64, 2048 chains (two per CU, all at once)   4.18e9 | 2.57e9   3.55e9 | 2.30e9   cache
+//   N = 64, 2052 chains                             2.77e9 | 1.67e9   2.77e9 | 1.72e9   cache
+//   N = 64, 4096 chains                             4.21e9 | 2.64e9   4.17e9 | 2.59e9   cache
+//   N = 80, 1024 chains (one per CU, all at once)   1.91e9 | 1.35e9   1.83e9 | 1.30e9   cache
+//   N = 80, 2048 chains                             1.88e9 | 1.35e9   2.34e9 | 1.67e9
 static bool polymer_cache_fits(size_t lds, int chains_per_block, long blocks, int cus)
 {
     const long room = (long)(160u * 1024u / lds);
-    return room * chains_per_block >= 12 || (room >= 1 && room * cus >= blocks);
+    return room * chains_per_block >= 8 || (room >= 1 && room * cus >= blocks);
 }
 
 template <bool TWO, bool MOVES>

@@ -1,4 +1,6 @@
-"""Rotations are planned 16 beads and up to four accepted ones ahead: chains of
+"""Moves are taken in pairs: odd and even chains, the last bead in the last
+lane of a set, and (steps) shifts of which few, half and most break a bond.
+Rotations are planned 16 beads and up to four accepted ones ahead: chains of
 a whole plan, of one bead more or less and of two beads, with flat weights
 (long runs of accepted rotations) and steep ones (most rejected).  Histograms,
 bins and float positions equal the oracle's."""
@@ -11,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("slope", [0.0, -1.0, -20.0])
-@pytest.mark.parametrize("N", [2, 15, 16, 17, 32, 33, 65])
+@pytest.mark.parametrize("N", [2, 15, 16, 17, 32, 33, 63, 65, 127])
 def test_planned_rotations(N, slope):
     from oracle import oracle as orc
     from paper_1312_2213_amd import muca
@@ -23,6 +25,30 @@ def test_planned_rotations(N, slope):
     cfg = muca.muca_config_default("polymer", 0, 2, chains, 31, n_beads=N, moves=1, **rng)
     g = muca.Run(cfg, positions=pos)
     lnw = slope * o.bin_centres()
+    o.lnW = np.array(lnw, np.float64)
+    g.set_lnw(lnw)
+    H = o.sweeps(15)
+    g.run_iteration(15)
+    g.merge_update()
+    assert np.array_equal(g.last_hist(), H)
+    got, bins, _ = g.chain_state()
+    assert np.array_equal(bins, o.bin)
+    assert np.array_equal(got, o.pos)
+
+
+@pytest.mark.parametrize("step", [0.05, 0.6, 2.0])
+@pytest.mark.parametrize("N", [31, 64, 96])
+def test_broken_bonds(N, step):
+    from oracle import oracle as orc
+    from paper_1312_2213_amd import muca
+    print(f"N={N}, step {step}", flush=True)
+    chains = 21
+    pos = polymer_walk(N, chains, 29)
+    rng = dict(x_lo=-400.0, x_hi=100.0, n_bins=1000, step=step)
+    o = orc.PolymerRun(n_beads=N, n_chains=chains, seed=37, pos=pos, moves=0, **rng)
+    cfg = muca.muca_config_default("polymer", 0, 2, chains, 37, n_beads=N, moves=0, **rng)
+    g = muca.Run(cfg, positions=pos)
+    lnw = -0.5 * o.bin_centres()
     o.lnW = np.array(lnw, np.float64)
     g.set_lnw(lnw)
     H = o.sweeps(15)
