@@ -54,13 +54,14 @@ PEAK_INT_OPS = 256 * 4 * 16 * 2.4e9
 # Metropolis update 13.
 OPS_PER_ATTEMPT = 23.0
 # HBM bytes of one 10^4-sweep launch of the Ising L=64 kernel (4096 chains,
-# 16 lanes per chain), from the rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled
+# one wavefront per chain), from the rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled
 # by a device copy of known size, and the sha256 of the sources and flags
 # that built the profiled kernel: the figure is reported only while they are
 # unchanged.
-HBM_TRAFFIC = {"bytes_per_launch": 3339.625 * 1024 * 2.0 + 2482.125 * 1024,
-               "kernel_sources_sha256": "b18bbd26c4072b73"}
-KERNEL_SOURCES = ["paper_1312_2213_amd/csrc/lattice_impl.h", "paper_1312_2213_amd/csrc/muca_internal.h",
+HBM_TRAFFIC = {"bytes_per_launch": 2455.5 * 1024 * 2.0 + 2770.125 * 1024,
+               "kernel_sources_sha256": "c863242ad38bca73"}
+KERNEL_SOURCES = ["paper_1312_2213_amd/csrc/lattice_impl.h", "paper_1312_2213_amd/csrc/lattice_tile.h",
+                  "paper_1312_2213_amd/csrc/muca_internal.h",
                   "paper_1312_2213_amd/csrc/philox.h", "paper_1312_2213_amd/csrc/lattice_ising.hip"]
 
 
@@ -451,8 +452,8 @@ def bench_ising64(args):
     traffic = HBM_TRAFFIC["bytes_per_launch"] if (
         sha == HBM_TRAFFIC["kernel_sources_sha256"] and S == 10000 and C == 4096
         and args.lanes_per_chain in (0, 16)) else None
-    # the kernel is branch-free: the same launch at weights that reject about
-    # half of the moves takes the same time
+    # the same launch at weights that reject about half of the moves (a tile's
+    # passes depend on the weights)
     rej = muca.Run(cfg, stream=stream)
     import numpy as np
     rej.set_lnw(-CPU_BETA * (-2.0 * L * L + 4.0 * np.arange(rej.n_bins)))
@@ -485,7 +486,7 @@ def bench_ising64(args):
                      "traffic_unit": "HBM bytes per launch (FETCH_SIZE x 2.0 + WRITE_SIZE, copy-calibrated)",
                      "traffic_kernel_sources_sha256": HBM_TRAFFIC["kernel_sources_sha256"],
                      "kernel_sources_sha256": sha,
-                     "kernel": "lattice_sweeps<Ising, L=64, bit-packed>", "kernel_ms": kern_ms,
+                     "kernel": "lattice_tiles<Ising, L=64>, bit-packed", "kernel_ms": kern_ms,
                      "ops_per_attempt": OPS_PER_ATTEMPT, "cycles_per_attempt_per_chain": cycles,
                      "kernel_ms_rejecting_weights": rej_ms,
                      "accept_rate_rejecting_weights": rej_stats["accept_rate"]},
