@@ -350,6 +350,9 @@ template <bool TWO, bool MOVES, bool CACHE>
 __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams p)
 {
     extern __shared__ __align__(16) uint32_t lhist[];
+    __shared__ unsigned long long accepted; // by the workgroup's chains
+    if (threadIdx.x == 0)
+        accepted = 0ull;
     for (int i = threadIdx.x; i < a.n_bins; i += blockDim.x)
         lhist[i] = 0u;
     __syncthreads();
@@ -910,10 +913,13 @@ __global__ __launch_bounds__(256) void polymer_sweeps(PolymerArgs a, PolyParams 
     if (j == 0) {
         a.energy[c] = E;
         a.bins[c] = b;
-        if (a.record && c < a.n_chains && a.accepts && nacc)
-            atomicAdd(a.accepts, (unsigned long long)nacc);
+        if (a.record && c < a.n_chains)
+            atomicAdd(&accepted, (unsigned long long)nacc);
     }
     __syncthreads();
+    // one atomic per workgroup on the run's one counter
+    if (threadIdx.x == 0 && a.accepts && accepted)
+        atomicAdd(a.accepts, accepted);
     for (int i = threadIdx.x; i < a.n_bins; i += blockDim.x) {
         const uint32_t v = lhist[i];
         if (v)
@@ -999,7 +1005,7 @@ hipError_t launch_patch_table(uint32_t *T, const uint32_t *pairs, int n, hipStre
 //   N = 80, 2048 chains                             1.88e9 | 1.35e9   2.34e9 | 1.67e9
 static bool polymer_cache_fits(size_t lds, int chains_per_block, long blocks, int cus)
 {
-    const long room = (long)(160u * 1024u / lds);
+    const long room = (long)(160u * 1024u / (lds + 16u)); // 16: the workgroup's counter
     return room * chains_per_block >= 8 || (room >= 1 && room * cus >= blocks);
 }
 
