@@ -89,24 +89,38 @@ static size_t align256(size_t x) { return (x + 255u) & ~(size_t)255u; }
 // Most chains of a run that takes the one-wavefront-per-chain kernels by
 // default.  Their rate stops growing once every SIMD has four wavefronts
 // (4096 chains); that of 1 to 4 lanes per chain grows until the lanes fill
-// the chip.  Measured, 1e9 attempts/s, a wavefront / the best of 1, 2 and 4
-// lanes per chain:
-//                  4096         8192         16384        32768
-//   Ising L = 64   280 / 100    244 / 199    299 / 396    310 / 618
-//   Ising L = 16   236 /  79    238 / 158    238 / 315
-//   MUMA  L = 32   399 /  90    413 / 179    417 / 356    417 / 562
-//   Potts L = 48   205 /  59    215 / 117    205 / 224    209 / 285
-//   Potts L = 24   130 /  53    134 / 106    134 / 210
-// and with the threshold table in global memory, whose latency few lanes per
-// chain hide worse,
-//   MUMA  L = 64   460 /  67    476 / 132    474 / 260    478 / 351
-//   Potts L = 64   243 /  51    242 / 101    233 / 195    244 / 242
-// The rates of few lanes per chain are linear in the chains between these
-// columns, which puts the lines near 1.1e4 (Ising), 1.2e4 (Potts) and 2.2e4
-// (MUMA), and about twice as far without a staged table.
-static long tile_max_chains(int model, bool staged)
+// the chip.  Where the two meet depends on the model (passes per tile and
+// their cost) and on the lattice (rows per tile; lanes without a site at
+// L = 24 and 48; launch costs at the smallest).  Measured, a wavefront's rate
+// over the best of 1, 2 and 4 lanes per chain, launches of 6 to 10 sweeps:
+//                   8192   12288   16384   24576 chains
+//   Ising L = 64    1.26    0.90    0.67    0.64
+//           L = 32  1.17    0.81    0.66    0.47
+//           L = 24  1.12    0.78    0.61    0.45
+//           L = 16  1.44    1.02    0.83    0.60
+//           L = 8   0.98    0.78    0.64    0.49   (6144: 1.17)
+//           L = 4   (3072: 0.98, 4096: 0.91, 6144: 0.64; 100 sweeps at 4096: 1.32)
+//   Potts L = 48    1.44    1.01    0.81    0.85
+//           L = 32  1.22    0.88    0.67    0.70
+//           L = 24  1.01    0.68    0.54    0.55
+//           L = 16  1.40    1.06    0.81    0.82
+//           L = 8   1.15    0.87    0.72    0.62
+//   MUMA  L = 48    2.10    1.42    1.11    0.94
+//           L = 32  2.24    1.54    1.17    1.00
+//           L = 24  2.04    1.40    1.11    0.80
+//           L = 16  1.68    1.22    0.98    0.81
+//           L = 8   1.26    0.99    0.83    0.65
+// With the table of L = 64 in global memory, whose latency few lanes per
+// chain hide worse, MUMA 1.94 at 24576 chains and 1.46 at 32768, Potts 1.15
+// and 0.89: twice as far.  The lines lie where the ratio is still about 1.08.
+static long tile_max_chains(int model, int L, bool staged)
 {
-    return (model == kIsing ? 10240 : model == kPotts ? 12288 : 20480) * (staged ? 1 : 2);
+    const int row = L >= 64 ? 0 : L >= 48 ? 1 : L >= 32 ? 2 : L >= 24 ? 3 : L >= 16 ? 4 : L >= 8 ? 5 : 6;
+    static const int ising[7] = {10240, 10240, 9216, 8704, 11520, 6912, 4096};
+    static const int potts[7] = {12288, 11520, 9728, 6144, 11776, 9216, 4096};
+    static const int muma[7] = {20480, 17408, 20480, 16896, 14336, 10752, 4096};
+    const long n = (model == kIsing ? ising : model == kPotts ? potts : muma)[row];
+    return L == 64 && !staged ? 2 * n : n;
 }
 
 static int bin_step(int model) { return model == kIsing ? 4 : (model == kPotts ? 1 : 2); }
@@ -196,7 +210,7 @@ int muca_geometry(const muca_config *c, Geometry *g)
         return muca_fail(MUCA_E_ARG, "%d bins exceed the LDS histogram", g->n_bins);
     g->table_in_lds = c->table_in_lds == 1 || (c->table_in_lds < 0 && g->lds_bytes <= 160u * 1024u);
     if (c->lanes_per_chain == 16 ||
-        (c->lanes_per_chain == 0 && (long)g->c_pad <= tile_max_chains(g->model, g->table_in_lds)))
+        (c->lanes_per_chain == 0 && (long)g->c_pad <= tile_max_chains(g->model, c->L, g->table_in_lds)))
         g->tile_chains = 16;
     if (g->cpb > 256 && !g->table_in_lds)
         return muca_fail(MUCA_E_ARG, "blocks of %d threads need the threshold table staged in LDS", g->cpb);

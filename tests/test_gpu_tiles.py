@@ -93,8 +93,9 @@ def test_workgroup_shapes_and_counter_flushes(chains_per_block):
     assert_same_state(o, g)
 
 
-@pytest.mark.parametrize("model,L,chains,tlds", [("ising", 8, 10240, 1), ("ising", 8, 10304, 1), ("potts", 8, 12288, 1),
-                                                 ("potts", 8, 24640, 0), ("muma", 8, 40960, 0), ("muma", 8, 20544, 1)])
+@pytest.mark.parametrize("model,L,chains,tlds", [("ising", 8, 6912, 1), ("ising", 8, 6976, 1), ("potts", 8, 9216, 1),
+                                                 ("potts", 8, 9280, 0), ("muma", 8, 10752, 0), ("muma", 8, 10816, 1),
+                                                 ("muma", 4, 4096, 1), ("ising", 4, 4160, 1)])
 def test_default_kernel_on_either_side_of_its_line(model, L, chains, tlds):
     """The default choice by chain count, against four lanes per chain."""
     from paper_1312_2213_amd import muca
