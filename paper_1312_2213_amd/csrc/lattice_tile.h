@@ -29,14 +29,14 @@
 // lane i holds its site's colour of every tile, four per register (Potts).
 //
 // Bound: instruction issue with four wavefronts per SIMD (Ising: scalar and
-// vector units about even, 130 instructions per tile of 64; Potts: vector),
+// vector units about even, 107 instructions per tile of 64; Potts: vector),
 // latency (LDS reads, the scalar chain) below that.  Measured per iteration,
 // before (16 lanes per chain, site by site) and after: Ising L = 64, 4096
-// chains, 400 sweeps 54.4 -> 18.1 ms; Ising L = 32 int8, 1000 chains, 35
-// sweeps 1.69 -> 0.34 ms; MUMA L = 32 with the joint histogram, 512 chains,
-// 67 sweeps 2.85 -> 0.52 ms; Potts q = 8 L = 48, 2048 chains, 362 sweeps
+// chains, 400 sweeps 54.5 -> 17.6 ms; Ising L = 32 int8, 1000 chains, 35
+// sweeps 1.69 -> 0.32 ms; MUMA L = 32 with the joint histogram, 512 chains,
+// 67 sweeps 2.85 -> 0.49 ms; Potts q = 8 L = 48, 2048 chains, 362 sweeps
 // 39.4 -> 10.9 ms; Potts q = 10 L = 64 (table in global memory), 1024 chains,
-// 60 sweeps 14.5 -> 2.7 ms.
+// 60 sweeps 14.4 -> 2.8 ms.
 #pragma once
 #include "lattice_impl.h"
 
