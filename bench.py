@@ -61,7 +61,7 @@ OPS_PER_ATTEMPT = 23.0
 HBM_TRAFFIC = {"bytes_per_launch": 2456.0625 * 1024 * 2.0 + 2410.125 * 1024,
                "kernel_sources_sha256": "b9014daa976b7c29"}
 KERNEL_SOURCES = ["paper_1312_2213_amd/csrc/lattice_impl.h", "paper_1312_2213_amd/csrc/lattice_tile.h",
-                  "paper_1312_2213_amd/csrc/muca_internal.h",
+                  "paper_1312_2213_amd/csrc/launch_rules.h", "paper_1312_2213_amd/csrc/muca_internal.h",
                   "paper_1312_2213_amd/csrc/philox.h", "paper_1312_2213_amd/csrc/lattice_ising.hip"]
 
 

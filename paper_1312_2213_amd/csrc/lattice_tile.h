@@ -39,6 +39,7 @@
 // 60 sweeps 14.4 -> 2.8 ms.
 #pragma once
 #include "lattice_impl.h"
+#include "launch_rules.h"
 
 namespace muca {
 
@@ -765,8 +766,7 @@ __device__ __forceinline__ void tile_block(const LatticeArgs &a, int c_first, in
         b = __builtin_amdgcn_readfirstlane(((const gi32 *)a.bins)[c]);
     }
     const int flush_every = kMaxBlockCount / n_c;
-    for (int s0 = 0; s0 < a.n_sweeps; s0 += flush_every) {
-        const int n = min(flush_every, a.n_sweeps - s0);
+    for_segments(a.n_sweeps, flush_every, [&](int32_t s0, int32_t n) {
         if (active) {
             uint32_t nacc = 0u;
             ch.sweeps(a, (uint32_t)(a.chain0 + c), a.g0 + (uint32_t)s0, n, lane, a.thresholds, tbase, b, nacc,
@@ -794,7 +794,7 @@ __device__ __forceinline__ void tile_block(const LatticeArgs &a, int c_first, in
             *accepted = 0u;
         }
         __syncthreads();
-    }
+    });
     if (active) {
         ch.store(a, c, lane);
         if (lane == 0)

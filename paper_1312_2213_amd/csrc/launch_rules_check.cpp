@@ -1,0 +1,68 @@
+// launch_rules_check.cpp -- prints what the rules of launch_rules.h give for
+// cases read from a text file, so that they can be built on their own with
+// sanitizers and compared with an independent implementation.
+//
+// Input, whitespace-separated, one case after another:
+//   segments <total> <at_most>
+// Output: one line per case:
+//   segments: number of segments, their sum, shortest, longest, and the
+//     sweeps before the last one (it stops at 10^7 segments)
+#include <algorithm>
+#include <cinttypes>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "launch_rules.h"
+
+namespace {
+
+FILE *in = nullptr;
+
+[[noreturn]] void fail(const char *what)
+{
+    std::fprintf(stderr, "launch_rules_check: bad input (%s)\n", what);
+    std::exit(2);
+}
+
+long long get_int()
+{
+    long long v;
+    if (std::fscanf(in, "%lld", &v) != 1)
+        fail("integer");
+    return v;
+}
+
+} // namespace
+
+int main(int argc, char **argv)
+{
+    if (argc != 2)
+        fail("usage: launch_rules_check <cases file>");
+    in = std::fopen(argv[1], "r");
+    if (!in)
+        fail("cannot open the cases file");
+    char kind[32];
+    while (std::fscanf(in, "%31s", kind) == 1) {
+        if (!std::strcmp(kind, "segments")) {
+            const int32_t total = (int32_t)get_int(), at_most = (int32_t)get_int();
+            int64_t k = 0, sum = 0, shortest = INT64_MAX, longest = 0, before = 0;
+            muca::for_segments(total, at_most, [&](int32_t done, int32_t n) {
+                if (done != sum || ++k > 10000000) {
+                    std::printf("segments do not end or do not follow each other\n");
+                    std::exit(1);
+                }
+                before = done;
+                sum += n;
+                shortest = std::min<int64_t>(shortest, n);
+                longest = std::max<int64_t>(longest, n);
+            });
+            std::printf("%" PRId64 " %" PRId64 " %" PRId64 " %" PRId64 " %" PRId64 "\n", k, sum, k ? shortest : 0,
+                        longest, before);
+        } else {
+            fail(kind);
+        }
+    }
+    std::fclose(in);
+    return 0;
+}
