@@ -91,7 +91,8 @@ typedef struct muca_config {
     double lj_eps, lj_sigma, lj_rcut;
     double fene_k, fene_r0, fene_R; /* FENE -(K/2) R^2 ln(1-((r-r0)/R)^2)     */
     float step;             /* side of the displacement cube                   */
-    int32_t lanes_per_chain; /* lattice: 0 = auto, else 1, 2 or 4 lanes share one
+    int32_t lanes_per_chain; /* lattice: 0 = chosen for each launch (see
+                                muca_tile_chains), else 1, 2 or 4 lanes share one
                                 chain's random-number work, or 16: a wavefront per
                                 chain (fewest attempts at a time in sequence; it
                                 counts as 16 threads in chains_per_block)      */
@@ -244,8 +245,8 @@ int muca_reweight(const muca_run *run, const double *betas, int32_t n, double *o
  * (Eq. 2 over the merged histogram; the blocks are independent groups of
  * chains, so leaving one out at a time gives the statistical error of any
  * reweighted average).  Lattice runs.
- *   muca_blocks_shape: n_blocks = the number of chain blocks (workgroups of
- *     the run's plain launch) and chains_per_block; block k holds chains
+ *   muca_blocks_shape: n_blocks = the number of chain blocks (whole
+ *     workgroups of the run's launches) and chains_per_block; block k holds chains
  *     [k * chains_per_block, (k + 1) * chains_per_block), padding chains
  *     (>= n_chains) never counted.  MUCA_E_ARG for a polymer run.
  *   muca_run_iteration_blocks: muca_run_iteration that also adds each
@@ -367,6 +368,11 @@ int muca_autotune(const muca_config *cfg, void *d_ws, uint64_t ws_bytes, int64_t
 
 /* Accessors (host copies; synchronise the run's stream). */
 int muca_sizes(const muca_run *run, int32_t *n_bins, int32_t *n_cols, int32_t *n_sites);
+/* Chains per workgroup (one wavefront each) if the run's next plain launch
+ * takes one wavefront per chain, else 0 (1 to 4 lanes per chain, polymers).
+ * With lanes_per_chain 0 it depends on the model, L, the number of chains and
+ * how well the run's iterations have measured its weights so far. */
+int muca_tile_chains(const muca_run *run, int32_t *chains);
 int muca_get_lnw(const muca_run *run, double *h_lnw, int32_t n_bins);
 int muca_get_last_hist(const muca_run *run, uint64_t *h_hist, int32_t n_bins);
 int muca_get_thresholds(const muca_run *run, uint32_t *h_t, int64_t count);

@@ -3,6 +3,7 @@
 // and a check program builds it on its own (with sanitizers).
 #pragma once
 
+#include <math.h>
 #include <stdint.h>
 
 namespace muca {
@@ -18,6 +19,101 @@ __attribute__((always_inline)) constexpr void for_segments(int32_t total, int32_
         f(total - left, n);
         left -= n;
     }
+}
+
+// ---------------------------------------------------------------------------
+// One wavefront per chain, or 1 to 4 lanes per chain
+// ---------------------------------------------------------------------------
+// How well the log weights of a run are known: the mean, over the links
+// between bins that its iterations have measured, of the statistical error
+// P^-1/2 of a link's ln ratio (P, the link's accumulated statistics, is that
+// ratio's inverse variance), at most 1 each.  0 for weights without
+// measurements: flat ones, or a caller's.
+inline double weights_noise(int n, const double *P)
+{
+    double sum = 0.0;
+    int links = 0;
+    for (int b = 0; b < n; ++b)
+        if (P[b] > 0.0) {
+            sum += P[b] > 1.0 ? 1.0 / sqrt(P[b]) : 1.0;
+            ++links;
+        }
+    return links ? sum / links : 0.0;
+}
+
+// A tile's passes grow with the noise of the weights (its thresholds then
+// differ from bin to bin), the time of 1 to 4 lanes per chain does not: the
+// two meet at fewer chains during the first iterations.  The classes of noise
+// by which the lines below are drawn: 0 settled (from the sixth to tenth
+// iteration of some ten to forty sweeps, the second of a few hundred), 1 in
+// between, 2 the first iterations.  Thresholds of multimagnetic runs are set
+// by beta as much as by the weights: their passes hardly change.
+enum { kSettled = 0, kBetween = 1, kRough = 2 };
+inline int weights_class(int model, double noise) // MUCA_ISING, MUCA_POTTS, MUCA_MUMA
+{
+    if (model == 0)
+        return noise < 0.05 ? kSettled : noise < 0.075 ? kBetween : kRough;
+    return model == 1 && noise >= 0.09 ? kRough : kSettled;
+}
+
+// Most chains of a run that takes the one-wavefront-per-chain kernel by
+// default.  Its time goes by rounds of 4096 chains, sixteen on each of 256
+// CUs: a table of 82 KB or more leaves room for one workgroup per CU, and so
+// do the 100 scalar registers of 1024 threads.  That of 1 to 4 lanes per
+// chain hardly changes up to 16384 chains, where four lanes give every SIMD a
+// wavefront.  So the lines lie at ends of rounds, or where a round begun
+// costs less than a full one.  Measured, time of the best of 1, 2 and 4 lanes
+// over that of one wavefront per chain, by the chains of a run (10 to 40
+// sweeps per iteration):
+//         second iteration           settled weights
+//           4096  4160  8192         4160  6144  8192  8256 10240 12288
+//   Ising
+//     64    2.07  1.15  0.92         1.82  1.79  1.55  1.25  1.12  1.02
+//     48    1.54  0.90  0.85         1.42  1.18  1.07  0.97  0.88  0.86
+//     32    1.29  0.85  0.93         1.32  1.24  1.18  0.93  0.91  0.82
+//     24    1.43  0.92  0.75         1.26  1.07  1.09  0.89  0.84  0.82
+//     16    1.27  0.91  0.97         1.39  1.31  1.28  0.99  0.94  0.93
+//     8     1.33  1.04  0.97         1.41  1.19  1.24  1.09  0.96  0.97
+//   Potts
+//     48    2.43  1.37  1.22         1.79  1.75  1.71  1.24  1.18  1.13
+//     32    1.62  0.94  1.03         1.55  1.43  1.36  1.03  0.98  0.92
+//     24    1.63  0.94  0.75         1.21  1.07  1.07  0.82  0.79  0.71
+//     16    1.26  0.93  0.84         1.56  1.39  1.38  1.09  1.03  0.98
+//     8     1.41  1.00  0.93         1.32  1.18  1.14  1.00  0.88  0.87
+//   Ising in between, one iteration each: L = 64 1.07 to 1.12 at 6144 and
+//     0.93 to 1.32 at 8192, L = 48 0.84 to 1.26 at 8192, L = 32 0.97 to 1.13 at 8192, L = 24 1.03 to 1.18 at 6144 and 0.79
+//     to 0.95 at 8192, L = 16 1.08 to 1.18 at 8192
+//   Potts L = 48, second iteration: 0.93 at 8256, 0.90 at 12288
+//   MUMA, second iteration and settled: L = 64 (staged) 1.34 and 1.48 at
+//     20480, L = 48 1.00 and 1.11 at 20480, L = 32 1.04 and 1.16 at 20480,
+//     L = 24 1.01 and 1.10 at 16384, 0.91 and 0.97 at 16896, L = 16 1.15 and
+//     1.06 at 14336, L = 8 1.65 and 1.17 at 12288
+//   L = 4, launches of 10 and 100 sweeps, against four lanes: Ising at 4096
+//     1.01 and 1.31, MUMA at 4096 1.21 and 1.93, Potts at 1536 1.00 and 1.39,
+//     at 2048 0.90 and 1.39, at 4096 0.83 and 0.96
+//   L = 64 with the table in global memory, whose latency few lanes per chain
+//     hide worse, second iteration and settled: Ising 1.13 and 1.93 at 8192,
+//     0.82 and 1.47 at 12288, 0.79 and 0.96 at 16384, Potts 1.21 and 1.70 at
+//     12288, 0.91 and 1.29 at 16384, 0.95 and 1.42 at 24576, MUMA 1.31 and
+//     1.35 at 40960
+// No line of a lattice that has 16 lanes per chain by default (all but Potts
+// of L = 4, 8 and 24) lies below the 4096 chains up to which it has them.
+inline long tile_max_chains(int model, int L, bool staged, int weights)
+{
+    const int row = L >= 64 ? (staged ? 1 : 0) : L >= 48 ? 2 : L >= 32 ? 3 : L >= 24 ? 4 : L >= 16 ? 5 : L >= 8 ? 6 : 7;
+    // [64 with the table in global memory, 64, 48, 32, 24, 16, 8, 4]
+    constexpr int lines[3][3][8] = {
+        {{12288, 10240, 8192, 8192, 8192, 8192, 8192, 4096},
+         {8192, 6144, 8192, 8192, 6144, 8192, 8192, 4096},
+         {8192, 4096, 4096, 4096, 4096, 4096, 4096, 4096}},
+        {{24576, 12288, 12288, 8192, 6144, 8192, 8192, 1536},
+         {24576, 12288, 12288, 8192, 6144, 8192, 8192, 1536},
+         {12288, 12288, 8192, 4096, 4096, 4096, 4096, 1536}},
+        {{40960, 20480, 20480, 20480, 16384, 14336, 12288, 4096},
+         {40960, 20480, 20480, 20480, 16384, 14336, 12288, 4096},
+         {40960, 20480, 20480, 20480, 16384, 14336, 12288, 4096}},
+    };
+    return lines[model][weights][row];
 }
 
 } // namespace muca

@@ -4,14 +4,19 @@
 //
 // Input, whitespace-separated, one case after another:
 //   segments <total> <at_most>
+//   noise <n> P[n]
+//   line <model> <L> <staged> <noise>
 // Output: one line per case:
 //   segments: number of segments, their sum, shortest, longest, and the
 //     sweeps before the last one (it stops at 10^7 segments)
+//   noise: weights_noise
+//   line: weights_class and tile_max_chains
 #include <algorithm>
 #include <cinttypes>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <vector>
 
 #include "launch_rules.h"
 
@@ -31,6 +36,14 @@ long long get_int()
     if (std::fscanf(in, "%lld", &v) != 1)
         fail("integer");
     return v;
+}
+
+double get_double()
+{
+    char tok[64];
+    if (std::fscanf(in, "%63s", tok) != 1)
+        fail("double");
+    return std::strtod(tok, nullptr);
 }
 
 } // namespace
@@ -59,6 +72,19 @@ int main(int argc, char **argv)
             });
             std::printf("%" PRId64 " %" PRId64 " %" PRId64 " %" PRId64 " %" PRId64 "\n", k, sum, k ? shortest : 0,
                         longest, before);
+        } else if (!std::strcmp(kind, "noise")) {
+            const int n = (int)get_int();
+            if (n < 0 || n > (1 << 20))
+                fail("length");
+            std::vector<double> P((size_t)n);
+            for (double &p : P)
+                p = get_double();
+            std::printf("%.17g\n", muca::weights_noise(n, P.data()));
+        } else if (!std::strcmp(kind, "line")) {
+            const int model = (int)get_int(), L = (int)get_int();
+            const bool staged = get_int() != 0;
+            const int weights = muca::weights_class(model, get_double());
+            std::printf("%d %ld\n", weights, muca::tile_max_chains(model, L, staged, weights));
         } else {
             fail(kind);
         }

@@ -86,43 +86,6 @@ static size_t align256(size_t x) { return (x + 255u) & ~(size_t)255u; }
 // ---------------------------------------------------------------------------
 // Geometry of a configuration
 // ---------------------------------------------------------------------------
-// Most chains of a run that takes the one-wavefront-per-chain kernels by
-// default.  Their rate stops growing once every SIMD has four wavefronts
-// (4096 chains); that of 1 to 4 lanes per chain grows until the lanes fill
-// the chip.  Where the two meet depends on the model (passes per tile and
-// their cost) and on the lattice (rows per tile; lanes without a site at
-// L = 24 and 48; launch costs at the smallest).  Measured, a wavefront's rate
-// over the best of 1, 2 and 4 lanes per chain, launches of 6 to 10 sweeps:
-//                   8192   12288   16384   24576 chains
-//   Ising L = 64    1.26    0.90    0.67    0.64
-//           L = 32  1.17    0.81    0.66    0.47
-//           L = 24  1.12    0.78    0.61    0.45
-//           L = 16  1.44    1.02    0.83    0.60
-//           L = 8   0.98    0.78    0.64    0.49   (6144: 1.17)
-//           L = 4   (3072: 0.98, 4096: 0.91, 6144: 0.64; 100 sweeps at 4096: 1.32)
-//   Potts L = 48    1.44    1.01    0.81    0.85
-//           L = 32  1.22    0.88    0.67    0.70
-//           L = 24  1.01    0.68    0.54    0.55
-//           L = 16  1.40    1.06    0.81    0.82
-//           L = 8   1.15    0.87    0.72    0.62
-//   MUMA  L = 48    2.10    1.42    1.11    0.94
-//           L = 32  2.24    1.54    1.17    1.00
-//           L = 24  2.04    1.40    1.11    0.80
-//           L = 16  1.68    1.22    0.98    0.81
-//           L = 8   1.26    0.99    0.83    0.65
-// With the table of L = 64 in global memory, whose latency few lanes per
-// chain hide worse, MUMA 1.94 at 24576 chains and 1.46 at 32768, Potts 1.15
-// and 0.89: twice as far.  The lines lie where the ratio is still about 1.08.
-static long tile_max_chains(int model, int L, bool staged)
-{
-    const int row = L >= 64 ? 0 : L >= 48 ? 1 : L >= 32 ? 2 : L >= 24 ? 3 : L >= 16 ? 4 : L >= 8 ? 5 : 6;
-    static const int ising[7] = {10240, 10240, 9216, 8704, 11520, 6912, 4096};
-    static const int potts[7] = {12288, 11520, 9728, 6144, 11776, 9216, 4096};
-    static const int muma[7] = {20480, 17408, 20480, 16896, 14336, 10752, 4096};
-    const long n = (model == kIsing ? ising : model == kPotts ? potts : muma)[row];
-    return L == 64 && !staged ? 2 * n : n;
-}
-
 static int bin_step(int model) { return model == kIsing ? 4 : (model == kPotts ? 1 : 2); }
 
 static int n_cols_of(int model) { return model == kIsing ? 5 : (model == kPotts ? 9 : 10); }
@@ -209,9 +172,6 @@ int muca_geometry(const muca_config *c, Geometry *g)
     if (hist_lds > 64u * 1024u)
         return muca_fail(MUCA_E_ARG, "%d bins exceed the LDS histogram", g->n_bins);
     g->table_in_lds = c->table_in_lds == 1 || (c->table_in_lds < 0 && g->lds_bytes <= 160u * 1024u);
-    if (c->lanes_per_chain == 16 ||
-        (c->lanes_per_chain == 0 && (long)g->c_pad <= tile_max_chains(g->model, c->L, g->table_in_lds)))
-        g->tile_chains = 16;
     if (g->cpb > 256 && !g->table_in_lds)
         return muca_fail(MUCA_E_ARG, "blocks of %d threads need the threshold table staged in LDS", g->cpb);
     // workspace carve
@@ -332,8 +292,10 @@ int muca_rebuild_thresholds(muca_run *r)
         const int rc = muca_polymer_build(r);
         if (rc || r->T.empty())
             return rc;
-    } else
+    } else {
         muca_lattice_thresholds(r->g.model, r->cfg.beta, r->g.n_bins, r->g.n_cols, r->lnW.data(), r->T.data());
+        r->weights = weights_class(r->g.model, weights_noise(r->g.n_bins, r->P.data()));
+    }
     return muca_upload_thresholds(r);
 }
 
@@ -379,7 +341,7 @@ try {
                 g.cpb = 512;
         }
     }
-    if (g.tile_chains) {
+    if (g.model != kPolymer) {
         // as many workgroups as there are CUs, down to one wavefront per SIMD
         int dev = 0, cus = 256;
         if (hipGetDevice(&dev) == hipSuccess)
@@ -476,6 +438,15 @@ try {
 }
 MUCA_ABI_CATCH
 
+// Whether the run's next plain launch takes one wavefront per chain.
+static bool takes_tiles(const muca_run *r)
+{
+    const Geometry &g = r->g;
+    if (g.model == kPolymer || r->cfg.lanes_per_chain != 0)
+        return g.model != kPolymer && r->cfg.lanes_per_chain == 16;
+    return (long)g.c_pad <= tile_max_chains(g.model, g.L, g.table_in_lds, r->weights);
+}
+
 int muca_enqueue_sweeps(muca_run *r, int64_t sweeps, bool record, hipStream_t s, unsigned long long *em,
                         unsigned long long *hist_blocks)
 {
@@ -510,7 +481,7 @@ int muca_enqueue_sweeps(muca_run *r, int64_t sweeps, bool record, hipStream_t s,
         a.hist_block_chains = g.cpb / g.lpc;
         a.layout = g.layout;
         a.tile_chains = g.tile_chains;
-        if (g.tile_chains)
+        if (takes_tiles(r))
             HIP_OR_POISON(r, launch_lattice_tiles(g.model, g.L, a, s));
         else
             HIP_OR_POISON(r, launch_lattice_sweeps(g.model, g.L, g.layout, g.lpc, g.cpb, a, s));
@@ -596,6 +567,18 @@ try {
         *n_blocks = (int32_t)(((int64_t)g.c_pad * g.lpc) / g.cpb);
     if (chains_per_block)
         *chains_per_block = g.cpb / g.lpc;
+    return MUCA_OK;
+}
+MUCA_ABI_CATCH
+
+extern "C" int muca_tile_chains(const muca_run *r, int32_t *chains)
+try {
+    int rc = check_run(r);
+    if (rc)
+        return rc;
+    if (!chains)
+        return muca_fail(MUCA_E_ARG, "null argument");
+    *chains = takes_tiles(r) ? r->g.tile_chains : 0;
     return MUCA_OK;
 }
 MUCA_ABI_CATCH
@@ -1162,6 +1145,8 @@ try {
     r->lnW = lnW;
     r->lnR = lnR;
     r->P = P;
+    if (r->g.model != kPolymer)
+        r->weights = weights_class(r->g.model, weights_noise(r->g.n_bins, r->P.data()));
     r->mask = mask;
     if (!r->T.empty()) // else the table is in the workspace just restored
         std::copy(T.begin(), T.end(), r->T.begin());

@@ -9,6 +9,7 @@
 
 #include "../../include/muca.h"
 #include "host_math.h"
+#include "launch_rules.h"
 
 namespace muca {
 
@@ -21,7 +22,7 @@ struct Geometry {
     int c_pad;           // chains rounded up to a multiple of 64
     int cpb;             // threads per block
     int lpc;             // lanes per chain
-    int tile_chains;     // > 0: one wavefront per chain, this many chains per workgroup
+    int tile_chains;     // chains per workgroup of the one-wavefront-per-chain kernel
     bool table_in_lds;
     size_t lds_bytes;    // LDS of one lattice block with the table staged
     size_t off_words, off_bins, off_values, off_table, off_hist, off_energy;
@@ -80,6 +81,7 @@ struct muca_run {
     int64_t iteration = 0;
     int64_t pending = 0;           // recorded sweeps since the last merge
     bool have_last = false;
+    int weights = muca::kSettled;  // lattice: class of the weights' noise
     bool poisoned = false;
     // pinned host staging: the histogram and accepted-move count read back at
     // a merge, and its device-side address

@@ -97,6 +97,7 @@ def _load():
         "muca_batch_tune": (ctypes.c_int, [vp, i64, vp, P(muca_batch_tuning)]),
         "muca_autotune": (ctypes.c_int, [P(muca_config), vp, u64, i64, vp, P(muca_config), P(ctypes.c_double)]),
         "muca_sizes": (ctypes.c_int, [vp, P(i32), P(i32), P(i32)]),
+        "muca_tile_chains": (ctypes.c_int, [vp, P(i32)]),
         "muca_get_lnw": (ctypes.c_int, [vp, vp, i32]),
         "muca_get_last_hist": (ctypes.c_int, [vp, vp, i32]),
         "muca_get_thresholds": (ctypes.c_int, [vp, vp, i64]),
@@ -123,7 +124,8 @@ EXPORTED = ("muca_config_default", "muca_workspace_bytes", "muca_init", "muca_ru
             "muca_em_shape", "muca_run_iteration_em", "muca_reweight_em",
             "muca_batch_workspace_bytes",
             "muca_batch_create", "muca_batch_run_iteration", "muca_batch_free",
-            "muca_batch_run_iteration_noalloc", "muca_batch_tune", "muca_autotune", "muca_sizes", "muca_get_lnw", "muca_get_last_hist",
+            "muca_batch_run_iteration_noalloc", "muca_batch_tune", "muca_autotune", "muca_sizes", "muca_tile_chains",
+            "muca_get_lnw", "muca_get_last_hist",
             "muca_get_thresholds", "muca_get_chain_state", "muca_set_lnw", "muca_set_thresholds",
             "muca_checkpoint", "muca_restore", "muca_free", "muca_last_error")
 
@@ -188,6 +190,13 @@ class Run:
     # -- the hot path ------------------------------------------------------
     def run_iteration(self, sweeps: int, stream=None):
         _check(LIB.muca_run_iteration(self.handle, int(sweeps), _stream_handle(stream or self.stream)))
+
+    def tile_chains(self) -> int:
+        """Chains per workgroup if the next launch takes one wavefront per
+        chain, else 0."""
+        n = ctypes.c_int32()
+        _check(LIB.muca_tile_chains(self.handle, ctypes.byref(n)))
+        return n.value
 
     def blocks_shape(self) -> tuple[int, int]:
         """(n_blocks, chains_per_block) of the per-block histograms."""

@@ -5,6 +5,7 @@ import os
 import shutil
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -40,3 +41,50 @@ def test_segments_cover_every_sweep_count(rules, total, at_most):
     assert longest == min(total, at_most)
     assert shortest == (((total - 1) % at_most + 1) if total else 0)
     assert before == (total - shortest if total else 0)
+
+
+def test_noise_of_the_weights(rules):
+    """The mean error P^-1/2 of the measured links, at most 1 each."""
+    rng = np.random.default_rng(5)
+    for n in (0, 1, 2, 65, 4097):
+        P = np.exp(rng.uniform(-5, 15, n)) * (rng.random(n) < 0.7)
+        want = np.minimum(1.0, P[P > 0] ** -0.5).mean() if (P > 0).any() else 0.0
+        got = rules(f"noise {n} " + " ".join(float(p).hex() for p in P))[0][0]
+        assert abs(got - want) <= 1e-12 * max(1.0, want), n
+
+
+# chain counts that four lanes per chain take as fast or faster: (model, L,
+# staged table, noise of the weights, chains)
+FEW = [(0, 64, 1, 0.02, 12288), (0, 64, 1, 0.09, 4160), (0, 64, 1, 0.09, 8192), (0, 48, 1, 0.02, 8256),
+       (0, 48, 1, 0.02, 10240), (0, 32, 1, 0.02, 8256), (0, 32, 1, 0.02, 9216), (0, 32, 1, 0.09, 4160),
+       (0, 24, 1, 0.02, 8256), (0, 24, 1, 0.02, 8704), (0, 24, 1, 0.1, 8192), (0, 16, 1, 0.02, 8256),
+       (0, 16, 1, 0.1, 4160), (0, 8, 1, 0.1, 8192), (0, 64, 0, 0.09, 10240), (0, 64, 0, 0.02, 16384),
+       (0, 64, 1, 0.06, 8192), (0, 24, 1, 0.06, 8192), (1, 32, 1, 0.02, 9728),
+       (1, 32, 1, 0.19, 4160), (1, 48, 1, 0.19, 8256), (1, 24, 1, 0.2, 6144), (1, 16, 1, 0.19, 8192),
+       (1, 8, 1, 0.02, 8256), (1, 8, 1, 0.19, 6144), (1, 4, 1, 0.3, 2048), (1, 4, 1, 0.01, 4096),
+       (1, 64, 0, 0.16, 16384), (2, 24, 1, 0.02, 16896), (2, 16, 1, 0.02, 16384)]
+# and that one wavefront per chain takes faster
+WAVE = [(0, 64, 1, 0.04, 8192), (0, 64, 1, 0.0, 8192), (0, 64, 1, 0.09, 4096), (0, 32, 1, 0.04, 8192),
+        (0, 32, 1, 0.1, 4096), (0, 32, 1, 0.06, 8192), (0, 64, 1, 0.06, 6144), (1, 64, 1, 0.2, 12288),
+        (0, 8, 1, 0.01, 8192), (1, 48, 1, 0.07, 12288), (1, 48, 1, 0.2, 8192),
+        (1, 64, 0, 0.04, 24576), (1, 64, 0, 0.2, 12288), (1, 16, 1, 0.05, 8192), (1, 4, 1, 0.4, 1024),
+        (2, 64, 0, 0.3, 40960), (2, 32, 1, 0.3, 20480), (2, 16, 1, 0.03, 14336), (2, 8, 1, 0.05, 12288)]
+
+
+def test_default_lines(rules):
+    got = rules(*(f"line {m} {L} {s} {noise}" for m, L, s, noise, _ in FEW + WAVE))
+    for (m, L, s, noise, chains), (_, line) in zip(FEW + WAVE, got):
+        assert (chains <= line) == ((m, L, s, noise, chains) in WAVE), (m, L, s, noise, chains, line)
+
+
+def test_no_line_below_the_chains_that_take_16_lanes(rules):
+    """Lattices whose lanes per chain are 16 by default up to 4096 chains
+    have one wavefront per chain there, whatever the weights; only Potts
+    lattices of L not a multiple of 16 (4 lanes) may lie lower."""
+    cases = [(m, L, s, noise) for m in (0, 1, 2) for L in (4, 8, 16, 24, 32, 48, 64) for s in (0, 1)
+             for noise in (0.0, 0.06, 1.0)]
+    lines = {c: v[1] for c, v in zip(cases, rules(*("line %d %d %d %g" % c for c in cases)))}
+    for (m, L, s, noise), line in lines.items():
+        if m != 1 or L % 16 == 0:
+            assert line >= 4096, (m, L, s, noise)
+        assert line <= lines[(m, L, s, 0.0)]
