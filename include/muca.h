@@ -358,9 +358,10 @@ int muca_batch_tune(muca_run *run, int64_t probe_sweeps, void *stream, muca_batc
 /* Autotuner: times `sweeps` sweeps of every compiled variant of cfg (layout,
  * lanes per chain, chains per block, threshold table in LDS or global) in
  * the caller's workspace d_ws and returns the fastest in *best (time per
- * sweep in *best_ms_per_sweep, -1 when taken from the cache).  A candidate
- * whose histogram, spins or bins differ from the first candidate's is
- * rejected.  With MUCA_AUTOTUNE_CACHE set to a file path, results are read
+ * sweep in *best_ms_per_sweep, -1 when taken from the cache).  Lattice
+ * candidates run on weights about as uneven as those of a run in progress.
+ * A candidate whose histogram, spins or bins differ from the first
+ * candidate's is rejected.  With MUCA_AUTOTUNE_CACHE set to a file path, results are read
  * from / written to that JSON file, keyed by GPU architecture and shape.
  * The workspace must hold the largest candidate (layout BYTE for Ising). */
 int muca_autotune(const muca_config *cfg, void *d_ws, uint64_t ws_bytes, int64_t sweeps, void *stream,

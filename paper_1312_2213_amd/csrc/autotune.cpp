@@ -2,8 +2,8 @@
 // block and threshold-table placement of a configuration by timing short
 // runs of every compiled candidate on the device.
 //
-// Every candidate runs the same chains (same seed, same sweeps) from the
-// same initial state; its merged histogram, final spins and bins are hashed
+// Every candidate runs the same chains (same seed, same sweeps, for lattices
+// the same uneven weights) from the same initial state; its merged histogram, final spins and bins are hashed
 // and compared with the first candidate's.  A candidate whose results differ
 // is rejected (and reported), so the choice can never change the physics.
 // Results are cached in a small JSON file (MUCA_AUTOTUNE_CACHE) keyed by the
@@ -147,18 +147,17 @@ try {
         else
             layouts = {MUCA_LAYOUT_BIT, MUCA_LAYOUT_BYTE};
         for (int lay : layouts)
-            for (int lpc : {1, 2, 4, 16})
-                for (int threads : {64, 256, 512})
-                    for (int tl : {0, 1}) {
-                        muca_config c = *cfg;
-                        c.layout = lay;
-                        c.lanes_per_chain = lpc;
-                        c.chains_per_block = threads / lpc > 0 ? threads / lpc : 1;
-                        if (c.chains_per_block * lpc != threads || (threads > 256 && tl == 0))
-                            continue;
-                        c.table_in_lds = tl;
-                        cands.push_back(c);
-                    }
+            for (const LaunchShape &shape : kTunedShapes)
+                for (int tl : {0, 1}) {
+                    muca_config c = *cfg;
+                    c.layout = lay;
+                    c.lanes_per_chain = shape.lanes;
+                    c.chains_per_block = shape.threads / shape.lanes;
+                    if (shape.threads > 256 && tl == 0)
+                        continue;
+                    c.table_in_lds = tl;
+                    cands.push_back(c);
+                }
     } else {
         for (int cpb : {1, 2, 4}) {
             muca_config c = *cfg;
@@ -192,8 +191,16 @@ try {
             muca_free(r);
             continue;
         }
+        int rc = MUCA_OK;
+        if (lattice) { // weights like those of a run in progress
+            std::vector<double> lnw(r->g.n_bins);
+            for (int b = 0; b < r->g.n_bins; ++b)
+                lnw[b] = probe_lnw(b);
+            rc = muca_set_lnw(r, lnw.data(), r->g.n_bins);
+        }
         // one untimed launch loads the code, then the timed one
-        int rc = muca_thermalize(r, 1, stream);
+        if (rc == MUCA_OK)
+            rc = muca_thermalize(r, 1, stream);
         (void)hipEventRecord(e0, s);
         if (rc == MUCA_OK)
             rc = muca_run_iteration(r, sweeps, stream);

@@ -81,8 +81,9 @@ inline int weights_class(int model, double noise) // MUCA_ISING, MUCA_POTTS, MUC
 //     16    1.26  0.93  0.84         1.56  1.39  1.38  1.09  1.03  0.98
 //     8     1.41  1.00  0.93         1.32  1.18  1.14  1.00  0.88  0.87
 //   Ising in between, one iteration each: L = 64 1.07 to 1.12 at 6144 and
-//     0.93 to 1.32 at 8192, L = 48 0.84 to 1.26 at 8192, L = 32 0.97 to 1.13 at 8192, L = 24 1.03 to 1.18 at 6144 and 0.79
-//     to 0.95 at 8192, L = 16 1.08 to 1.18 at 8192
+//     0.93 to 1.32 at 8192, L = 48 0.84 to 1.26 at 8192, L = 32 0.97 to 1.13
+//     at 8192, L = 24 1.03 to 1.18 at 6144 and 0.79 to 0.95 at 8192, L = 16
+//     1.08 to 1.18 at 8192
 //   Potts L = 48, second iteration: 0.93 at 8256, 0.90 at 12288
 //   MUMA, second iteration and settled: L = 64 (staged) 1.34 and 1.48 at
 //     20480, L = 48 1.00 and 1.11 at 20480, L = 32 1.04 and 1.16 at 20480,
@@ -114,6 +115,46 @@ inline long tile_max_chains(int model, int L, bool staged, int weights)
          {40960, 20480, 20480, 20480, 16384, 14336, 12288, 4096}},
     };
     return lines[model][weights][row];
+}
+
+// Chains per workgroup of the one-wavefront-per-chain kernel, at most
+// `most`: as many workgroups as there are CUs, down to one wavefront per SIMD.
+inline int default_tile_chains(int most, long n_chains, int cus)
+{
+    int n = most < 16 ? most : 16;
+    while (n > 4 && n_chains <= (long)cus * (n / 2))
+        n /= 2;
+    return n;
+}
+
+// ---------------------------------------------------------------------------
+// What the autotuners time
+// ---------------------------------------------------------------------------
+// Lanes per chain and threads per block.  Sixteen lanes are a wavefront per
+// chain: workgroups of 4, 8 and 16 chains, the ones that are taken by default
+// (2048 chains of Potts q = 8, L = 48, settled weights: 41 cycles per site at
+// 8, 54 and 70 at 16 and 4 with a staged table).
+struct LaunchShape {
+    int lanes, threads;
+};
+constexpr LaunchShape kTunedShapes[] = {{1, 64}, {1, 256}, {1, 512}, {2, 64},  {2, 256},  {2, 512},
+                                        {4, 64}, {4, 256}, {4, 512}, {16, 64}, {16, 128}, {16, 256}};
+
+// Log weights on which candidates are timed: independent and uniform in
+// (-0.15, 0.15).  On flat weights a tile takes the fewest passes it can, and
+// one wavefront per chain would be preferred where it is the slower one as
+// soon as the weights move.  Cycles per site, flat / these / a run's twelfth
+// to thirtieth iteration of ten sweeps: Ising L = 64, 8192 chains 41.4 / 65.0
+// / 71.8 to 66.6, Ising L = 32, 4096 chains 23.7 / 43.0 / 50.8 to 47.9, Potts
+// L = 48, 4096 chains 43.0 / 57.5 / 54.9 to 53.6 (four lanes: 101, 107, 170,
+// whatever the weights).
+inline double probe_lnw(int bin)
+{
+    uint64_t z = ((uint64_t)bin + 1) * 0x9E3779B97F4A7C15ull; // splitmix64
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    return 0.3 * ((double)(z >> 11) * 0x1p-53 - 0.5);
 }
 
 } // namespace muca

@@ -6,11 +6,17 @@
 //   segments <total> <at_most>
 //   noise <n> P[n]
 //   line <model> <L> <staged> <noise>
+//   tile <most> <n_chains> <cus>
+//   shapes
+//   probe <bins>
 // Output: one line per case:
 //   segments: number of segments, their sum, shortest, longest, and the
 //     sweeps before the last one (it stops at 10^7 segments)
 //   noise: weights_noise
 //   line: weights_class and tile_max_chains
+//   tile: default_tile_chains
+//   shapes: lanes and threads of every entry of kTunedShapes
+//   probe: probe_lnw of every bin
 #include <algorithm>
 #include <cinttypes>
 #include <cstdio>
@@ -85,6 +91,19 @@ int main(int argc, char **argv)
             const bool staged = get_int() != 0;
             const int weights = muca::weights_class(model, get_double());
             std::printf("%d %ld\n", weights, muca::tile_max_chains(model, L, staged, weights));
+        } else if (!std::strcmp(kind, "tile")) {
+            const int most = (int)get_int();
+            const long n = (long)get_int();
+            std::printf("%d\n", muca::default_tile_chains(most, n, (int)get_int()));
+        } else if (!std::strcmp(kind, "shapes")) {
+            for (const muca::LaunchShape &s : muca::kTunedShapes)
+                std::printf("%d %d ", s.lanes, s.threads);
+            std::printf("\n");
+        } else if (!std::strcmp(kind, "probe")) {
+            const int n = (int)get_int();
+            for (int b = 0; b < n; ++b)
+                std::printf("%.17g ", muca::probe_lnw(b));
+            std::printf("\n");
         } else {
             fail(kind);
         }

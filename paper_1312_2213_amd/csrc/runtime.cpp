@@ -342,13 +342,12 @@ try {
         }
     }
     if (g.model != kPolymer) {
-        // as many workgroups as there are CUs, down to one wavefront per SIMD
         int dev = 0, cus = 256;
         if (hipGetDevice(&dev) == hipSuccess)
             (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        g.tile_chains = std::min(16, g.cpb / g.lpc);
-        while (c->chains_per_block == 0 && g.tile_chains > 4 && (long)c->n_chains <= (long)cus * (g.tile_chains / 2))
-            g.tile_chains /= 2;
+        // a caller's blocks are kept, up to sixteen chains
+        g.tile_chains = c->chains_per_block ? std::min(16, g.cpb / g.lpc)
+                                            : default_tile_chains(g.cpb / g.lpc, c->n_chains, cus);
     }
     RoctxRange range("muca_init");
     muca_run *r = new muca_run();

@@ -88,3 +88,26 @@ def test_no_line_below_the_chains_that_take_16_lanes(rules):
         if m != 1 or L % 16 == 0:
             assert line >= 4096, (m, L, s, noise)
         assert line <= lines[(m, L, s, 0.0)]
+
+
+def test_autotuner_times_every_default_workgroup(rules):
+    """The workgroups that a run takes by default are among the autotuner's
+    candidates, and no launch is timed twice."""
+    flat = [int(v) for v in rules("shapes")[0]]
+    shapes = list(zip(flat[::2], flat[1::2]))
+    launches = [(l, t) if l < 16 else (l, min(16, t // l)) for l, t in shapes]
+    assert len(set(launches)) == len(launches), launches
+    chains = [1, 64, 1024, 1025, 1536, 2048, 2049, 4096, 20480]
+    for n, (tile,) in zip(chains, rules(*(f"tile 16 {n} 256" for n in chains))):
+        assert tile == (4 if n <= 1024 else 8 if n <= 2048 else 16), n
+        assert (16, 16 * tile) in shapes, n
+    assert {(l, 256) for l in (1, 2, 4)} <= set(shapes)
+    assert [v for v, in rules("tile 4 4096 256", "tile 64 4096 256")] == [4, 16]
+
+
+def test_probe_weights(rules):
+    """Independent and uniform in (-0.15, 0.15), the same on every call."""
+    a, b = np.array(rules("probe 8193", "probe 8193"))
+    assert np.array_equal(a, b) and np.all(np.abs(a) < 0.15)
+    assert abs(a.mean()) < 5 * 0.15 / np.sqrt(3 * len(a)) and abs(a.std() - 0.15 / np.sqrt(3)) < 0.003
+    assert abs(np.corrcoef(a[:-1], a[1:])[0, 1]) < 0.06
