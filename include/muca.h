@@ -333,8 +333,8 @@ int muca_batch_run_iteration_noalloc(muca_run *const *runs, int32_t n_runs, cons
  * change.  A candidate whose first 16 chains end in a different state than
  * the first candidate's is rejected (counted in `rejected`).  Results are
  * read from / written to the JSON file named by MUCA_AUTOTUNE_CACHE (key:
- * architecture and class; an item's time does not depend on the number of
- * chains).  The run keeps the measurement: a batched launch with
+ * architecture, class, the kernels' revision, and the number of chains up to
+ * sixteen, beyond which an item's time does not depend on it).  The run keeps the measurement: a batched launch with
  * lanes_per_chain 0 (muca_batch_create, muca_batch_run_iteration_noalloc)
  * whose runs are all tuned takes per run the table placement of the faster
  * item, and for the round the lanes per chain that give the shorter
@@ -362,7 +362,8 @@ int muca_batch_tune(muca_run *run, int64_t probe_sweeps, void *stream, muca_batc
  * candidates run on weights about as uneven as those of a run in progress.
  * A candidate whose histogram, spins or bins differ from the first
  * candidate's is rejected.  With MUCA_AUTOTUNE_CACHE set to a file path, results are read
- * from / written to that JSON file, keyed by GPU architecture and shape.
+ * from / written to that JSON file, keyed by GPU architecture, shape and the
+ * kernels' revision.
  * The workspace must hold the largest candidate (layout BYTE for Ising). */
 int muca_autotune(const muca_config *cfg, void *d_ws, uint64_t ws_bytes, int64_t sweeps, void *stream,
                   muca_config *best, double *best_ms_per_sweep);

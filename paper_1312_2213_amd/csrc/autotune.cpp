@@ -7,7 +7,7 @@
 // and compared with the first candidate's.  A candidate whose results differ
 // is rejected (and reported), so the choice can never change the physics.
 // Results are cached in a small JSON file (MUCA_AUTOTUNE_CACHE) keyed by the
-// device architecture and the problem shape.
+// device architecture, the problem shape and the kernels' revision.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -39,7 +39,7 @@ std::string cache_key(const muca_config *c, const char *arch)
 {
     std::ostringstream k;
     k << arch << "/m" << c->model << "/L" << c->L << "/q" << c->q << "/C" << c->n_chains << "/lay" << c->layout
-      << "/N" << c->n_beads;
+      << "/N" << c->n_beads << "/r" << kTunedRevision;
     return k.str();
 }
 

@@ -762,10 +762,14 @@ MUCA_ABI_CATCH
 // threshold table in LDS or in global memory), measured on probe launches of
 // the run's first work item that are undone afterwards.
 // ---------------------------------------------------------------------------
+// The probed item holds the run's chains where it has fewer than sixteen, so
+// their number is part of the key (an item of four lanes per chain runs its
+// padding chains too).
 static std::string batch_cache_key(const muca_run *r, const char *arch)
 {
     char buf[160];
-    std::snprintf(buf, sizeof buf, "batch/%s/m%d/lay%d/L%d/q%d", arch, r->g.model, r->g.layout, r->g.L, r->cfg.q);
+    std::snprintf(buf, sizeof buf, "batch/%s/m%d/lay%d/L%d/q%d/c%d/r%d", arch, r->g.model, r->g.layout, r->g.L,
+                  r->cfg.q, std::min(kTileItemChains, r->cfg.n_chains), kTunedRevision);
     return buf;
 }
 

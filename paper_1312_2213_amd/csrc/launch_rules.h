@@ -140,6 +140,13 @@ struct LaunchShape {
 constexpr LaunchShape kTunedShapes[] = {{1, 64}, {1, 256}, {1, 512}, {2, 64},  {2, 256},  {2, 512},
                                         {4, 64}, {4, 256}, {4, 512}, {16, 64}, {16, 128}, {16, 256}};
 
+// Revision of what they time, part of every key of MUCA_AUTOTUNE_CACHE: an
+// entry is read only by a library whose kernels, candidates and probe weights
+// are the ones that it was measured with.  Raise it when any of them changes.
+// (1, without a mark in the key: 16 lanes were lanes of one wavefront shared
+// by four chains.)
+constexpr int kTunedRevision = 2;
+
 // Log weights on which candidates are timed: independent and uniform in
 // (-0.15, 0.15).  On flat weights a tile takes the fewest passes it can, and
 // one wavefront per chain would be preferred where it is the slower one as
