@@ -362,71 +362,29 @@ static void fill_desc(BatchDesc &d, const muca_run *r, int64_t sweeps, bool tlds
     d.variant = variant_index(tiles ? r->g.model : kind_of(r), l_index(r->g.L), tlds ? 1 : 0);
 }
 
-// Chains of one work item: 64 at four lanes per chain, up to sixteen at one
-// wavefront per chain.
-constexpr int kItemChains = 64, kTileItemChains = 16;
-
-static long items_of(const muca_run *r, int chains) { return (r->cfg.n_chains + chains - 1) / chains; }
-
 // What the planner assumes of one work item of a run: its time with the
 // table placement it takes.  Measured (muca_batch_tune) when every run of the
-// round is tuned, else nominal: cycles per site of a workgroup alone on its
-// CU, about the mean over L of what the kernels measure.
-struct ItemTime {
-    double t[2]; // [four lanes per chain, 64 chains | a wavefront per chain, 16 chains]; < 0: not a candidate
-    int tlds[2];
-};
-
-static ItemTime item_time(const muca_run *r, int64_t sweeps, bool tuned)
+// round is tuned, else nominal.
+static RoundRun round_run(const muca_run *r, int64_t sweeps, bool tuned)
 {
-    ItemTime x;
+    RoundRun x{};
+    x.chains = r->cfg.n_chains;
     for (int o = 0; o < 2; ++o) {
         double best;
         if (tuned) {
             const double g = r->batch_us[o][0], l = r->batch_us[o][1];
-            x.tlds[o] = l >= 0.0 && (g < 0.0 || l < g);
-            best = x.tlds[o] ? l : g;
+            x.table_in_lds[o] = l >= 0.0 && (g < 0.0 || l < g);
+            best = x.table_in_lds[o] ? l : g;
         } else {
-            static const double cycles[3][2] = {{110.0, 34.0}, {180.0, 44.0}, {110.0, 21.0}}; // Ising, Potts, MUMA
-            best = cycles[r->g.model][o] * (double)r->g.n_sites;
-            x.tlds[o] = 1;
+            best = nominal_cycles(r->g.model, r->g.L, o != 0) * (double)r->g.n_sites;
+            x.table_in_lds[o] = true;
         }
+        if (o)
+            best *= tile_slowdown(r->g.model, r->weights);
         x.t[o] = best < 0.0 ? -1.0 : best * (double)sweeps;
     }
     return x;
 }
-
-// Workgroups of 8 and 4 wavefronts leave the CU's issue slots to fewer of
-// them: an item of 8 (4) chains takes this share of the time of one of 16
-// (Potts L = 48: 42, 31 and 23 cycles per site; Ising L = 64: 23, 18 and 13).
-static double tile_share(int chains) { return chains == 16 ? 1.0 : chains == 8 ? 0.75 : 0.55; }
-
-// Estimated length of a round on n_cus slots: all items spread evenly, and no
-// less than the slot that takes two items where they outnumber the slots.
-// Two workgroups of four lanes per chain side by side on a CU do 1.3 times
-// the work of one (Ising L = 32: 357 -> 479e9 attempts/s).
-struct RoundLength {
-    double longest = 0.0, shortest = 0.0, total = 0.0;
-    long items = 0;
-    void add(long k, double t)
-    {
-        longest = std::max(longest, t);
-        shortest = items ? std::min(shortest, t) : t;
-        total += (double)k * t;
-        items += k;
-    }
-    double estimate(int n_cus, double per_cu) const
-    {
-        const double rounds = std::ceil((double)items / (double)n_cus);
-        return std::max(std::max(longest, total / (double)n_cus), rounds * shortest) / per_cu;
-    }
-};
-
-struct RunPlan {
-    ItemTime x;
-    int chains;
-    double cost; // of one item
-};
 
 // Plans one batched round: checks the runs, moves each to stream s, chooses
 // the kind of work item (lpc_fixed, or when 0 the one with the shorter
@@ -436,7 +394,7 @@ struct RunPlan {
 // entries of the caller's; nothing is allocated here, so the entry point that
 // must not allocate can use it.  Returns a muca_status.
 static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int lpc_fixed, int max_runs, int max_items,
-                      int n_cus, int lds_limit, uint8_t *stage, RunPlan *work, hipStream_t s, RoundPlan *out)
+                      int n_cus, int lds_limit, uint8_t *stage, RoundRun *work, hipStream_t s, RoundPlan *out)
 {
     if (n > max_runs)
         return muca_fail(MUCA_E_ARG, "%d runs exceed the batch capacity %d", n, max_runs);
@@ -459,61 +417,24 @@ static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int l
     for (int i = 0; i < n; ++i)
         tuned = tuned && runs[i]->batch_tuned;
     size_t lds4 = 0;
-    RoundLength len4, len16;
-    bool has[2] = {lpc_fixed != 16, lpc_fixed != 4};
     for (int i = 0; i < n; ++i) {
-        ItemTime &x = work[i].x;
-        x = item_time(runs[i], sweeps[i], tuned && lpc_fixed == 0);
-        for (int o = 0; o < 2; ++o) { // a placement in LDS must fit this device
-            x.tlds[o] = x.tlds[o] && runs[i]->g.table_in_lds && runs[i]->g.lds_bytes <= lds_budget;
-            has[o] = has[o] && x.t[o] >= 0.0;
-        }
-        lds4 = std::max(lds4, x.tlds[0] ? runs[i]->g.lds_bytes : (size_t)0);
-        len4.add(items_of(runs[i], kItemChains), x.t[0]);
-        len16.add(items_of(runs[i], kTileItemChains), x.t[1]);
+        work[i] = round_run(runs[i], sweeps[i], tuned && lpc_fixed == 0);
+        for (bool &lds : work[i].table_in_lds) // a placement in LDS must fit this device
+            lds = lds && runs[i]->g.table_in_lds && runs[i]->g.lds_bytes <= lds_budget;
+        lds4 = std::max(lds4, work[i].table_in_lds[0] ? runs[i]->g.lds_bytes : (size_t)0);
     }
     // Work items cover the run's chains only: items made of padding chains
     // alone are not launched (padding chains are never histogrammed or read).
-    if (lpc_fixed == 0) { // the larger items may fit where the smaller ones do not
-        has[1] = has[1] && len16.items <= max_items;
-        has[0] = has[0] || !has[1];
-    }
-    const long n_min = has[1] ? len16.items : len4.items;
-    if (n_min > max_items)
-        return muca_fail(MUCA_E_ARG, "%ld work items exceed the batch capacity %d", n_min, max_items);
-    bool tiles = has[1];
-    if (tiles) {
-        // no item longer than the longest run's in items of 16, 8 or 4
-        // chains; every run takes its largest items within that
-        auto chains_within = [&](int i, double limit) {
-            int c = kTileItemChains;
-            while (c > 4 && work[i].x.t[1] * tile_share(c) > limit * 1.001)
-                c /= 2;
-            return c;
-        };
-        double best = -1.0, limit = len16.longest;
-        for (int c = kTileItemChains; c >= 4; c /= 2) {
-            RoundLength len;
-            for (int i = 0; i < n; ++i) {
-                const int k = chains_within(i, len16.longest * tile_share(c));
-                len.add(items_of(runs[i], k), work[i].x.t[1] * tile_share(k));
-            }
-            const double est = len.estimate(n_cus, 1.0);
-            if (len.items <= max_items && (best < 0.0 || est < 0.999 * best))
-                best = est, limit = len16.longest * tile_share(c);
-        }
-        for (int i = 0; i < n; ++i) {
-            work[i].chains = chains_within(i, limit);
-            work[i].cost = work[i].x.t[1] * tile_share(work[i].chains);
-        }
-        if (has[0] && len4.items <= max_items && len4.estimate(n_cus, lds4 <= 80u * 1024u ? 1.3 : 1.0) < best)
-            tiles = false;
-    }
-    if (!tiles)
-        for (int i = 0; i < n; ++i) {
-            work[i].chains = kItemChains;
-            work[i].cost = work[i].x.t[0];
-        }
+    // Two workgroups of four lanes per chain side by side on a CU do 1.3
+    // times the work of one (Ising L = 32: 357 -> 479e9 attempts/s).
+    long items = 0;
+    const int kind = choose_round(work, n, lpc_fixed != 16, lpc_fixed != 4, max_items, n_cus,
+                                  lds4 <= 80u * 1024u ? 1.3 : 1.0, &items);
+    if (kind == kRoundNoKernel)
+        return muca_fail(MUCA_E_STATE, "no batched kernel kept the results of every run when they were tuned");
+    if (kind == kRoundTooManyItems)
+        return muca_fail(MUCA_E_ARG, "%ld work items exceed the batch capacity %d", items, max_items);
+    const bool tiles = kind == kRoundTiles;
     const StageLayout sl = stage_layout(max_runs, max_items);
     BatchHeader *hdr = (BatchHeader *)stage;
     BatchDesc *desc = (BatchDesc *)(stage + sl.desc_off);
@@ -525,10 +446,10 @@ static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int l
         if (int rc = muca_use_stream(r, s))
             return rc; // the run's last threshold upload may still be queued elsewhere
         const size_t hist = (size_t)lds_hist_words(r->g.n_bins) * 4u;
-        const bool tlds = work[i].x.tlds[tiles ? 1 : 0] != 0;
+        const bool tlds = work[i].table_in_lds[tiles ? 1 : 0];
         lds = std::max(lds, tlds ? r->g.lds_bytes : hist);
-        fill_desc(desc[i], r, sweeps[i], tlds, tiles, work[i].chains);
-        for (int c0 = 0; c0 < r->cfg.n_chains; c0 += work[i].chains)
+        fill_desc(desc[i], r, sweeps[i], tlds, tiles, work[i].item_chains);
+        for (int c0 = 0; c0 < r->cfg.n_chains; c0 += work[i].item_chains)
             hitems[n_items++] = BatchItem{i, c0};
     }
     // longest first (per-item cost); equal costs keep the run and chain order
@@ -540,8 +461,10 @@ static int plan_round(muca_run *const *runs, int n, const int64_t *sweeps, int l
     });
     std::memset(hdr, 0, sizeof *hdr);
     hdr->n_items = n_items;
-    // one resident workgroup per CU when the LDS staging is large, two otherwise
-    const int per_cu = lds > 80u * 1024u ? 1 : 2;
+    // Workgroups that a CU holds at once: one of 1024 threads (its 98 vector
+    // registers leave a SIMD four wavefronts), of 256 threads two unless their
+    // LDS is large.
+    const int per_cu = tiles || lds > 80u * 1024u ? 1 : 2;
     out->grid = std::max(1, std::min(n_items, n_cus * per_cu));
     out->lds = lds;
     out->n_items = n_items;
@@ -603,7 +526,7 @@ try {
         b->poisoned = true;
         return muca_fail(MUCA_E_HIP, "batched launch: %s", hipGetErrorString(e));
     }
-    std::vector<RunPlan> work(n);
+    std::vector<RoundRun> work(n);
     RoundPlan plan;
     if (int rc = plan_round(runs, n, sweeps, b->lpc, b->max_runs, b->max_items, b->n_cus, b->lds_limit, sl.h_buf,
                             work.data(), s, &plan))
@@ -721,7 +644,7 @@ try {
     }
     // host staging on the stack: the copy below is complete before return
     alignas(256) uint8_t stage[kScratchStage];
-    RunPlan work[kScratchRuns];
+    RoundRun work[kScratchRuns];
     RoundPlan plan;
     hipStream_t s = (hipStream_t)stream;
     if (int rc = plan_round(runs, n, sweeps, lanes_per_chain, kScratchRuns, kScratchItems, n_cus, lds_limit, stage,

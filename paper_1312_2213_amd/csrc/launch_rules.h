@@ -164,4 +164,137 @@ inline double probe_lnw(int bin)
     return 0.3 * ((double)(z >> 11) * 0x1p-53 - 0.5);
 }
 
+// ---------------------------------------------------------------------------
+// Work items of a batched round
+// ---------------------------------------------------------------------------
+// Chains of one work item: 64 at four lanes per chain, 16, 8 or 4 at one
+// wavefront per chain.
+constexpr int kItemChains = 64, kTileItemChains = 16;
+
+// Cycles per site of a full item alone on its CU, for runs whose item times
+// were not measured: [Ising, Potts, MUMA][L = 64, 48, 32, 24, 16, 8][four
+// lanes, a wavefront per chain].  Measured at 16384 and 4096 chains, one
+// workgroup on every CU, settled weights (Potts L = 64: table in global
+// memory).
+inline double nominal_cycles(int model, int L, bool tiles)
+{
+    constexpr double cycles[3][6][2] = {
+        {{100, 33}, {106, 42}, {108, 44}, {127, 48}, {128, 44}, {177, 50}},
+        {{196, 57}, {178, 55}, {173, 60}, {188, 78}, {190, 65}, {225, 77}},
+        {{151, 20}, {110, 26}, {111, 24}, {133, 31}, {120, 29}, {181, 36}},
+    };
+    return cycles[model][L >= 64 ? 0 : L >= 48 ? 1 : L >= 32 ? 2 : L >= 24 ? 3 : L >= 16 ? 4 : 5][tiles ? 1 : 0];
+}
+
+// What an item of a wavefront per chain takes of that time with weights of a
+// class (see weights_class): second iteration over settled, Ising 1.3 (L =
+// 64) to 1.8 (L = 24), Potts 1.2 (L = 16) to 1.7 (L = 32).
+inline double tile_slowdown(int model, int weights)
+{
+    return weights == kRough ? (model == 0 ? 1.6 : 1.4) : weights == kBetween ? 1.25 : 1.0;
+}
+
+// Workgroups of 8 and 4 wavefronts leave the CU's issue slots to fewer of
+// them: an item of 8 (4) chains takes this share of the time of one of 16
+// (Potts L = 48: 42, 31 and 23 cycles per site; Ising L = 64: 23, 18 and 13).
+inline double tile_share(int chains) { return chains == 16 ? 1.0 : chains == 8 ? 0.75 : 0.55; }
+
+// Estimated length of a round on n_cus CUs.  side_by_side: the work that two
+// items on one CU do in the time of one alone, 1 where a CU holds one item.
+// They raise the throughput of rounds with more items than CUs; no item is
+// shorter for it.
+struct RoundLength {
+    double longest = 0.0, shortest = 0.0, total = 0.0;
+    long items = 0;
+    void add(long k, double t)
+    {
+        longest = t > longest ? t : longest;
+        shortest = items == 0 || t < shortest ? t : shortest;
+        total += (double)k * t;
+        items += k;
+    }
+    double estimate(int n_cus, double side_by_side) const
+    {
+        const long rounds = (items + n_cus - 1) / n_cus;
+        double len = total / ((double)n_cus * side_by_side); // all items spread evenly
+        if (items > n_cus) { // some CU takes at least `rounds` items
+            const double busiest = (double)rounds * shortest / side_by_side;
+            len = busiest > len ? busiest : len;
+        }
+        return longest > len ? longest : len;
+    }
+};
+
+// One run of a round.  In: its chains and the time of a full item at [four
+// lanes per chain, a wavefront per chain], < 0 where that kernel changed the
+// run's results when it was measured, and the table placement that each time
+// stands for (kept here for the caller).  Out: chains per item and an item's
+// time.
+struct RoundRun {
+    long chains;
+    double t[2];
+    bool table_in_lds[2];
+    int item_chains;
+    double cost;
+    long items(int per_item) const { return (chains + per_item - 1) / per_item; }
+};
+
+enum { kRoundFourLanes = 0, kRoundTiles = 1, kRoundTooManyItems = -1, kRoundNoKernel = -2 };
+
+// The kernel of a round (one for all its runs: the one with the shorter
+// estimate) and its items.  may4, may16: the caller's choice of kernels.  A
+// kernel that any run rejected is out, and so is one whose items exceed
+// max_items (counted in items of 64 or 16 chains); *n_items: the items of the
+// kernel that comes closest to fitting.
+inline int choose_round(RoundRun *runs, int n, bool may4, bool may16, int max_items, int n_cus, double side_by_side,
+                        long *n_items)
+{
+    RoundLength len4, len16;
+    for (int i = 0; i < n; ++i) {
+        may4 = may4 && runs[i].t[0] >= 0.0;
+        may16 = may16 && runs[i].t[1] >= 0.0;
+        len4.add(runs[i].items(kItemChains), runs[i].t[0]);
+        len16.add(runs[i].items(kTileItemChains), runs[i].t[1]);
+    }
+    if (!may4 && !may16)
+        return kRoundNoKernel;
+    *n_items = may4 ? len4.items : len16.items;
+    may4 = may4 && len4.items <= max_items;
+    may16 = may16 && len16.items <= max_items;
+    if (!may4 && !may16)
+        return kRoundTooManyItems;
+    if (may16) {
+        // no item longer than the longest run's in items of 16, 8 or 4
+        // chains; every run takes its largest items within that
+        auto chains_within = [&](int i, double limit) {
+            int c = kTileItemChains;
+            while (c > 4 && runs[i].t[1] * tile_share(c) > limit * 1.001)
+                c /= 2;
+            return c;
+        };
+        double best = -1.0, limit = len16.longest;
+        for (int c = kTileItemChains; c >= 4; c /= 2) {
+            RoundLength len;
+            for (int i = 0; i < n; ++i) {
+                const int k = chains_within(i, len16.longest * tile_share(c));
+                len.add(runs[i].items(k), runs[i].t[1] * tile_share(k));
+            }
+            const double est = len.estimate(n_cus, 1.0);
+            if (len.items <= max_items && (best < 0.0 || est < 0.999 * best))
+                best = est, limit = len16.longest * tile_share(c);
+        }
+        for (int i = 0; i < n; ++i) {
+            runs[i].item_chains = chains_within(i, limit);
+            runs[i].cost = runs[i].t[1] * tile_share(runs[i].item_chains);
+        }
+        if (!may4 || len4.estimate(n_cus, side_by_side) >= best)
+            return kRoundTiles;
+    }
+    for (int i = 0; i < n; ++i) {
+        runs[i].item_chains = kItemChains;
+        runs[i].cost = runs[i].t[0];
+    }
+    return kRoundFourLanes;
+}
+
 } // namespace muca

@@ -9,6 +9,7 @@
 //   tile <most> <n_chains> <cus>
 //   shapes
 //   probe <bins>
+//   round <may4> <may16> <max_items> <n_cus> <side_by_side> <n> (<chains> <t4> <t16>)[n]
 // Output: one line per case:
 //   segments: number of segments, their sum, shortest, longest, and the
 //     sweeps before the last one (it stops at 10^7 segments)
@@ -17,6 +18,7 @@
 //   tile: default_tile_chains
 //   shapes: lanes and threads of every entry of kTunedShapes
 //   probe: probe_lnw of every bin
+//   round: choose_round, then chains per item and item time of every run
 #include <algorithm>
 #include <cinttypes>
 #include <cstdio>
@@ -103,6 +105,25 @@ int main(int argc, char **argv)
             const int n = (int)get_int();
             for (int b = 0; b < n; ++b)
                 std::printf("%.17g ", muca::probe_lnw(b));
+            std::printf("\n");
+        } else if (!std::strcmp(kind, "round")) {
+            const bool may4 = get_int() != 0, may16 = get_int() != 0;
+            const int max_items = (int)get_int(), n_cus = (int)get_int();
+            const double side = get_double();
+            const int n = (int)get_int();
+            if (n < 1 || n > 4096)
+                fail("runs");
+            std::vector<muca::RoundRun> r((size_t)n);
+            for (muca::RoundRun &x : r) {
+                x = muca::RoundRun{};
+                x.chains = (long)get_int();
+                x.t[0] = get_double();
+                x.t[1] = get_double();
+            }
+            long items = 0;
+            std::printf("%d", muca::choose_round(r.data(), n, may4, may16, max_items, n_cus, side, &items));
+            for (const muca::RoundRun &x : r)
+                std::printf(" %d %.17g", x.item_chains, x.cost);
             std::printf("\n");
         } else {
             fail(kind);

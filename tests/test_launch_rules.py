@@ -111,3 +111,79 @@ def test_probe_weights(rules):
     assert np.array_equal(a, b) and np.all(np.abs(a) < 0.15)
     assert abs(a.mean()) < 5 * 0.15 / np.sqrt(3 * len(a)) and abs(a.std() - 0.15 / np.sqrt(3)) < 0.003
     assert abs(np.corrcoef(a[:-1], a[1:])[0, 1]) < 0.06
+
+
+def round_line(runs, may4=1, may16=1, max_items=4096, cus=256, side=1.0):
+    return f"round {may4} {may16} {max_items} {cus} {side} {len(runs)} " + " ".join("%d %r %r" % r for r in runs)
+
+
+def length(items, cus, side):
+    """Length of a round of (number of items, time of each)."""
+    n = sum(k for k, _ in items)
+    out = max([max(t for _, t in items), sum(k * t for k, t in items) / (cus * side)])
+    return max(out, -(-n // cus) * min(t for _, t in items) / side) if n > cus else out
+
+
+SHARE = {16: 1.0, 8: 0.75, 4: 0.55}
+
+
+def best_tiles(runs, max_items, cus):
+    """(estimate, chains per item) over the three item lengths of the longest run."""
+    longest = max(t for _, _, t in runs)
+    out = []
+    for c in (16, 8, 4):
+        within = [next(k for k in (16, 8, 4) if k == 4 or t * SHARE[k] <= 1.001 * longest * SHARE[c])
+                  for _, _, t in runs]
+        items = [(-(-n // k), t * SHARE[k]) for (n, _, t), k in zip(runs, within)]
+        if sum(k for k, _ in items) <= max_items:
+            out.append((length(items, cus, 1.0), within))
+    return out
+
+
+def test_no_item_is_shorter_for_sharing_its_cu(rules):
+    """12288 chains in 192 items of 64: each has a CU of its own, and the
+    round takes what one takes, whatever two do side by side."""
+    runs = [(12288, 110.0, 34.0)]
+    assert rules(round_line(runs, side=1.3))[0][0] == 1          # 3 rounds of 34 against 110
+    assert rules(round_line([(12288, 101.0, 34.0)], side=1.3))[0][0] == 0
+    assert rules(round_line([(512 * 64, 100.0, 20.0)], side=1.3))[0][0] == 0  # 154 against 160
+    assert rules(round_line([(512 * 64, 100.0, 20.0)], side=1.0))[0][0] == 1  # 200 against 160
+
+
+def test_a_kernel_that_any_run_rejected_is_not_taken(rules):
+    ok, no4, no16 = (640, 110.0, 34.0), (640, -1.0, 34.0), (640, 110.0, -1.0)
+    got = rules(round_line([ok, no4]), round_line([ok, no16]), round_line([no4, no16]),
+                round_line([ok, no4], max_items=70), round_line([ok, ok], max_items=70),
+                round_line([ok, ok], max_items=19), round_line([ok, no16], max_items=19),
+                round_line([ok], may4=0, max_items=39), round_line([ok], may4=0, max_items=40),
+                round_line([ok], may16=0))
+    assert [g[0] for g in got] == [1, 0, -2, -1, 0, -1, -1, -1, 1, 0]
+    assert got[1][1:] == [64, 110.0, 64, 110.0]
+
+
+def test_rounds_take_the_shorter_estimate(rules):
+    rng = np.random.default_rng(9)
+    cases = []
+    for _ in range(300):
+        n = int(rng.integers(1, 9))
+        runs = [(int(np.exp(rng.uniform(0, 10.5))), float(t), float(t * rng.uniform(0.1, 0.6)))
+                for t in np.exp(rng.uniform(0, 4, n))]
+        cases.append((runs, int(rng.choice([64, 512, 4096, 100000])), float(rng.choice([1.0, 1.3]))))
+    for (runs, max_items, side), got in zip(cases, rules(*(round_line(r, max_items=m, side=s) for r, m, s in cases))):
+        four = [(-(-n // 64), t) for n, t, _ in runs]
+        four = length(four, 256, side) if sum(k for k, _ in four) <= max_items else None
+        tiles = best_tiles(runs, max_items, 256) if sum(-(-n // 16) for n, _, _ in runs) <= max_items else []
+        if not tiles and four is None:
+            assert got[0] == -1
+            continue
+        best = min((e for e, _ in tiles), default=None)
+        if best is None or (four is not None and four < 0.999 * best):
+            assert got[0] == 0, (runs, max_items, side)
+        elif four is None or four > 1.001 * best:
+            assert got[0] == 1, (runs, max_items, side)
+        if got[0] == 1:  # an estimate within 0.1 % of the shortest
+            within = [int(k) for k in got[1::2]]
+            assert any(w == within and e <= 1.002 * best for e, w in tiles)
+            assert got[2::2] == pytest.approx([t * SHARE[k] for (_, _, t), k in zip(runs, within)])
+        else:
+            assert got[1:] == [v for _, t, _ in runs for v in (64, t)]
