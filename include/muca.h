@@ -328,9 +328,9 @@ int muca_batch_run_iteration_noalloc(muca_run *const *runs, int32_t n_runs, cons
  * 4 or 16 lanes per chain (64 or 16 chains per work item), and
  * the threshold table staged in LDS (where it fits) or read from global
  * memory.  Each probe runs the run's first work item for probe_sweeps sweeps
- * (0: about 5e4 site updates per chain) alone on the device; the run's
- * device state is saved before and restored after, so its results do not
- * change.  A candidate whose first 16 chains end in a different state than
+ * (0: about 5e4 site updates per chain) alone on the device, on
+ * weights about as uneven as those of a run in progress; the run's device
+ * state is saved before and restored after, so its results do not change.  A candidate whose first 16 chains end in a different state than
  * the first candidate's is rejected (counted in `rejected`).  Results are
  * read from / written to the JSON file named by MUCA_AUTOTUNE_CACHE (key:
  * architecture, class, the kernels' revision, and the number of chains up to

@@ -779,8 +779,15 @@ try {
         const int64_t sw = probe_sweeps ? probe_sweeps : std::max<int64_t>(1, (50000 + r->g.n_sites - 1) / r->g.n_sites);
         const size_t lds_budget = (size_t)std::min(lds_limit, 160 * 1024) - 256;
         const bool lds_fits = r->g.table_in_lds && r->g.lds_bytes <= lds_budget;
-        // the probes change the run's device state (the first item's chains,
-        // bins, histogram, accepted-move count): saved here, restored after each
+        // the probes change the run's device state (thresholds, the first
+        // item's chains, bins, histogram, accepted-move count): saved here,
+        // restored after each.  They run on uneven weights, whatever the
+        // run's own are: a tile's passes depend on them
+        std::vector<double> lnw(r->g.n_bins);
+        for (int b = 0; b < r->g.n_bins; ++b)
+            lnw[b] = probe_lnw(b);
+        std::vector<uint32_t> T((size_t)r->g.n_bins * r->g.n_cols);
+        muca_lattice_thresholds(r->g.model, r->cfg.beta, r->g.n_bins, r->g.n_cols, lnw.data(), T.data());
         std::vector<uint8_t> saved(r->g.ws_bytes);
         HIP_OR_POISON(r, hipStreamSynchronize(s));
         HIP_OR_POISON(r, hipMemcpy(saved.data(), r->ws, saved.size(), hipMemcpyDeviceToHost));
@@ -793,6 +800,8 @@ try {
         std::vector<int32_t> bins(nc);
         bool have_ref = false;
         uint64_t ref = 0;
+        if (e == hipSuccess)
+            e = hipMemcpy(r->d_table, T.data(), T.size() * 4u, hipMemcpyHostToDevice);
         if (e == hipSuccess) // loads the code and warms the caches: untimed
             e = probe_item(r, d_scratch, 16, lds_fits, sw, s, e0, e1, nullptr);
         for (int o = 0; o < 2 && e == hipSuccess; ++o)
@@ -800,6 +809,8 @@ try {
                 if (tl && !lds_fits)
                     continue;
                 e = hipMemcpy(r->ws, saved.data(), saved.size(), hipMemcpyHostToDevice);
+                if (e == hipSuccess)
+                    e = hipMemcpy(r->d_table, T.data(), T.size() * 4u, hipMemcpyHostToDevice);
                 float ms = 0.0f;
                 if (e == hipSuccess)
                     e = probe_item(r, d_scratch, o ? 16 : 4, tl != 0, sw, s, e0, e1, &ms);
