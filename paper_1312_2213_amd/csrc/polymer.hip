@@ -112,7 +112,8 @@ __device__ __forceinline__ double dist2d(double ax, double ay, double az, double
     return dx * dx + dy * dy + dz * dz;
 }
 
-// (x, y, z) = (nx, ny, nz) in the lanes of m; every lane of the wave is active
+// (x, y, z) = (nx, ny, nz) in the lanes of m; every lane of the wave is active.
+// Each output is written before the next input is read: none may share a register.
 __device__ __forceinline__ void set_bead(uint64_t m, double &x, double &y, double &z, double nx, double ny, double nz)
 {
     asm volatile("s_mov_b64 exec, %3\n\t"
@@ -120,7 +121,7 @@ __device__ __forceinline__ void set_bead(uint64_t m, double &x, double &y, doubl
         "v_mov_b64 %1, %5\n\t"
         "v_mov_b64 %2, %6\n\t"
         "s_mov_b64 exec, -1"
-        : "+v"(x), "+v"(y), "+v"(z)
+        : "+&v"(x), "+&v"(y), "+&v"(z)
         : "s"(m), "v"(nx), "v"(ny), "v"(nz));
 }
 
