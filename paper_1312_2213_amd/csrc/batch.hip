@@ -380,7 +380,7 @@ static RoundRun round_run(const muca_run *r, int64_t sweeps, bool tuned)
             x.table_in_lds[o] = true;
         }
         if (o)
-            best *= tile_slowdown(r->g.model, r->weights);
+            best *= tile_slowdown(r->g.model, muca_weights_class(r));
         x.t[o] = best < 0.0 ? -1.0 : best * (double)sweeps;
     }
     return x;

@@ -292,10 +292,8 @@ int muca_rebuild_thresholds(muca_run *r)
         const int rc = muca_polymer_build(r);
         if (rc || r->T.empty())
             return rc;
-    } else {
+    } else
         muca_lattice_thresholds(r->g.model, r->cfg.beta, r->g.n_bins, r->g.n_cols, r->lnW.data(), r->T.data());
-        r->weights = weights_class(r->g.model, weights_noise(r->g.n_bins, r->P.data()));
-    }
     return muca_upload_thresholds(r);
 }
 
@@ -437,13 +435,19 @@ try {
 }
 MUCA_ABI_CATCH
 
+int muca_weights_class(const muca_run *r) { return weights_class(r->g.model, weights_noise(r->g.n_bins, r->P.data())); }
+
 // Whether the run's next plain launch takes one wavefront per chain.
 static bool takes_tiles(const muca_run *r)
 {
     const Geometry &g = r->g;
     if (g.model == kPolymer || r->cfg.lanes_per_chain != 0)
         return g.model != kPolymer && r->cfg.lanes_per_chain == 16;
-    return (long)g.c_pad <= tile_max_chains(g.model, g.L, g.table_in_lds, r->weights);
+    const long n = g.c_pad;
+    if (n <= tile_max_chains(g.model, g.L, g.table_in_lds, kRough)) // no line is lower
+        return true;
+    return n <= tile_max_chains(g.model, g.L, g.table_in_lds, kSettled) &&
+           n <= tile_max_chains(g.model, g.L, g.table_in_lds, muca_weights_class(r));
 }
 
 int muca_enqueue_sweeps(muca_run *r, int64_t sweeps, bool record, hipStream_t s, unsigned long long *em,
@@ -1144,8 +1148,6 @@ try {
     r->lnW = lnW;
     r->lnR = lnR;
     r->P = P;
-    if (r->g.model != kPolymer)
-        r->weights = weights_class(r->g.model, weights_noise(r->g.n_bins, r->P.data()));
     r->mask = mask;
     if (!r->T.empty()) // else the table is in the workspace just restored
         std::copy(T.begin(), T.end(), r->T.begin());

@@ -81,7 +81,6 @@ struct muca_run {
     int64_t iteration = 0;
     int64_t pending = 0;           // recorded sweeps since the last merge
     bool have_last = false;
-    int weights = muca::kSettled;  // lattice: class of the weights' noise
     bool poisoned = false;
     // pinned host staging: the histogram and accepted-move count read back at
     // a merge, and its device-side address
@@ -162,6 +161,8 @@ int muca_polymer_init(muca_run *r, const float *h_pos);
 // which the caller uploads); the caller has synchronised the run's stream.
 int muca_polymer_build(muca_run *r);
 int64_t muca_table_size(const muca_run *r);
+// Class of the noise of a lattice run's weights (launch_rules.h).
+int muca_weights_class(const muca_run *r);
 // queues the upload of the host threshold mirror on the run's stream
 int muca_upload_thresholds(muca_run *r);
 int muca_polymer_enqueue(muca_run *r, int64_t sweeps, bool record, hipStream_t s);

@@ -44,11 +44,13 @@ def test_segments_cover_every_sweep_count(rules, total, at_most):
 
 
 def test_noise_of_the_weights(rules):
-    """The mean error P^-1/2 of the measured links, at most 1 each."""
+    """The mean error P^-1/2 of the measured links, at most 1 each, over at
+    most 1024 evenly spaced ones."""
     rng = np.random.default_rng(5)
-    for n in (0, 1, 2, 65, 4097):
+    for n in (0, 1, 2, 65, 1024, 1025, 4097, 8193):
         P = np.exp(rng.uniform(-5, 15, n)) * (rng.random(n) < 0.7)
-        want = np.minimum(1.0, P[P > 0] ** -0.5).mean() if (P > 0).any() else 0.0
+        Q = P[::max(1, -(-n // 1024))]
+        want = np.minimum(1.0, Q[Q > 0] ** -0.5).mean() if (Q > 0).any() else 0.0
         got = rules(f"noise {n} " + " ".join(float(p).hex() for p in P))[0][0]
         assert abs(got - want) <= 1e-12 * max(1.0, want), n
 
@@ -87,7 +89,7 @@ def test_no_line_below_the_chains_that_take_16_lanes(rules):
     for (m, L, s, noise), line in lines.items():
         if m != 1 or L % 16 == 0:
             assert line >= 4096, (m, L, s, noise)
-        assert line <= lines[(m, L, s, 0.0)]
+        assert lines[(m, L, s, 1.0)] <= line <= lines[(m, L, s, 0.0)]
 
 
 def test_autotuner_times_every_default_workgroup(rules):
