@@ -42,7 +42,7 @@ uint32_t muca_threshold_of(double D)
     const double v = std::exp(D) * 4294967296.0; // times 2^32: exact
     if (v >= 4294967295.0)
         return 0xffffffffu;
-    return (uint32_t)std::floor(v);
+    return (uint32_t)v; // v >= 0: truncation is floor
 }
 
 void muca_lattice_thresholds(int model, double beta, int n_bins, int n_cols, const double *lnW, uint32_t *T)
