@@ -28,15 +28,18 @@
 // during a launch: lane t holds tile t as a 64-bit mask (Ising, MUMA), or
 // lane i holds its site's colour of every tile, four per register (Potts).
 //
-// Bound: instruction issue with four wavefronts per SIMD (Ising: scalar and
-// vector units about even, 107 instructions per tile of 64; Potts: vector),
-// latency (LDS reads, the scalar chain) below that.  Measured per iteration,
-// before (16 lanes per chain, site by site) and after: Ising L = 64, 4096
-// chains, 400 sweeps 54.5 -> 17.6 ms; Ising L = 32 int8, 1000 chains, 35
-// sweeps 1.69 -> 0.32 ms; MUMA L = 32 with the joint histogram, 512 chains,
-// 67 sweeps 2.85 -> 0.49 ms; Potts q = 8 L = 48, 2048 chains, 362 sweeps
-// 39.4 -> 10.9 ms; Potts q = 10 L = 64 (table in global memory), 1024 chains,
-// 60 sweeps 14.4 -> 2.8 ms.
+// Bound, by SQ counters on weights of runs in progress.  Four wavefronts per
+// SIMD: the vector unit is busy 63 to 75 % of the cycles and the scalar unit
+// 55 % (Ising L = 64, 4096 chains: 68 vector, 59 scalar and 3 LDS
+// instructions per tile of 64), the rest are waits between dependent
+// instructions of all four.  Two: 59 % (Potts L = 48, 2048 chains: 118, 36 and
+// 7 per tile of 48).  One or fewer: a tile is one chain of LDS reads, ballots
+// and scalar operations.  Measured per iteration, before (16 lanes per chain,
+// site by site) and after: Ising L = 64, 4096 chains, 400 sweeps 54.5 -> 17.6
+// ms; Ising L = 32 int8, 1000 chains, 35 sweeps 1.69 -> 0.32 ms; MUMA L = 32
+// with the joint histogram, 512 chains, 67 sweeps 2.85 -> 0.49 ms; Potts q = 8
+// L = 48, 2048 chains, 362 sweeps 39.4 -> 10.9 ms; Potts q = 10 L = 64 (table
+// in global memory), 1024 chains, 60 sweeps 14.4 -> 2.8 ms.
 #pragma once
 #include "lattice_impl.h"
 #include "launch_rules.h"

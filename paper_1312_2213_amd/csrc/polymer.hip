@@ -329,9 +329,10 @@ __device__ __forceinline__ bool lane_bit(uint64_t mask) { return __builtin_amdgc
 // broadcast, bond changes wait in the lanes that add them, lanes of a move
 // are scalar masks shifted along the chain, cache addresses are stepped), and
 // two moves share the chain: their pair terms overlap, and tree, bins,
-// thresholds and decisions are paid once.  About 75 vector instructions a
-// shift, where single moves took 96 and lane reads, masks from comparisons
-// and 64-bit addresses 142.  Moves/s, with those / single moves / pairs:
+// thresholds and decisions are paid once.  82 vector instructions a shift,
+// the sweep's own shared out (counted at N = 40, 4096 chains: vector unit
+// busy 77 % of the cycles), where single moves took 96 and lane reads, masks
+// from comparisons and 64-bit addresses 142.  Moves/s, with those / single moves / pairs:
 //   N = 40, 4096 chains, shifts    3.1e9 / 4.4e9 / 4.6e9    full set  1.5e9 / 2.5e9 / 2.6e9
 //   N = 40,  512 chains, shifts    9.3e8 / 1.1e9 / 1.4e9
 //   N = 80, 4096 chains, shifts    1.9e9 / 2.7e9 / 2.6e9    full set  1.15e9 / 1.8e9 / 1.9e9
