@@ -279,13 +279,13 @@ int muca_reweight_em(const muca_run *run, const uint64_t *h_em, int64_t n_em, co
  *   muca_batch_workspace_bytes: device bytes for up to max_runs runs and
  *     max_items work items (two staging areas, used by alternate rounds).
  *   muca_batch_create: lanes_per_chain 4 or 16 (a wavefront per chain) for
- *     every run, or 0 to choose per launch: 16 where the items fit max_items
- *     (see muca_batch_tune for runs whose item times were measured), in
- *     smaller items while every item has a compute unit of its own.  use_graph != 0 captures [descriptor
- *     upload, queue reset, persistent kernel] in a hipGraph once per staging
- *     area and relaunches it (requires a non-null stream).  d_ws is
- *     caller-owned (256-byte aligned); the handle owns two small pinned host
- *     buffers.
+ *     every run, or 0 to choose per launch the one that fits max_items with
+ *     the shorter estimate of the round (see muca_batch_tune for runs whose
+ *     item times were measured; 16: in items of 16, 8 or 4 chains).
+ *     use_graph != 0 captures [descriptor upload, queue reset, persistent
+ *     kernel] in a hipGraph once per staging area and relaunches it (requires
+ *     a non-null stream).  d_ws is caller-owned (256-byte aligned); the handle
+ *     owns two small pinned host buffers.
  *   muca_batch_run_iteration: equivalent to muca_run_iteration(runs[i],
  *     sweeps[i]) for every i; returns once the launch is enqueued.  Rounds
  *     alternate between two staging areas, each fenced by an event, so the

@@ -9,7 +9,7 @@ def test_workgroups_of_eight_chains(monkeypatch):
     the CUs idle, four make two rounds; eight are 1.3 times as fast."""
     from paper_1312_2213_amd import muca
     monkeypatch.delenv("MUCA_AUTOTUNE_CACHE", raising=False)
-    best, _ = muca.muca_autotune(muca.muca_config_default("potts", 48, 8, 2048, 3), 10)
+    best, _ = muca.muca_autotune(muca.muca_config_default("potts", 48, 8, 2048, 3), 60)
     assert (best.lanes_per_chain, best.chains_per_block) == (16, 8)
 
 
@@ -19,7 +19,7 @@ def test_candidates_are_timed_on_weights_that_move(monkeypatch):
     as long as four lanes per chain."""
     from paper_1312_2213_amd import muca
     monkeypatch.delenv("MUCA_AUTOTUNE_CACHE", raising=False)
-    best, _ = muca.muca_autotune(muca.muca_config_default("ising", 32, 2, 16384, 3, layout=muca.MUCA_LAYOUT_BIT), 20)
+    best, _ = muca.muca_autotune(muca.muca_config_default("ising", 32, 2, 16384, 3, layout=muca.MUCA_LAYOUT_BIT), 60)
     assert best.lanes_per_chain == 4
 
 
